@@ -631,50 +631,63 @@ struct dgdft_alb {
     HCHECK(hipGetLastError());
   }
 
-  // The eigensolver of the Rayleigh-Ritz step: dg_rr_eig (orders up to 512,
-  // one 1024-lane workgroup per element) and, when some element's order is
-  // 513..832, for those elements the tridiagonalisation over TRI_NWG
-  // workgroups each (dg_tri_step, one launch per Householder step) and
-  // dg_rr_eig_wide_rest (inside graph capture the single-workgroup
-  // dg_rr_eig_wide instead); each skips the other's elements.  Outside graph
-  // capture dg_rr_eig runs on the group's second stream beside the others.
+  // The stages of eig_split.h after the tridiagonalisation, for `count`
+  // matrices of orders up to nmax, at most kmax eigenpairs each.
+  static void eig_stages(const EigSrc& src, int count, int nmax, int kmax, hipStream_t s) {
+    if (nmax < 1 || count < 1) return;
+    const int pb = cdiv(kmax, EIG_BIS_COLS), pi = cdiv(kmax, EIG_INV_COLS), pt = cdiv(kmax, EIG_BT_COLS);
+    const size_t nd = sizeof(double) * nmax;
+    hipLaunchKernelGGL(dg_eig_bisect, dim3(count * pb), dim3(EIG_BIS_THREADS), 2 * nd, s, src, pb);
+    hipLaunchKernelGGL(dg_eig_invit, dim3(count * pi), dim3(EIG_INV_COLS), 2 * nd + sizeof(double) * EIG_INV_TILE,
+                       s, src, pi);
+    hipLaunchKernelGGL(dg_eig_cluster, dim3(count), dim3(EIG_CL_THREADS), 2 * nd, s, src);
+    hipLaunchKernelGGL(dg_eig_back, dim3(count * pt), dim3(EIG_BT_THREADS), EIG_BT_NB * (nd + sizeof(double)), s,
+                       src, pt);
+    HCHECK(hipGetLastError());
+  }
+
+  // The eigensolver of the Rayleigh-Ritz step (see lobpcg.hip).  Outside graph
+  // capture the one-workgroup tridiagonalisations of orders up to 512 run on
+  // the group's second stream beside the per-step launches of the wide ones.
   void rr_eig_pair(const std::vector<int>& act, int single) {
-    bool wide = false;
-    for (int e : act) wide = wide || eig_wide((single ? 1 : (hasP_host(e) ? 3 : 2)) * eh[e].J);
-    if (!wide || capturing) {
-      rr_one(act, dg_rr_eig, SMALL_THREADS, single);
-      if (wide) rr_one(act, dg_rr_eig_wide, EIG_WIDE_THREADS, single);
-      return;
-    }
-    auto P = make_prefix(act, [&](int) { return 1; });   // copied on the group's stream
-    HCHECK(hipEventRecord(g_fork[cur_g], stream));
-    HCHECK(hipStreamWaitEvent(g_aux[cur_g], g_fork[cur_g], 0));
-    hipStream_t main = stream;
-    stream = g_aux[cur_g];
-    pbeg(DGDFT_K_RR, 0, 0);
-    hipLaunchKernelGGL(dg_rr_eig, dim3(P.na), dim3(SMALL_THREADS), 0, stream, ed, P.active, P.na, single);
-    pend();
-    HCHECK(hipGetLastError());
-    HCHECK(hipEventRecord(g_auxdone[cur_g], stream));
-    stream = main;
-    // orders 513..832: the tridiagonalisation over TRI_NWG workgroups per
-    // element, one launch per Householder step up to the largest order an
-    // element can have (3 J, or J on X alone; an element past its own order
-    // returns at once), then the rest of the eigensolver
-    int nmax = 0;
+    int nmax = 0, kmax = 0, wmax = 0;
+    bool small = false, large = false;
     for (int e : act) {
-      const int nb = (single ? 1 : 3) * eh[e].J;
-      if (nb >= EIG_WIDE_MIN) nmax = std::max(nmax, std::min(nb, EIG_WIDE_MAX));
+      const int n = (single ? 1 : (hasP_host(e) ? 3 : 2)) * eh[e].J;
+      if (n > EIG_MAXN) { large = true; continue; }
+      nmax = std::max(nmax, n);
+      kmax = std::max(kmax, eh[e].J);
+      if (eig_wide(n)) wmax = std::max(wmax, n); else small = true;
+      // inside a captured graph an element may lose its P block (n = 2 J)
+      if (!single && capturing && 2 * eh[e].J < EIG_WIDE_MIN) small = true;
     }
+    auto P = make_prefix(act, [&](int) { return 1; });
+    EigSrc src{};
+    src.E = ed;
+    src.active = P.active;
+    src.single = single;
     pbeg(DGDFT_K_RR, 0, 0);
-    for (int k = 0; k + 2 <= nmax; ++k)
-      hipLaunchKernelGGL(dg_tri_step, dim3(P.na * TRI_NWG), dim3(TRI_STEP_THREADS), 0, stream, ed,
-                         P.active, P.na, single, k);
-    hipLaunchKernelGGL(dg_rr_eig_wide_rest, dim3(P.na), dim3(EIG_WIDE_THREADS), 0, stream, ed, P.active,
-                       P.na, single);
-    pend();
+    const bool fork = wmax > 0 && small && !capturing;
+    hipStream_t ts = stream;
+    if (fork) {
+      ts = g_aux[cur_g];
+      HCHECK(hipEventRecord(g_fork[cur_g], stream));
+      HCHECK(hipStreamWaitEvent(ts, g_fork[cur_g], 0));
+    }
+    if (small)
+      hipLaunchKernelGGL(dg_rr_tri, dim3(P.na), dim3(SMALL_THREADS), 0, ts, ed, P.active, P.na, single);
+    if (fork) HCHECK(hipEventRecord(g_auxdone[cur_g], ts));
+    if (wmax > 0 && capturing)
+      hipLaunchKernelGGL(dg_rr_tri_wide, dim3(P.na), dim3(SMALL_THREADS), 0, stream, ed, P.active, P.na, single);
+    else
+      for (int k = 0; k + 2 <= wmax; ++k)
+        hipLaunchKernelGGL(dg_tri_step, dim3(P.na * TRI_NWG), dim3(TRI_STEP_THREADS), 0, stream, src, k);
+    if (large)
+      hipLaunchKernelGGL(dg_rr_eig_large, dim3(P.na), dim3(SMALL_THREADS), 0, stream, ed, P.active, P.na, single);
     HCHECK(hipGetLastError());
-    HCHECK(hipStreamWaitEvent(stream, g_auxdone[cur_g], 0));
+    if (fork) HCHECK(hipStreamWaitEvent(stream, g_auxdone[cur_g], 0));
+    eig_stages(src, P.na, nmax, kmax, stream);
+    pend();
   }
 
   // Rayleigh-Ritz step (see lobpcg.hip): per-element factorisations and
@@ -854,8 +867,18 @@ struct dgdft_alb {
         hipLaunchKernelGGL(dg_advance, dim3(cdiv(P.na, 256)), dim3(256), 0, stream, ed, P.active, P.na);
         break;
       case 4:
-        hipLaunchKernelGGL(dg_alb_coeffs, dim3(P.na), dim3(SMALL_THREADS), 0, stream, ed, P.active,
-                           P.na, out);
+        hipLaunchKernelGGL(dg_alb_tri, dim3(P.na), dim3(SMALL_THREADS), 0, stream, ed, P.active, P.na);
+        {
+          EigSrc src{};
+          src.kind = 1;
+          src.E = ed;
+          src.active = P.active;
+          int nmax = 0, kmax = 0;
+          for (int e : act)
+            if (eh[e].J <= EIG_MAXN) { nmax = std::max(nmax, eh[e].J); kmax = std::max(kmax, eh[e].nalb); }
+          eig_stages(src, P.na, nmax, kmax, stream);
+        }
+        hipLaunchKernelGGL(dg_alb_coeffs, dim3(P.na), dim3(256), 0, stream, ed, P.active, P.na, out);
         break;
     }
     pend();
@@ -2281,9 +2304,7 @@ struct TmpDev {
 
 // Workspace doubles of the batched eigensolver per matrix (its matrix copy,
 // eigenvector accumulator, vectors and inverse-iteration work).
-static size_t syev_work_doubles(int n, int k) {
-  return 2 * (size_t)n * n + 8 * (size_t)n + 6 * (size_t)n * k;
-}
+static size_t syev_work_doubles(int n, int k) { return (size_t)syev_stride(n, k); }
 
 static bool syev_args_ok(int32_t count, int32_t n, int32_t k, const double* A, const double* w,
                          const double* Z, int32_t method) {
@@ -2293,12 +2314,22 @@ static bool syev_args_ok(int32_t count, int32_t n, int32_t k, const double* A, c
 
 static void launch_syev(int32_t count, int32_t n, int32_t k, const double* A, double* w, double* Z,
                         int32_t method, double* work, hipStream_t s) {
-  if (method == 0 && eig_wide(n)) {
-    hipLaunchKernelGGL(dg_syev_batch_copy, dim3(count), dim3(256), 0, s, A, n, k, work);
-    for (int st = 0; st + 2 <= n; ++st)
-      hipLaunchKernelGGL(dg_tri_step_batch, dim3(count * TRI_NWG), dim3(TRI_STEP_THREADS), 0, s, n, k, work,
-                         st);
-    hipLaunchKernelGGL(dg_syev_batch_wide_rest, dim3(count), dim3(EIG_WIDE_THREADS), 0, s, w, Z, n, k, work);
+  if (method == 0 && n <= EIG_MAXN) {
+    const int nb = cdiv(n, SYEV_COPY_TILE);
+    EigSrc src{};
+    src.kind = 2;
+    src.work = work;
+    src.w = w;
+    src.Z = Z;
+    src.n = n;
+    src.k = k;
+    hipLaunchKernelGGL(dg_syev_batch_copy, dim3((unsigned)count * nb * nb), dim3(256), 0, s, A, n, k, work);
+    if (eig_wide(n))
+      for (int st = 0; st + 2 <= n; ++st)
+        hipLaunchKernelGGL(dg_tri_step, dim3(count * TRI_NWG), dim3(TRI_STEP_THREADS), 0, s, src, st);
+    else
+      hipLaunchKernelGGL(dg_syev_batch_tri, dim3(count), dim3(SMALL_THREADS), 0, s, n, k, work);
+    dgdft_alb::eig_stages(src, count, n, k, s);
   } else
     hipLaunchKernelGGL(dg_syev_batch, dim3(count), dim3(SMALL_THREADS), 0, s, A, w, Z, n, k, work,
                        method);

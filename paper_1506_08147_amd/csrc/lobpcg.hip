@@ -9,6 +9,7 @@
 // cooperative routines of small_dense.h, all FP64.
 #include "common.h"
 #include "small_dense.h"
+#include "eig_split.h"
 
 namespace dg {
 
@@ -321,71 +322,135 @@ dg_carry_in(Elem* __restrict__ E, const int* __restrict__ active, int na) {
   }
 }
 
-// Matrices of order EIG_WIDE_MIN..EIG_WIDE_MAX go to the wide path: the
-// one-pass tridiagonalisation on four row groups (dg_rr_eig_wide) or over
-// TRI_NWG workgroups per matrix (dg_tri_step), and a back-transformation
-// with 13 rows per lane, on 1024-lane workgroups.
+// The eigensolver of the Rayleigh-Ritz step: tridiagonalisation, then the
+// stages of eig_split.h, for orders up to EIG_MAXN; larger orders stay in one
+// workgroup (dg_rr_eig_large).  Tridiagonalisation: one workgroup per element
+// up to order 512 (dg_rr_tri), over TRI_NWG workgroups per element with one
+// launch per Householder step for EIG_WIDE_MIN..EIG_MAXN (dg_tri_step; one
+// workgroup, dg_rr_tri_wide, inside graph capture).
 constexpr int EIG_WIDE_MIN = 513;
-constexpr int EIG_WIDE_MAX = 832;
-constexpr int EIG_WIDE_THREADS = 1024;
 
-__host__ __device__ inline bool eig_wide(int n) { return n >= EIG_WIDE_MIN && n <= EIG_WIDE_MAX; }
+__host__ __device__ inline bool eig_wide(int n) { return n >= EIG_WIDE_MIN && n <= EIG_MAXN; }
 
-template <bool WIDE, bool PRE = false>
-__device__ __forceinline__ void rr_eig_body(Elem* __restrict__ E, const int* __restrict__ active,
+// Where the matrices of a batch are: the Rayleigh-Ritz matrices of elements
+// (kind 0), the restricted Grams of elements (1), or a plain batch (2: copies
+// and workspaces of dgdft_small_syev).
+struct EigSrc {
+  int kind;
+  const Elem* E;
+  const int* active;
+  int single;
+  double *work, *w, *Z;
+  int n, k;
+};
+
+__host__ __device__ inline long long syev_stride(int n, int k) { return 2LL * n * n + 8LL * n + 6LL * n * k; }
+
+__device__ __forceinline__ EigView eig_view(const EigSrc& s, int b) {
+  EigView m{};
+  if (s.kind == 2) {
+    m.n = s.n;
+    m.k = s.k;
+    m.A = s.work + b * syev_stride(s.n, s.k);
+    m.work = m.A + (long long)s.n * s.n;
+    m.w = s.w + (long long)b * s.n;
+    m.Z = s.Z + (long long)b * s.n * s.k;
+    return m;
+  }
+  const Elem& e = s.E[s.active[b]];
+  const int n = (s.kind == 1 || s.single ? 1 : (has_p(e) ? 3 : 2)) * e.J;
+  if ((s.kind == 0 && e.fl[FL_RR_PATH] == 1) || n > EIG_MAXN) return m;
+  m.n = n;
+  m.k = s.kind == 1 ? e.nalb : e.J;
+  m.A = sm(e, SM_A);
+  m.Z = sm(e, SM_Z);
+  m.w = sm(e, SM_V) + 7 * n;
+  m.work = sm(e, SM_W0);       // and SM_W1, which follows it
+  return m;
+}
+
+// Stage kernels: `per` workgroups per matrix (the largest of the batch needs
+// them all), 2 nmax doubles of LDS and what the stage adds.
+extern "C" __global__ void __launch_bounds__(EIG_BIS_THREADS)
+dg_eig_bisect(EigSrc s, int per) {
+  extern __shared__ double dyn[];
+  __shared__ double red[32];
+  eig_bisect_body(eig_view(s, blockIdx.x / per), blockIdx.x % per, dyn, red);
+}
+
+extern "C" __global__ void __launch_bounds__(EIG_INV_COLS)
+dg_eig_invit(EigSrc s, int per) {
+  extern __shared__ double dyn[];
+  __shared__ double red[32];
+  eig_invit_body(eig_view(s, blockIdx.x / per), blockIdx.x % per, dyn, red);
+}
+
+extern "C" __global__ void __launch_bounds__(EIG_CL_THREADS)
+dg_eig_cluster(EigSrc s) {
+  extern __shared__ double dyn[];
+  __shared__ double red[32];
+  eig_cluster_body(eig_view(s, blockIdx.x), dyn, red);
+}
+
+extern "C" __global__ void __launch_bounds__(EIG_BT_THREADS)
+dg_eig_back(EigSrc s, int per) {
+  extern __shared__ double dyn[];
+  eig_back_any(eig_view(s, blockIdx.x / per), blockIdx.x % per, dyn);
+}
+
+template <bool WIDE>
+__device__ __forceinline__ void rr_tri_body(Elem* __restrict__ E, const int* __restrict__ active,
                                             int single, double* red, double* lds) {
   DevTeam t{red};
   const Elem& e = E[active[blockIdx.x]];
   if (e.fl[FL_RR_PATH] == 1) return;
-  const int J = e.J;
-  const int kb = single ? 1 : (has_p(e) ? 3 : 2);
-  const int n = kb * J;
-  if (eig_wide(n) != WIDE) return;   // the other kernel's element
-  double* A = sm(e, SM_A);
-  double* Z = sm(e, SM_Z);
-  double* vec = sm(e, SM_V);
-  double* w = vec + 7 * n;
-  // workspace: SM_W0 and SM_W1 (consecutive)
-  syev_lowest<WIDE, PRE>(t, A, n, n, J, w, Z, n, sm(e, SM_W0), (int*)(vec + 10 * n), lds, EIG_LDS);
+  const int n = (single ? 1 : (has_p(e) ? 3 : 2)) * e.J;
+  if (n > EIG_MAXN || eig_wide(n) != WIDE) return;   // another kernel's element
+  double* work = sm(e, SM_W0);
+  tridiagonalize_lower<WIDE>(t, sm(e, SM_A), n, n, work, work + n, work + 2 * n, lds, lds + n, lds + 2 * n,
+                             EIG_LDS - 2 * n);
 }
 
 extern "C" __global__ void __launch_bounds__(SMALL_THREADS)
-dg_rr_eig(Elem* __restrict__ E, const int* __restrict__ active, int na, int single) {
+dg_rr_tri(Elem* __restrict__ E, const int* __restrict__ active, int na, int single) {
   __shared__ double red[32];
   __shared__ double lds[EIG_LDS];
-  rr_eig_body<false>(E, active, single, red, lds);
+  rr_tri_body<false>(E, active, single, red, lds);
 }
 
-extern "C" __global__ void __launch_bounds__(EIG_WIDE_THREADS)
-dg_rr_eig_wide(Elem* __restrict__ E, const int* __restrict__ active, int na, int single) {
+extern "C" __global__ void __launch_bounds__(SMALL_THREADS)
+dg_rr_tri_wide(Elem* __restrict__ E, const int* __restrict__ active, int na, int single) {
   __shared__ double red[32];
   __shared__ double lds[EIG_LDS];
-  rr_eig_body<true>(E, active, single, red, lds);
+  rr_tri_body<true>(E, active, single, red, lds);
 }
 
-// The tridiagonalisation of the dg_rr_eig_wide elements spread over TRI_NWG
-// workgroups each, one launch per Householder step k (see tri_step), and the
-// rest of their eigensolver after it.
-constexpr int TRI_STEP_LDS = 4 * EIG_WIDE_MAX + 4 * (EIG_WIDE_MAX / TRI_NWG + 1);
+// Orders above EIG_MAXN: the whole eigensolver in one workgroup.
+extern "C" __global__ void __launch_bounds__(SMALL_THREADS)
+dg_rr_eig_large(Elem* __restrict__ E, const int* __restrict__ active, int na, int single) {
+  __shared__ double red[32];
+  __shared__ double lds[EIG_LDS];
+  DevTeam t{red};
+  const Elem& e = E[active[blockIdx.x]];
+  if (e.fl[FL_RR_PATH] == 1) return;
+  const int n = (single ? 1 : (has_p(e) ? 3 : 2)) * e.J;
+  if (n <= EIG_MAXN) return;
+  double* vec = sm(e, SM_V);
+  syev_lowest(t, sm(e, SM_A), n, n, e.J, vec + 7 * n, sm(e, SM_Z), n, sm(e, SM_W0), (int*)(vec + 10 * n), lds,
+              EIG_LDS);
+}
+
+constexpr int TRI_STEP_LDS = 4 * EIG_MAXN + 4 * (EIG_MAXN / TRI_NWG + 1);
 
 extern "C" __global__ void __launch_bounds__(TRI_STEP_THREADS)
-dg_tri_step(Elem* __restrict__ E, const int* __restrict__ active, int na, int single, int k) {
+dg_tri_step(EigSrc s, int k) {
   __shared__ double red[32];
   __shared__ double lds[TRI_STEP_LDS];
   DevTeam t{red};
-  const int ai = blockIdx.x / TRI_NWG, w = blockIdx.x - ai * TRI_NWG;
-  const Elem& e = E[active[ai]];
-  if (e.fl[FL_RR_PATH] == 1) return;
-  const int n = (single ? 1 : (has_p(e) ? 3 : 2)) * e.J;
-  if (!eig_wide(n)) return;
-  tri_step(t, sm(e, SM_A), n, n, k, w, sm(e, SM_W0), lds);
-}
-
-extern "C" __global__ void __launch_bounds__(EIG_WIDE_THREADS)
-dg_rr_eig_wide_rest(Elem* __restrict__ E, const int* __restrict__ active, int na, int single) {
-  __shared__ double red[32];
-  __shared__ double lds[EIG_LDS];
-  rr_eig_body<true, true>(E, active, single, red, lds);
+  const int b = blockIdx.x / TRI_NWG;
+  const EigView m = eig_view(s, b);
+  if (!eig_wide(m.n)) return;
+  tri_step(t, m.A, m.n, m.n, k, blockIdx.x - b * TRI_NWG, m.work, lds);
 }
 
 // Path 3: T = I - E/2 + 3 E^2/8 - 5 E^3/16 from E (SM_L), E^2 (SM_U) and
@@ -695,32 +760,43 @@ dg_gather_box(Elem* __restrict__ E, const int* __restrict__ active, const int* _
 // sigma (descending) and T = V S^-1 / sqrt(dV) (J x n_alb, SM_T), so that
 // Psi_E T are the ALBs in the dV sum phi^2 = 1 normalisation.  The n_alb
 // largest eigenpairs of G are the lowest of -G, from the Rayleigh-Ritz
-// eigensolver (tridiagonalisation, multisection and inverse iteration).
+// eigensolver: tridiagonalisation here, then the stages of eig_split.h (or
+// all of it here above order EIG_MAXN), then dg_alb_coeffs.
 extern "C" __global__ void __launch_bounds__(SMALL_THREADS)
-dg_alb_coeffs(Elem* __restrict__ E, const int* __restrict__ active, int na, double* sigma) {
+dg_alb_tri(Elem* __restrict__ E, const int* __restrict__ active, int na) {
   __shared__ double red[32];
   __shared__ double lds[EIG_LDS];
   DevTeam t{red};
   const Elem& e = E[active[blockIdx.x]];
-  const int n = e.J, na_ = e.nalb;
+  const int n = e.J;
   double* G = sm(e, SM_G);
   double* A = sm(e, SM_A);
-  double* Z = sm(e, SM_Z);
   double* vec = sm(e, SM_V);
-  double* w = vec + 7 * n;
+  double* work = sm(e, SM_W0);
   sym_from_upper(t, G, n, n);
   for (int p = t.tid(); p < n * n; p += t.nt()) A[p] = -G[p];
   t.sync();
-  syev_lowest<false>(t, A, n, n, na_, w, Z, n, sm(e, SM_W0), (int*)(vec + 10 * n), lds, EIG_LDS);
+  if (n > EIG_MAXN)
+    syev_lowest(t, A, n, n, e.nalb, vec + 7 * n, sm(e, SM_Z), n, work, (int*)(vec + 10 * n), lds, EIG_LDS);
+  else
+    tridiagonalize_lower<false>(t, A, n, n, work, work + n, work + 2 * n, lds, lds + n, lds + 2 * n,
+                                EIG_LDS - 2 * n);
+}
+
+extern "C" __global__ void __launch_bounds__(256)
+dg_alb_coeffs(Elem* __restrict__ E, const int* __restrict__ active, int na, double* sigma) {
+  const Elem& e = E[active[blockIdx.x]];
+  const int n = e.J, na_ = e.nalb;
+  const double* Z = sm(e, SM_Z);
+  const double* w = sm(e, SM_V) + 7 * n;
   double* Tm = sm(e, SM_T);
   const double isdv = 1.0 / sqrt(e.dv);
-  for (int p = t.tid(); p < n * na_; p += t.nt()) {
+  for (int p = threadIdx.x; p < n * na_; p += 256) {
     int i = p % n, c = p / n;
     double s = sqrt(fmax(-w[c], 0.0));
     Tm[p] = s > 0.0 ? Z[i + (long long)n * c] * isdv / s : 0.0;
   }
-  for (int c = t.tid(); c < na_; c += t.nt()) sigma[e.off_nalb + c] = sqrt(fmax(-w[c], 0.0));
-  t.sync();
+  for (int c = threadIdx.x; c < na_; c += 256) sigma[e.off_nalb + c] = sqrt(fmax(-w[c], 0.0));
 }
 
 // ALB column c of block `src` (rows 0..N_E-1) -> output, sign such that the
@@ -867,8 +943,8 @@ dg_check_finite(const double* __restrict__ a, long long n, int* flag) {
 namespace dg {
 // Batched symmetric eigensolver for tests: matrix b of A (n x n, upper
 // triangle read) -> w[b*n ..] ascending, Z[b*n*k ..] first k eigenvectors.
-// method 0: Householder + bisection + inverse iteration (lowest k only);
-// method 1: Householder + implicit QL on the whole spectrum.
+// method 0 above order EIG_MAXN: Householder + bisection + inverse iteration
+// (lowest k only); method 1: Householder + implicit QL on the whole spectrum.
 extern "C" __global__ void __launch_bounds__(SMALL_THREADS)
 dg_syev_batch(const double* __restrict__ A, double* w, double* Z, int n, int k, double* work,
               int method) {
@@ -876,7 +952,7 @@ dg_syev_batch(const double* __restrict__ A, double* w, double* Z, int n, int k, 
   __shared__ double lds[EIG_LDS];
   DevTeam t{red};
   long long b = blockIdx.x;
-  double* Aw = work + b * (2LL * n * n + 8LL * n + 6LL * n * k);
+  double* Aw = work + b * syev_stride(n, k);
   double* U = Aw + (long long)n * n;
   double* vec = U + (long long)n * n;
   copy_mat(t, A + b * n * n, n, Aw, n, n, n);
@@ -888,39 +964,41 @@ dg_syev_batch(const double* __restrict__ A, double* w, double* Z, int n, int k, 
   }
 }
 
-// Method 0 for orders EIG_WIDE_MIN..EIG_WIDE_MAX (same layout as
-// dg_syev_batch) in three parts: copy, one launch per Householder step over
-// TRI_NWG workgroups per matrix, the rest of the eigensolver.
+// Method 0 up to order EIG_MAXN: the lower triangle of each matrix's copy from
+// its upper one, in 32 x 32 tiles through LDS (blockIdx.x = matrix x tile),
+// then the tridiagonalisation and the stages of eig_split.h.
+constexpr int SYEV_COPY_TILE = 32;
 extern "C" __global__ void __launch_bounds__(256)
 dg_syev_batch_copy(const double* __restrict__ A, int n, int k, double* work) {
-  __shared__ double red[32];
-  DevTeam t{red};
-  long long b = blockIdx.x;
-  double* Aw = work + b * (2LL * n * n + 8LL * n + 6LL * n * k);
-  copy_mat(t, A + b * n * n, n, Aw, n, n, n);
-  sym_from_upper(t, Aw, n, n);
+  constexpr int TS = SYEV_COPY_TILE;
+  __shared__ double tile[TS][TS + 1];
+  const int nb = cdiv(n, TS);
+  const int q = blockIdx.x % (nb * nb), bi = q % nb, bj = q / nb;
+  if (bj > bi) return;
+  const long long b = blockIdx.x / (nb * nb);
+  const double* S = A + b * n * n;
+  double* Aw = work + b * syev_stride(n, k);
+  const int r = threadIdx.x % TS, c0 = threadIdx.x / TS;
+#pragma unroll
+  for (int c = c0; c < TS; c += 256 / TS) {
+    const int row = bj * TS + r, col = bi * TS + c;
+    tile[c][r] = (row < n && col < n) ? gld(S + row + (long long)n * col) : 0.0;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int c = c0; c < TS; c += 256 / TS) {
+    const int row = bi * TS + r, col = bj * TS + c;
+    if (row < n && col <= row) gst(Aw + row + (long long)n * col, tile[r][c]);
+  }
 }
 
-extern "C" __global__ void __launch_bounds__(TRI_STEP_THREADS)
-dg_tri_step_batch(int n, int k, double* work, int step) {
-  __shared__ double red[32];
-  __shared__ double lds[TRI_STEP_LDS];
-  DevTeam t{red};
-  const long long b = blockIdx.x / TRI_NWG;
-  const int w = (int)(blockIdx.x - b * TRI_NWG);
-  double* Aw = work + b * (2LL * n * n + 8LL * n + 6LL * n * k);
-  tri_step(t, Aw, n, n, step, w, Aw + (long long)n * n, lds);
-}
-
-extern "C" __global__ void __launch_bounds__(EIG_WIDE_THREADS)
-dg_syev_batch_wide_rest(double* w, double* Z, int n, int k, double* work) {
+extern "C" __global__ void __launch_bounds__(SMALL_THREADS)
+dg_syev_batch_tri(int n, int k, double* work) {
   __shared__ double red[32];
   __shared__ double lds[EIG_LDS];
   DevTeam t{red};
-  long long b = blockIdx.x;
-  double* Aw = work + b * (2LL * n * n + 8LL * n + 6LL * n * k);
-  double* U = Aw + (long long)n * n;
-  double* vec = U + (long long)n * n;
-  syev_lowest<true, true>(t, Aw, n, n, k, w + b * n, Z + b * n * k, n, U, (int*)vec, lds, EIG_LDS);
+  double* Aw = work + blockIdx.x * syev_stride(n, k);
+  double* wk = Aw + (long long)n * n;
+  tridiagonalize_lower<false>(t, Aw, n, n, wk, wk + n, wk + 2 * n, lds, lds + n, lds + 2 * n, EIG_LDS - 2 * n);
 }
 }  // namespace dg

@@ -514,15 +514,13 @@ __device__ __forceinline__ double wave_sum_dpp(double v) {
 
 // Shapes of the one-pass tridiagonalisation (rows per lane in chunks of 64,
 // columns per wave pass, row groups) for workgroups of 1024 lanes: orders up
-// to 512, and 513..832; and the columns per wave of the back-transformation
-// for orders 513..832.
+// to 512, and 513..832.
 #define TRI_R 2
 #define TRI_U 2
 #define TRI_H 4
 #define TRI_WIDE_R 4
 #define TRI_WIDE_U 2
 #define TRI_WIDE_H 4
-#define BT_WIDE_U 1
 
 // Device fast path of tridiagonalize_lower with one pass over the trailing
 // block per Householder step: the rank-2 update left by reflector k-1 and the
@@ -1451,12 +1449,9 @@ __device__ __forceinline__ void bt_fast(T& t, const double* A, int lda, const do
   }
 }
 
-template <bool WIDE = false, class T>
+template <class T>
 __host__ __device__ void backtransform(T& t, const double* A, int lda, const double* tau, int n,
                                        double* Z, int ldz, int k, double* lds, int lds_size) {
-  if constexpr (T::is_device && WIDE) {
-    if (lds_size >= n + 16 && n <= 64 * 13) { bt_fast<13, BT_WIDE_U>(t, A, lda, tau, n, Z, ldz, k, lds, lds_size); return; }
-  }
   if constexpr (T::is_device) {
     if (lds_size >= n + 16 && n <= 64 * 6) { bt_fast<6, 2>(t, A, lda, tau, n, Z, ldz, k, lds, lds_size); return; }
     if (lds_size >= n + 16 && n <= 64 * 7) { bt_fast<7, 2>(t, A, lda, tau, n, Z, ldz, k, lds, lds_size); return; }
@@ -1486,18 +1481,15 @@ __host__ __device__ void backtransform(T& t, const double* A, int lda, const dou
 // Lowest k eigenpairs of the symmetric A (lower triangle read, destroyed):
 // w[0..k) ascending, Z (n x k).  work: 9 n + 6 n k doubles; cl: k ints
 // (global); lds: >= 2n doubles (and >= k for the generic back-transform).
-// WIDE: the device paths for orders up to 832.
-// PRE: the tridiagonalisation is already done (by tri_step): d, e, tau in
-// work, reflectors in A.
-template <bool WIDE = false, bool PRE = false, class T>
+template <class T>
 __host__ __device__ void syev_lowest(T& t, double* A, int lda, int n, int k, double* w, double* Z,
                                      int ldz, double* work, int* cl, double* lds, int lds_size) {
   double* d = work;
   double* e = work + n;
   double* tau = work + 2 * n;
-  if (!PRE) tridiagonalize_lower<WIDE>(t, A, lda, n, d, e, tau, lds, lds + n, lds + 2 * n, lds_size - 2 * n);
+  tridiagonalize_lower(t, A, lda, n, d, e, tau, lds, lds + n, lds + 2 * n, lds_size - 2 * n);
   tridiag_lowest(t, d, e, n, k, w, Z, ldz, work + 3 * n, cl, lds, lds_size);
-  backtransform<WIDE>(t, A, lda, tau, n, Z, ldz, k, lds, lds_size);
+  backtransform(t, A, lda, tau, n, Z, ldz, k, lds, lds_size);
 }
 
 }  // namespace dg

@@ -1,0 +1,42 @@
+"""The eigensolver's stages (multisection, inverse iteration, clusters,
+back-transformation) spread over workgroups, at the edges of their tiles."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(M, w, Z, k):
+    """Backward error and orthogonality of the lowest k eigenpairs, in units of
+    rounding times the order."""
+    n = M.shape[-1]
+    for i in range(M.shape[0]):
+        ref = np.linalg.eigvalsh(M[i])
+        sc = max(1.0, np.abs(ref).max())
+        assert np.abs(w[i][:k] - ref[:k]).max() <= 1e-13 * sc * n
+        Zi = Z[i].T
+        assert np.abs(M[i] @ Zi - Zi * w[i][:k]).max() <= 1e-12 * sc * np.sqrt(n)
+        assert np.abs(Zi.T @ Zi - np.eye(k)).max() <= 1e-12 * np.sqrt(n)
+
+
+# orders at the row chunks of the back-transformation (128, 256, 448, 640) and
+# its reflector blocks of 8; counts at the 16 eigenvalues and 64 vectors of a
+# workgroup, and all of them
+@pytest.mark.parametrize("n,k", [(2, 1), (3, 3), (9, 9), (10, 8), (63, 17), (64, 64), (65, 16), (128, 65),
+                                 (129, 129), (256, 63), (257, 1), (448, 128), (449, 113), (512, 171),
+                                 (640, 16), (641, 200), (832, 278), (832, 832)])
+def test_orders_and_counts(n, k):
+    import torch
+    from paper_1506_08147_amd import small_syev
+    rng = np.random.default_rng(7 * n + k)
+    M = rng.standard_normal((3, n, n))
+    M = M + M.transpose(0, 2, 1)
+    if n >= 9:   # a cluster of equal eigenvalues inside the lowest k
+        Q, _ = np.linalg.qr(M[1])
+        d = np.sort(rng.standard_normal(n))
+        d[1:min(n, 7)] = d[1]
+        M[1] = (Q * d) @ Q.T
+        M[1] = 0.5 * (M[1] + M[1].T)
+    M[2] = np.diag(np.arange(n, 0, -1.0))   # nothing to reflect, no off-diagonal
+    w, Z = small_syev(torch.from_numpy(M).to("cuda:0"), k)
+    _check(M, w.cpu().numpy(), Z.cpu().numpy(), k)
