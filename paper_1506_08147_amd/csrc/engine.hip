@@ -106,8 +106,8 @@ struct dgdft_alb {
   hipStream_t g_stream[NGROUP] = {};
   hipEvent_t g_join = nullptr;
   hipEvent_t g_done[NGROUP] = {};
-  // per group: a second stream on which the eigensolver of the smaller
-  // Rayleigh-Ritz orders runs beside the one of the larger (fork / join)
+  // per group: a second stream on which the tridiagonalisations of the smaller
+  // Rayleigh-Ritz orders run beside those of the larger (fork / join)
   hipStream_t g_aux[NGROUP] = {};
   hipEvent_t g_fork[NGROUP] = {};
   hipEvent_t g_auxdone[NGROUP] = {};
@@ -646,20 +646,44 @@ struct dgdft_alb {
     HCHECK(hipGetLastError());
   }
 
-  // The eigensolver of the Rayleigh-Ritz step (see lobpcg.hip).  Outside graph
-  // capture the one-workgroup tridiagonalisations of orders up to 512 run on
-  // the group's second stream beside the per-step launches of the wide ones.
-  void rr_eig_pair(const std::vector<int>& act, int single) {
-    int nmax = 0, kmax = 0, wmax = 0;
-    bool small = false, large = false;
+  // Orders of a batch's eigenproblems: the largest of each tridiagonalisation
+  // class (tri.h; 0: none), and the largest number of eigenpairs.
+  struct EigOrders {
+    int reg = 0, step = 0, wide = 0, kmax = 0;
+    void add(int n, int k) {
+      int& c = n <= TRI_REG_MAX ? reg : n <= TRI_STEP_SPLIT ? step : wide;
+      c = std::max(c, n);
+      kmax = std::max(kmax, k);
+    }
+  };
+  // Tridiagonalisation of `count` matrices: the wide class on stream s, the
+  // others (which start with it and end before it) on stream s2.
+  static void eig_tri(const EigSrc& src, int count, const EigOrders& o, hipStream_t s, hipStream_t s2) {
+    if (o.reg) hipLaunchKernelGGL(dg_tri_reg, dim3(count), dim3(TRI_REG_THREADS), 0, s2, src);
+    for (int k = 0; k + 2 <= std::max(o.step, o.wide); ++k) {
+      if (k + 2 <= o.wide)
+        hipLaunchKernelGGL(dg_tri_step, dim3(count * TRI_NWG_MAX), dim3(TRI_STEP_THREADS), tri_step_lds(o.wide), s,
+                           src, k);
+      if (k + 2 <= o.step)
+        hipLaunchKernelGGL(dg_tri_step_s, dim3(count * TRI_NWG_S), dim3(TRI_STEP_THREADS_S), tri_step_lds(o.step),
+                           s2, src, k);
+    }
+    HCHECK(hipGetLastError());
+  }
+  static void eig_solve(const EigSrc& src, int count, const EigOrders& o, hipStream_t s) {
+    eig_tri(src, count, o, s, s);
+    eig_stages(src, count, std::max({o.reg, o.step, o.wide}), o.kmax, s);
+  }
+
+  // The eigensolver of the Rayleigh-Ritz step (see lobpcg.hip).
+  void rr_eig(const std::vector<int>& act, int single) {
+    EigOrders o;
+    bool large = false;
     for (int e : act) {
       const int n = (single ? 1 : (hasP_host(e) ? 3 : 2)) * eh[e].J;
-      if (n > EIG_MAXN) { large = true; continue; }
-      nmax = std::max(nmax, n);
-      kmax = std::max(kmax, eh[e].J);
-      if (eig_wide(n)) wmax = std::max(wmax, n); else small = true;
+      if (n > EIG_MAXN) large = true; else o.add(n, eh[e].J);
       // inside a captured graph an element may lose its P block (n = 2 J)
-      if (!single && capturing && 2 * eh[e].J < EIG_WIDE_MIN) small = true;
+      if (!single && capturing && 2 * eh[e].J <= EIG_MAXN) o.add(2 * eh[e].J, eh[e].J);
     }
     auto P = make_prefix(act, [&](int) { return 1; });
     EigSrc src{};
@@ -667,27 +691,20 @@ struct dgdft_alb {
     src.active = P.active;
     src.single = single;
     pbeg(DGDFT_K_RR, 0, 0);
-    const bool fork = wmax > 0 && small && !capturing;
-    hipStream_t ts = stream;
-    if (fork) {
-      ts = g_aux[cur_g];
-      HCHECK(hipEventRecord(g_fork[cur_g], stream));
-      HCHECK(hipStreamWaitEvent(ts, g_fork[cur_g], 0));
-    }
-    if (small)
-      hipLaunchKernelGGL(dg_rr_tri, dim3(P.na), dim3(SMALL_THREADS), 0, ts, ed, P.active, P.na, single);
-    if (fork) HCHECK(hipEventRecord(g_auxdone[cur_g], ts));
-    if (wmax > 0 && capturing)
-      hipLaunchKernelGGL(dg_rr_tri_wide, dim3(P.na), dim3(SMALL_THREADS), 0, stream, ed, P.active, P.na, single);
-    else
-      for (int k = 0; k + 2 <= wmax; ++k)
-        hipLaunchKernelGGL(dg_tri_step, dim3(P.na * TRI_NWG), dim3(TRI_STEP_THREADS), 0, stream, src, k);
     if (large)
       hipLaunchKernelGGL(dg_rr_eig_large, dim3(P.na), dim3(SMALL_THREADS), 0, stream, ed, P.active, P.na, single);
-    HCHECK(hipGetLastError());
-    if (fork) HCHECK(hipStreamWaitEvent(stream, g_auxdone[cur_g], 0));
-    eig_stages(src, P.na, nmax, kmax, stream);
+    if (o.wide && (o.reg || o.step) && !capturing) {
+      HCHECK(hipEventRecord(g_fork[cur_g], stream));
+      HCHECK(hipStreamWaitEvent(g_aux[cur_g], g_fork[cur_g], 0));
+      eig_tri(src, P.na, o, stream, g_aux[cur_g]);
+      HCHECK(hipEventRecord(g_auxdone[cur_g], g_aux[cur_g]));
+      HCHECK(hipStreamWaitEvent(stream, g_auxdone[cur_g], 0));
+      eig_stages(src, P.na, o.wide, o.kmax, stream);
+    } else {
+      eig_solve(src, P.na, o, stream);
+    }
     pend();
+    HCHECK(hipGetLastError());
   }
 
   // Rayleigh-Ritz step (see lobpcg.hip): per-element factorisations and
@@ -749,7 +766,7 @@ struct dgdft_alb {
       sgemm(act, single, 0, 0, SM_H, 0, SM_T, 0, SM_U, 0, N, N, N, N, N, N, 1.0, 0.0, 3);
       sgemm(act, single, 0, 0, SM_T, 0, SM_U, 0, SM_A, 0, N, N, N, N, N, N, 1.0, 0.0, 3);
     }
-    rr_eig_pair(act, single);
+    rr_eig(act, single);
     // path 0: C = L^-T Y
     sgemm(act, single, 0, 0, SM_T, 0, SM_Z, 0, SM_C, 0, N, Jc, N, N, N, N, 1.0, 0.0, 0);
     // path 3: C = T Y
@@ -867,16 +884,16 @@ struct dgdft_alb {
         hipLaunchKernelGGL(dg_advance, dim3(cdiv(P.na, 256)), dim3(256), 0, stream, ed, P.active, P.na);
         break;
       case 4:
-        hipLaunchKernelGGL(dg_alb_tri, dim3(P.na), dim3(SMALL_THREADS), 0, stream, ed, P.active, P.na);
+        hipLaunchKernelGGL(dg_alb_matrix, dim3(P.na), dim3(SMALL_THREADS), 0, stream, ed, P.active, P.na);
         {
           EigSrc src{};
           src.kind = 1;
           src.E = ed;
           src.active = P.active;
-          int nmax = 0, kmax = 0;
+          EigOrders o;
           for (int e : act)
-            if (eh[e].J <= EIG_MAXN) { nmax = std::max(nmax, eh[e].J); kmax = std::max(kmax, eh[e].nalb); }
-          eig_stages(src, P.na, nmax, kmax, stream);
+            if (eh[e].J <= EIG_MAXN) o.add(eh[e].J, eh[e].nalb);
+          eig_solve(src, P.na, o, stream);
         }
         hipLaunchKernelGGL(dg_alb_coeffs, dim3(P.na), dim3(256), 0, stream, ed, P.active, P.na, out);
         break;
@@ -2324,12 +2341,9 @@ static void launch_syev(int32_t count, int32_t n, int32_t k, const double* A, do
     src.n = n;
     src.k = k;
     hipLaunchKernelGGL(dg_syev_batch_copy, dim3((unsigned)count * nb * nb), dim3(256), 0, s, A, n, k, work);
-    if (eig_wide(n))
-      for (int st = 0; st + 2 <= n; ++st)
-        hipLaunchKernelGGL(dg_tri_step, dim3(count * TRI_NWG), dim3(TRI_STEP_THREADS), 0, s, src, st);
-    else
-      hipLaunchKernelGGL(dg_syev_batch_tri, dim3(count), dim3(SMALL_THREADS), 0, s, n, k, work);
-    dgdft_alb::eig_stages(src, count, n, k, s);
+    dgdft_alb::EigOrders o;
+    o.add(n, k);
+    dgdft_alb::eig_solve(src, count, o, s);
   } else
     hipLaunchKernelGGL(dg_syev_batch, dim3(count), dim3(SMALL_THREADS), 0, s, A, w, Z, n, k, work,
                        method);

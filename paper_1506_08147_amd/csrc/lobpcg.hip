@@ -9,14 +9,13 @@
 // cooperative routines of small_dense.h, all FP64.
 #include "common.h"
 #include "small_dense.h"
-#include "eig_split.h"
+#include "tri.h"
 
 namespace dg {
 
 constexpr double CHOL_TOL = 1e-10;   // smallest admissible pivot of a unit-diagonal Gram
 constexpr int SMALL_THREADS = 1024;
-// LDS of the eigensolver workgroups (doubles): the one-pass tridiagonalisation
-// needs (waves + 4) n, i.e. up to n = 512 at 1024 threads
+// LDS of the one-workgroup eigensolver (doubles)
 constexpr int EIG_LDS = 10240;
 
 __device__ __forceinline__ double wave_sum(double v) {
@@ -322,15 +321,10 @@ dg_carry_in(Elem* __restrict__ E, const int* __restrict__ active, int na) {
   }
 }
 
-// The eigensolver of the Rayleigh-Ritz step: tridiagonalisation, then the
-// stages of eig_split.h, for orders up to EIG_MAXN; larger orders stay in one
-// workgroup (dg_rr_eig_large).  Tridiagonalisation: one workgroup per element
-// up to order 512 (dg_rr_tri), over TRI_NWG workgroups per element with one
-// launch per Householder step for EIG_WIDE_MIN..EIG_MAXN (dg_tri_step; one
-// workgroup, dg_rr_tri_wide, inside graph capture).
-constexpr int EIG_WIDE_MIN = 513;
-
-__host__ __device__ inline bool eig_wide(int n) { return n >= EIG_WIDE_MIN && n <= EIG_MAXN; }
+// The eigensolver of the Rayleigh-Ritz step: tridiagonalisation (tri.h: in
+// registers up to order TRI_REG_MAX, else one launch per Householder step),
+// then the stages of eig_split.h, for orders up to EIG_MAXN; larger orders
+// stay in one workgroup (dg_rr_eig_large).
 
 // Where the matrices of a batch are: the Rayleigh-Ritz matrices of elements
 // (kind 0), the restricted Grams of elements (1), or a plain batch (2: copies
@@ -398,31 +392,28 @@ dg_eig_back(EigSrc s, int per) {
   eig_back_any(eig_view(s, blockIdx.x / per), blockIdx.x % per, dyn);
 }
 
-template <bool WIDE>
-__device__ __forceinline__ void rr_tri_body(Elem* __restrict__ E, const int* __restrict__ active,
-                                            int single, double* red, double* lds) {
-  DevTeam t{red};
-  const Elem& e = E[active[blockIdx.x]];
-  if (e.fl[FL_RR_PATH] == 1) return;
-  const int n = (single ? 1 : (has_p(e) ? 3 : 2)) * e.J;
-  if (n > EIG_MAXN || eig_wide(n) != WIDE) return;   // another kernel's element
-  double* work = sm(e, SM_W0);
-  tridiagonalize_lower<WIDE>(t, sm(e, SM_A), n, n, work, work + n, work + 2 * n, lds, lds + n, lds + 2 * n,
-                             EIG_LDS - 2 * n);
+extern "C" __global__ void __launch_bounds__(TRI_REG_THREADS)
+dg_tri_reg(EigSrc s) {
+  __shared__ double lds[TRI_REG_LDS];
+  const EigView m = eig_view(s, blockIdx.x);
+  if (m.n > TRI_REG_MAX) return;           // dg_tri_step's matrix
+  tri_reg(m, lds);
 }
 
-extern "C" __global__ void __launch_bounds__(SMALL_THREADS)
-dg_rr_tri(Elem* __restrict__ E, const int* __restrict__ active, int na, int single) {
-  __shared__ double red[32];
-  __shared__ double lds[EIG_LDS];
-  rr_tri_body<false>(E, active, single, red, lds);
+// tri_nwg(nmax) workgroups per matrix and tri_step_lds(nmax) bytes of LDS, nmax
+// the largest order of the launch's class.
+extern "C" __global__ void __launch_bounds__(TRI_STEP_THREADS)
+dg_tri_step(EigSrc s, int k) {
+  extern __shared__ double dyn[];
+  const int b = blockIdx.x / TRI_NWG_MAX;
+  tri_step<true>(eig_view(s, b), k, blockIdx.x - b * TRI_NWG_MAX, dyn);
 }
 
-extern "C" __global__ void __launch_bounds__(SMALL_THREADS)
-dg_rr_tri_wide(Elem* __restrict__ E, const int* __restrict__ active, int na, int single) {
-  __shared__ double red[32];
-  __shared__ double lds[EIG_LDS];
-  rr_tri_body<true>(E, active, single, red, lds);
+extern "C" __global__ void __launch_bounds__(TRI_STEP_THREADS_S)
+dg_tri_step_s(EigSrc s, int k) {
+  extern __shared__ double dyn[];
+  const int b = blockIdx.x / TRI_NWG_S;
+  tri_step<false>(eig_view(s, b), k, blockIdx.x - b * TRI_NWG_S, dyn);
 }
 
 // Orders above EIG_MAXN: the whole eigensolver in one workgroup.
@@ -438,19 +429,6 @@ dg_rr_eig_large(Elem* __restrict__ E, const int* __restrict__ active, int na, in
   double* vec = sm(e, SM_V);
   syev_lowest(t, sm(e, SM_A), n, n, e.J, vec + 7 * n, sm(e, SM_Z), n, sm(e, SM_W0), (int*)(vec + 10 * n), lds,
               EIG_LDS);
-}
-
-constexpr int TRI_STEP_LDS = 4 * EIG_MAXN + 4 * (EIG_MAXN / TRI_NWG + 1);
-
-extern "C" __global__ void __launch_bounds__(TRI_STEP_THREADS)
-dg_tri_step(EigSrc s, int k) {
-  __shared__ double red[32];
-  __shared__ double lds[TRI_STEP_LDS];
-  DevTeam t{red};
-  const int b = blockIdx.x / TRI_NWG;
-  const EigView m = eig_view(s, b);
-  if (!eig_wide(m.n)) return;
-  tri_step(t, m.A, m.n, m.n, k, blockIdx.x - b * TRI_NWG, m.work, lds);
 }
 
 // Path 3: T = I - E/2 + 3 E^2/8 - 5 E^3/16 from E (SM_L), E^2 (SM_U) and
@@ -760,10 +738,9 @@ dg_gather_box(Elem* __restrict__ E, const int* __restrict__ active, const int* _
 // sigma (descending) and T = V S^-1 / sqrt(dV) (J x n_alb, SM_T), so that
 // Psi_E T are the ALBs in the dV sum phi^2 = 1 normalisation.  The n_alb
 // largest eigenpairs of G are the lowest of -G, from the Rayleigh-Ritz
-// eigensolver: tridiagonalisation here, then the stages of eig_split.h (or
-// all of it here above order EIG_MAXN), then dg_alb_coeffs.
+// eigensolver (all of it here above order EIG_MAXN), then dg_alb_coeffs.
 extern "C" __global__ void __launch_bounds__(SMALL_THREADS)
-dg_alb_tri(Elem* __restrict__ E, const int* __restrict__ active, int na) {
+dg_alb_matrix(Elem* __restrict__ E, const int* __restrict__ active, int na) {
   __shared__ double red[32];
   __shared__ double lds[EIG_LDS];
   DevTeam t{red};
@@ -772,15 +749,12 @@ dg_alb_tri(Elem* __restrict__ E, const int* __restrict__ active, int na) {
   double* G = sm(e, SM_G);
   double* A = sm(e, SM_A);
   double* vec = sm(e, SM_V);
-  double* work = sm(e, SM_W0);
   sym_from_upper(t, G, n, n);
   for (int p = t.tid(); p < n * n; p += t.nt()) A[p] = -G[p];
   t.sync();
   if (n > EIG_MAXN)
-    syev_lowest(t, A, n, n, e.nalb, vec + 7 * n, sm(e, SM_Z), n, work, (int*)(vec + 10 * n), lds, EIG_LDS);
-  else
-    tridiagonalize_lower<false>(t, A, n, n, work, work + n, work + 2 * n, lds, lds + n, lds + 2 * n,
-                                EIG_LDS - 2 * n);
+    syev_lowest(t, A, n, n, e.nalb, vec + 7 * n, sm(e, SM_Z), n, sm(e, SM_W0), (int*)(vec + 10 * n), lds,
+                EIG_LDS);
 }
 
 extern "C" __global__ void __launch_bounds__(256)
@@ -992,13 +966,4 @@ dg_syev_batch_copy(const double* __restrict__ A, int n, int k, double* work) {
   }
 }
 
-extern "C" __global__ void __launch_bounds__(SMALL_THREADS)
-dg_syev_batch_tri(int n, int k, double* work) {
-  __shared__ double red[32];
-  __shared__ double lds[EIG_LDS];
-  DevTeam t{red};
-  double* Aw = work + blockIdx.x * syev_stride(n, k);
-  double* wk = Aw + (long long)n * n;
-  tridiagonalize_lower<false>(t, Aw, n, n, wk, wk + n, wk + 2 * n, lds, lds + n, lds + 2 * n, EIG_LDS - 2 * n);
-}
 }  // namespace dg

@@ -512,455 +512,13 @@ __device__ __forceinline__ double wave_sum_dpp(double v) {
   return v;
 }
 
-// Shapes of the one-pass tridiagonalisation (rows per lane in chunks of 64,
-// columns per wave pass, row groups) for workgroups of 1024 lanes: orders up
-// to 512, and 513..832.
-#define TRI_R 2
-#define TRI_U 2
-#define TRI_H 4
-#define TRI_WIDE_R 4
-#define TRI_WIDE_U 2
-#define TRI_WIDE_H 4
-
-// Device fast path of tridiagonalize_lower with one pass over the trailing
-// block per Householder step: the rank-2 update left by reflector k-1 and the
-// symmetric product of reflector k (p = tk A2 v) read and write every entry
-// of A2 = A[k+1:, k+1:] once.  Column k itself is updated first, separately,
-// since reflector k is built from it.  Each entry gets the same operations in
-// the same order as with a separate product pass and update pass.  The waves
-// form H row groups x (waves / H) column groups: row group h owns the
-// 64-row chunks h, h + H, h + 2H, ... (R chunks, m <= 64 H R), and each lane
-// keeps its rows of both reflectors, q and its share of the row sums in
-// registers; a wave takes U columns per pass and loads the next pass's
-// columns before working on the current ones, so that a pass's loads are in
-// flight while the previous pass computes.  Chunks wholly above a column's
-// diagonal or below the block are skipped.  Outputs, for the caller to add in
-// a fixed order: column parts (sum over a row group's rows i >= j of
-// A2[i][j] v[i]) at scratch[h n + j], row parts (sum over a column group's
-// columns j < i of A2[i][j] v[j]) at scratch[(H + c) n + i].  v, p: n doubles
-// each; scratch: (waves + 2) * n doubles (parts, second v buffer).
-template <int R, int U, int H, class T>
-__device__ __forceinline__ void tri_fused_pass(T& t, double* A2, int lda, int n, int m,
-                                               const double* v, const double* vo,
-                                               const double* qo, bool upd, double* scratch) {
-  const int lane = t.tid() & 63, wv = t.tid() >> 6, nw = (t.nt() + 63) >> 6;
-  const int h = wv % H, c = wv / H, nc = nw / H;
-  double* pc = scratch + (long long)h * n;
-  double* part = scratch + (long long)(H + c) * n;
-  double vr[R], acc[R], vor[R], qor[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int i = 64 * (h + H * r) + lane;
-    vr[r] = i < m ? v[i] : 0.0;
-    vor[r] = (upd && i < m) ? vo[i] : 0.0;
-    qor[r] = (upd && i < m) ? qo[i] : 0.0;
-    acc[r] = 0.0;
-  }
-  const int step = U * nc;
-  double xn[U][R];
-  auto fetch = [&](int j0) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int j = j0 + u * nc;
-      const double* col = A2 + (long long)lda * (j < m ? j : 0);
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int cb = 64 * (h + H * r), i = cb + lane;
-        double a = 0.0;
-        if (j < m && cb + 63 >= j && cb < m) {     // wave-uniform chunk test
-          if (i >= j && i < m) a = gld(col + i);
-        }
-        xn[u][r] = a;
-      }
-    }
-  };
-  if (c < m) fetch(c);
-  for (int j0 = c; j0 < m; j0 += step) {
-    double x[U][R], vj[U], sm[U], voj[U], qoj[U];
-    int jj[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      jj[u] = j0 + u * nc;
-      const bool has = jj[u] < m;
-      vj[u] = has ? v[jj[u]] : 0.0;
-      voj[u] = (upd && has) ? vo[jj[u]] : 0.0;
-      qoj[u] = (upd && has) ? qo[jj[u]] : 0.0;
-#pragma unroll
-      for (int r = 0; r < R; ++r) x[u][r] = xn[u][r];
-    }
-    if (j0 + step < m) fetch(j0 + step);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      sm[u] = 0.0;
-      const int j = jj[u];
-      double* col = A2 + (long long)lda * (j < m ? j : 0);
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int cb = 64 * (h + H * r), i = cb + lane;
-        if (j < m && cb + 63 >= j && cb < m) {
-          if (i >= j && i < m) {
-            double a = x[u][r];
-            if (upd) {
-              a -= vor[r] * qoj[u] + qor[r] * voj[u];
-              gst(col + i, a);
-            }
-            sm[u] += a * vr[r];
-            if (i > j) acc[r] += a * vj[u];
-          }
-        }
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) sm[u] = wave_sum_dpp(sm[u]);
-    if (lane == 0) {
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (jj[u] < m) pc[jj[u]] = sm[u];
-    }
-  }
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int i = 64 * (h + H * r) + lane;
-    if (i < m) part[i] = acc[r];
-  }
-}
-
-// Lower-triangle rank-2 update B -= vo qo^T + qo vo^T of the mm x mm block B
-// (wave per column); the tail of the fused tridiagonalisation.
-template <class T>
-__device__ __forceinline__ void tri_rank2_tail(T& t, double* B, int lda, int mm, const double* vo,
-                                               const double* qo) {
-  const int lane = t.tid() & 63, wv = t.tid() >> 6, nw = (t.nt() + 63) >> 6;
-  for (int j = wv; j < mm; j += nw) {
-    const double vj = vo[j], qj = qo[j];
-    double* col = B + (long long)lda * j;
-    for (int i = j + lane; i < mm; i += 64) col[i] -= vo[i] * qj + qo[i] * vj;
-  }
-  t.sync();
-}
-
-template <int R, int U, int H, class T>
-__device__ void tridiagonalize_fused(T& t, double* A, int lda, int n, double* d, double* e,
-                                     double* tau, double* v, double* p, double* scratch) {
-  const int nw = (t.nt() + 63) >> 6;
-  double* vcur = v;
-  double* vold = scratch + (long long)(H + nw / H) * n;   // after the parts
-  bool pend = false;   // reflector k-1's update of A[k:, k:] not yet applied (vold, q in p)
-  for (int k = 0; k + 2 < n; ++k) {
-    const int m = n - k - 1;
-    double* colk = &IDX(A, lda, k, k);
-    // column k (rows k..n-1): pending update, then rows k+2.. into vcur[1..]
-    double part = 0.0;
-    {
-      const double vo0 = pend ? vold[0] : 0.0, qo0 = pend ? p[0] : 0.0;
-      for (int r = t.tid(); r <= m; r += t.nt()) {
-        int i = r + 2 <= m ? r + 2 : r - (m - 1);     // rows 2.. first, then 0 and 1
-        double a = gld(colk + i);
-        if (pend) {
-          a -= vold[i] * qo0 + p[i] * vo0;
-          gst(colk + i, a);
-        }
-        if (i >= 2) {
-          vcur[i - 1] = a;
-          part += a * a;
-        }
-      }
-    }
-    double a2 = t.sum(part);
-    double x0 = gld(colk + 1);
-    if (a2 == 0.0) {
-      if (t.tid() == 0) { e[k] = x0; tau[k] = 0.0; }
-      if (pend) tri_rank2_tail(t, &IDX(A, lda, k + 1, k + 1), lda, m, vold + 1, p + 1);
-      pend = false;
-      t.sync();
-      continue;
-    }
-    double nrm = sqrt(x0 * x0 + a2);
-    double beta = (x0 >= 0.0) ? -nrm : nrm;
-    double v0 = x0 - beta;
-    double tk = 2.0 / (v0 * v0 + a2);
-    if (t.tid() == 0) vcur[0] = v0;
-    t.sync();                                       // every lane has read x0
-    if (t.tid() == 0) { gst(colk + 1, v0); e[k] = beta; tau[k] = tk; }
-    double* A2 = &IDX(A, lda, k + 1, k + 1);
-    tri_fused_pass<R, U, H>(t, A2, lda, n, m, vcur, vold + 1, p + 1, pend, scratch);
-    t.sync();
-    {
-      const int nparts = H + nw / H;     // H column parts, then the row parts
-      for (int i = t.tid(); i < m; i += t.nt()) {
-        double s = 0.0;
-        for (int w = 0; w < nparts; ++w) s += scratch[(long long)w * n + i];
-        p[i] = s;
-      }
-    }
-    t.sync();
-    double vp = 0.0;
-    for (int i = t.tid(); i < m; i += t.nt()) { p[i] *= tk; vp += vcur[i] * p[i]; }
-    double K = 0.5 * tk * t.sum(vp);
-    for (int i = t.tid(); i < m; i += t.nt()) p[i] -= K * vcur[i];   // p := q
-    t.sync();
-    double* sw = vold;
-    vold = vcur;
-    vcur = sw;
-    pend = true;
-  }
-  if (pend) tri_rank2_tail(t, &IDX(A, lda, n - 2, n - 2), lda, 2, vold, p);
-  for (int i = t.tid(); i < n; i += t.nt()) d[i] = IDX(A, lda, i, i);
-  if (t.tid() == 0) {
-    if (n >= 2) e[n - 2] = IDX(A, lda, n - 1, n - 2);
-    if (n >= 1) e[n - 1] = 0.0;
-    if (n >= 2) tau[n - 2] = 0.0;
-  }
-  t.sync();
-}
-
-// ---------------------------------------------------------------------------
-// The same one-pass tridiagonalisation spread over TRI_NWG workgroups of
-// TRI_STEP_THREADS lanes per matrix, one kernel launch per Householder step k
-// (launches k = 0 .. n - 2).  A launch never waits for another workgroup:
-// every workgroup of a matrix recomputes the small per-step vectors itself
-// from what the previous launch left in device memory (double-buffered by
-// the parity of k):
-//   phase A  reflector k-1 (vbuf) and the parts of p = A v (pcol, prow) ->
-//            q_{k-1} = t p - (t/2)(v.t p) v, the update still pending on the
-//            trailing block; workgroup 0 stores reflector k-1 into column
-//            k-1 of A, where the back-transformation reads it;
-//   phase B  column k with the pending update -> reflector k (d[k], e[k],
-//            tau[k], vbuf written by workgroup 0);
-//   phase C  the workgroup's columns j = w, w + TRI_NWG, ... of the trailing
-//            block A[k+1:, k+1:]: pending update applied and stored, column
-//            parts (rows i >= j) and row parts (columns j < i) of A v.
-// Launch n - 2 applies the last pending update to the 2 x 2 tail.  Each
-// entry gets the operations of the single-workgroup form; sums are taken in
-// another order.  work: d, e, tau (3 n) then the step buffers (20 n).
-constexpr int TRI_NWG = 8;
-constexpr int TRI_STEP_THREADS = 256;
-constexpr int TRI_STEP_R = 4;      // 64-row chunks per lane (4 row groups): n <= 1024
-constexpr int TRI_STEP_U = 2;      // columns per wave pass
-
-__host__ __device__ inline int tri_step_lds(int n) { return 4 * n + 4 * (n / TRI_NWG + 1); }
-__host__ __device__ inline long long tri_step_work(int n) { return (long long)(3 + 4 + 2 * TRI_NWG) * n; }
-
-template <int R, int U, class T>
-__device__ __forceinline__ void tri_step_pass(T& t, double* A2, int lda, int n, int m, int w,
-                                              const double* v, const double* vo, const double* qo,
-                                              bool upd, double* pcl, double* prow_out,
-                                              double* pcol_out) {
-  const int lane = t.tid() & 63, h = t.tid() >> 6;            // row group h of 4
-  const int ncw = w < m ? (m - w + TRI_NWG - 1) / TRI_NWG : 0;  // this workgroup's columns
-  const int NCW = n / TRI_NWG + 1;
-  double vr[R], acc[R], vor[R], qor[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int i = 64 * (h + 4 * r) + lane;
-    vr[r] = i < m ? v[i] : 0.0;
-    vor[r] = (upd && i < m) ? vo[i] : 0.0;
-    qor[r] = (upd && i < m) ? qo[i] : 0.0;
-    acc[r] = 0.0;
-  }
-  double xn[U][R];
-  auto fetch = [&](int t0) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int j = w + TRI_NWG * (t0 + u);
-      const double* col = A2 + (long long)lda * (j < m ? j : 0);
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int cb = 64 * (h + 4 * r), i = cb + lane;
-        double a = 0.0;
-        if (j < m && cb + 63 >= j && cb < m) {     // wave-uniform chunk test
-          if (i >= j && i < m) a = gld(col + i);
-        }
-        xn[u][r] = a;
-      }
-    }
-  };
-  if (ncw > 0) fetch(0);
-  for (int t0 = 0; t0 < ncw; t0 += U) {
-    double x[U][R], vj[U], sm[U], voj[U], qoj[U];
-    int jj[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      jj[u] = w + TRI_NWG * (t0 + u);
-      const bool has = jj[u] < m;
-      vj[u] = has ? v[jj[u]] : 0.0;
-      voj[u] = (upd && has) ? vo[jj[u]] : 0.0;
-      qoj[u] = (upd && has) ? qo[jj[u]] : 0.0;
-#pragma unroll
-      for (int r = 0; r < R; ++r) x[u][r] = xn[u][r];
-    }
-    if (t0 + U < ncw) fetch(t0 + U);
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      sm[u] = 0.0;
-      const int j = jj[u];
-      double* col = A2 + (long long)lda * (j < m ? j : 0);
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const int cb = 64 * (h + 4 * r), i = cb + lane;
-        if (j < m && cb + 63 >= j && cb < m) {
-          if (i >= j && i < m) {
-            double a = x[u][r];
-            if (upd) {
-              a -= vor[r] * qoj[u] + qor[r] * voj[u];
-              gst(col + i, a);
-            }
-            sm[u] += a * vr[r];
-            if (i > j) acc[r] += a * vj[u];
-          }
-        }
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) sm[u] = wave_sum_dpp(sm[u]);
-    if (lane == 0) {
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (t0 + u < ncw) pcl[h * NCW + t0 + u] = sm[u];
-    }
-  }
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int i = 64 * (h + 4 * r) + lane;
-    if (i < m) gst(prow_out + i, acc[r]);
-  }
-  t.sync();
-  for (int q = t.tid(); q < ncw; q += t.nt())
-    gst(pcol_out + w + TRI_NWG * q,
-        ((pcl[q] + pcl[NCW + q]) + pcl[2 * NCW + q]) + pcl[3 * NCW + q]);
-}
-
-// Step k of the tridiagonalisation of the n x n symmetric A (lower triangle)
-// by workgroup w of the matrix.  lds: tri_step_lds(n) doubles.
-template <class T>
-__device__ void tri_step(T& t, double* A, int lda, int n, int k, int w, double* work, double* lds) {
-  if (n < 3 || k > n - 2) return;
-  double* d = work;
-  double* e = work + n;
-  double* tau = work + 2 * n;
-  double* pcol = work + 3 * n;                         // [2][n]
-  double* prow = work + 5 * n;                         // [2][TRI_NWG][n]
-  double* vbuf = work + (5 + 2 * TRI_NWG) * n;         // [2][n]
-  const int par = k & 1, opar = par ^ 1;
-  double* vo = lds;
-  double* qo = lds + n;
-  double* v = lds + 2 * n;
-  double* pt = lds + 3 * n;
-  double* pcl = lds + 4 * n;
-  const int mo = n - k;                                // rows of reflector k-1 (from row k)
-  // phase A: the update left pending by step k-1
-  if (k > 0) {
-    const double tko = gld(tau + k - 1);
-    const double* pc = pcol + (long long)opar * n;
-    const double* pr = prow + (long long)opar * TRI_NWG * n;
-    const double* vb = vbuf + (long long)opar * n;
-    double part = 0.0;
-    for (int i = t.tid(); i < mo; i += t.nt()) {
-      double s = gld(pc + i);
-      for (int q = 0; q < TRI_NWG; ++q) s += gld(pr + (long long)q * n + i);
-      const double vi = gld(vb + i);
-      const double pp = tko * s;
-      vo[i] = vi;
-      pt[i] = pp;
-      part += vi * pp;
-      if (w == 0) gst(A + (long long)(k + i) + (long long)lda * (k - 1), vi);
-    }
-    const double K = 0.5 * tko * t.sum(part);
-    for (int i = t.tid(); i < mo; i += t.nt()) qo[i] = pt[i] - K * vo[i];
-    t.sync();
-  }
-  if (k == n - 2) {
-    // 2 x 2 tail
-    if (w == 0 && t.tid() == 0) {
-      double a00 = gld(A + (long long)k + (long long)lda * k);
-      double a10 = gld(A + (long long)(k + 1) + (long long)lda * k);
-      double a11 = gld(A + (long long)(k + 1) + (long long)lda * (k + 1));
-      if (k > 0) {
-        a00 -= vo[0] * qo[0] + qo[0] * vo[0];
-        a10 -= vo[1] * qo[0] + qo[1] * vo[0];
-        a11 -= vo[1] * qo[1] + qo[1] * vo[1];
-      }
-      d[k] = a00;
-      d[k + 1] = a11;
-      e[k] = a10;
-      e[k + 1] = 0.0;
-      tau[k] = 0.0;
-    }
-    return;
-  }
-  // phase B: column k -> reflector k
-  const int m = n - k - 1;
-  const bool upd = k > 0;
-  const double vo0 = upd ? vo[0] : 0.0, qo0 = upd ? qo[0] : 0.0;
-  double part = 0.0;
-  for (int i = t.tid(); i <= m; i += t.nt()) {
-    double a = gld(A + (long long)(k + i) + (long long)lda * k);
-    if (upd) a -= vo[i] * qo0 + qo[i] * vo0;
-    if (i >= 2) {
-      v[i - 1] = a;
-      part += a * a;
-    } else {
-      pt[i] = a;       // phase A's use of pt is over (it ended with a barrier)
-    }
-  }
-  const double a2 = t.sum(part);
-  const double a0 = pt[0], x0 = pt[1];
-  double beta = x0, v0 = 0.0, tk = 0.0;
-  if (a2 != 0.0) {
-    const double nrm = sqrt(x0 * x0 + a2);
-    beta = (x0 >= 0.0) ? -nrm : nrm;
-    v0 = x0 - beta;
-    tk = 2.0 / (v0 * v0 + a2);
-  }
-  if (a2 == 0.0) {
-    for (int i = t.tid(); i < m; i += t.nt()) v[i] = 0.0;
-  } else if (t.tid() == 0) {
-    v[0] = v0;
-  }
-  t.sync();
-  if (w == 0) {
-    if (t.tid() == 0) {
-      d[k] = a0;
-      e[k] = beta;
-      tau[k] = tk;
-    }
-    double* vb = vbuf + (long long)par * n;
-    for (int i = t.tid(); i < m; i += t.nt()) gst(vb + i, v[i]);
-  }
-  // phase C: this workgroup's columns of the trailing block
-  tri_step_pass<TRI_STEP_R, TRI_STEP_U>(t, A + (long long)(k + 1) + (long long)lda * (k + 1), lda, n, m,
-                                        w, v, vo + 1, qo + 1, upd, pcl,
-                                        prow + (long long)par * TRI_NWG * n + (long long)w * n,
-                                        pcol + (long long)par * n);
-}
-
 // Householder tridiagonalisation reading and updating only the lower
 // triangle of the symmetric A.  Same outputs as tridiagonalize().  v, p:
 // scratch of n doubles each (LDS on the device).
-// WIDE: instantiate the device path for orders up to 832 (TRI_WIDE_H row
-// groups of up to TRI_WIDE_R chunks of 64 rows).
-template <bool WIDE = false, class T>
+template <class T>
 __host__ __device__ void tridiagonalize_lower(T& t, double* A, int lda, int n, double* d, double* e,
-                                              double* tau, double* v, double* p,
-                                              double* scratch = nullptr, int scratch_size = 0) {
+                                              double* tau, double* v, double* p) {
   const int lane = t.tid() & 63, wv = t.tid() >> 6, nw = (t.nt() + 63) >> 6;
-  if constexpr (T::is_device && WIDE) {
-    if (n <= 64 * 13 && nw % TRI_WIDE_H == 0 && scratch &&
-        (TRI_WIDE_H + nw / TRI_WIDE_H + 1) * n <= scratch_size) {
-      tridiagonalize_fused<TRI_WIDE_R, TRI_WIDE_U, TRI_WIDE_H>(t, A, lda, n, d, e, tau, v, p, scratch);
-      return;
-    }
-  }
-  // Device path (tridiagonalize_fused) for n <= 512 with (waves + 2) * n
-  // doubles of LDS scratch: two row groups of up to 4 chunks of 64 rows, two
-  // columns per wave pass (within the 128 registers per lane of a 1024-lane
-  // workgroup).
-  if constexpr (T::is_device) {
-    if (n <= 64 * 8 && nw % TRI_H == 0 && scratch && (TRI_H + nw / TRI_H + 1) * n <= scratch_size) {
-      tridiagonalize_fused<TRI_R, TRI_U, TRI_H>(t, A, lda, n, d, e, tau, v, p, scratch);
-      return;
-    }
-  }
   for (int k = 0; k + 2 < n; ++k) {
     const int m = n - k - 1;
     double part = 0.0;
@@ -1487,7 +1045,7 @@ __host__ __device__ void syev_lowest(T& t, double* A, int lda, int n, int k, dou
   double* d = work;
   double* e = work + n;
   double* tau = work + 2 * n;
-  tridiagonalize_lower(t, A, lda, n, d, e, tau, lds, lds + n, lds + 2 * n, lds_size - 2 * n);
+  tridiagonalize_lower(t, A, lda, n, d, e, tau, lds, lds + n);
   tridiag_lowest(t, d, e, n, k, w, Z, ldz, work + 3 * n, cl, lds, lds_size);
   backtransform(t, A, lda, tau, n, Z, ldz, k, lds, lds_size);
 }

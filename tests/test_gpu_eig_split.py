@@ -24,7 +24,7 @@ def _check(M, w, Z, k):
 # workgroup, and all of them
 @pytest.mark.parametrize("n,k", [(2, 1), (3, 3), (9, 9), (10, 8), (63, 17), (64, 64), (65, 16), (128, 65),
                                  (129, 129), (256, 63), (257, 1), (448, 128), (449, 113), (512, 171),
-                                 (640, 16), (641, 200), (832, 278), (832, 832)])
+                                 (640, 16), (641, 200), (832, 278), (832, 832), (192, 64), (193, 65), (191, 30), (255, 255), (513, 40), (768, 9), (769, 9)])
 def test_orders_and_counts(n, k):
     import torch
     from paper_1506_08147_amd import small_syev
