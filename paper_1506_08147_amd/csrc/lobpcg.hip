@@ -9,6 +9,7 @@
 // cooperative routines of small_dense.h, all FP64.
 #include "common.h"
 #include "small_dense.h"
+#include "chol.h"
 #include "tri.h"
 
 namespace dg {
@@ -83,6 +84,7 @@ dg_teter_energy(Elem* __restrict__ E, const int* __restrict__ active, int na) {
 extern "C" __global__ void __launch_bounds__(SMALL_THREADS)
 dg_cholqr(Elem* __restrict__ E, const int* __restrict__ active, int na, int init) {
   __shared__ double red[32];
+  __shared__ double lds[CH_LDS];
   DevTeam t{red};
   const Elem& e = E[active[blockIdx.x]];
   const int n = e.J;
@@ -102,10 +104,10 @@ dg_cholqr(Elem* __restrict__ E, const int* __restrict__ active, int na, int init
     Ls[p] = G[p] / (dm[i] * dm[j]);
   }
   t.sync();
-  int ok = chol_lower(t, Ls, n, n, CHOL_TOL);
+  int ok = chol_any(t, Ls, n, n, CHOL_TOL, lds);
   if (ok) {
     double* Lt = sm(e, SM_A);
-    tri_inv_lower_t(t, Ls, n, Lt, n, n);   // Lt = L^-T
+    tri_inv_t_any(t, Ls, n, Lt, n, n, lds);   // Lt = L^-T
     for (int p = t.tid(); p < n * n; p += t.nt()) {
       int i = p % n;
       Tm[p] = Lt[p] / dm[i];
@@ -183,7 +185,8 @@ constexpr double CARRY_RES = 3e-5;
 extern "C" __global__ void __launch_bounds__(SMALL_THREADS)
 dg_rr_reduce(Elem* __restrict__ E, const int* __restrict__ active, int na, int single) {
   __shared__ double red[32];
-  __shared__ double tiles[(SMALL_THREADS / 64) * SYM_TILE_LDS];
+  __shared__ double lds[CH_LDS];
+  static_assert((SMALL_THREADS / 64) * SYM_TILE_LDS <= CH_LDS, "tiles of the symmetric fill");
   DevTeam t{red};
   const Elem& e = E[active[blockIdx.x]];
   const int J = e.J;
@@ -200,8 +203,8 @@ dg_rr_reduce(Elem* __restrict__ E, const int* __restrict__ active, int na, int s
   double* vec = sm(e, SM_V);
   double* dm = vec + 6 * n;
   double* w = vec + 7 * n;
-  sym_from_upper_tiles(t, H, n, n, tiles);
-  sym_from_upper_tiles(t, M, n, n, tiles);
+  sym_from_upper_tiles(t, H, n, n, lds);
+  sym_from_upper_tiles(t, M, n, n, lds);
   // a step on X alone (start, final check) leaves nothing to carry
   if (single && t.tid() == 0) e.fl[FL_CARRY] = 0;
   if (!single) {
@@ -237,10 +240,10 @@ dg_rr_reduce(Elem* __restrict__ E, const int* __restrict__ active, int na, int s
     A[p] = H[p] / (dm[i] * dm[j]);       // D^-1 Hh D^-1
   }
   t.sync();
-  int ok = chol_lower(t, Lm, n, n, CHOL_TOL);
+  int ok = chol_any(t, Lm, n, n, CHOL_TOL, lds);
   int nk = n;
   if (ok) {
-    tri_inv_lower_t(t, Lm, n, Tm, n, n);   // Tm = L^-T; products follow on dg_sgemm
+    tri_inv_t_any(t, Lm, n, Tm, n, n, lds);   // Tm = L^-T; products follow on dg_sgemm
     if (t.tid() == 0) e.fl[FL_RR_PATH] = 0;
     t.sync();
     return;
@@ -657,6 +660,7 @@ dg_rr_e(Elem* __restrict__ E, const int* __restrict__ active, int na, int single
 extern "C" __global__ void __launch_bounds__(SMALL_THREADS)
 dg_rr_dchol(Elem* __restrict__ E, const int* __restrict__ active, int na, int single) {
   __shared__ double red[32];
+  __shared__ double lds[CH_LDS];
   DevTeam t{red};
   const Elem& e = E[active[blockIdx.x]];
   const int J = e.J;
@@ -683,13 +687,13 @@ dg_rr_dchol(Elem* __restrict__ E, const int* __restrict__ active, int na, int si
       A[p] /= dm[i] * dm[j];
     }
     t.sync();
-    pok = chol_lower(t, A, J, J, CHOL_TOL);
+    pok = chol_any(t, A, J, J, CHOL_TOL, lds);
   }
   double rmax = 0.0;
   for (int i = t.tid(); i < e.jc; i += t.nt()) rmax = fmax(rmax, e.resid[i]);
   const bool carry = t.maxv(rmax) >= CARRY_RES || e.jc < J;
   if (pok) {
-    tri_inv_lower_t(t, A, J, Lm, J, J);                                   // Lm = L^-T
+    tri_inv_t_any(t, A, J, Lm, J, J, lds);                                   // Lm = L^-T
     for (int p = t.tid(); p < n * J; p += t.nt()) Ez[p] /= dm[p / n];
     if (t.tid() == 0) { e.fl[FL_HASP_NEXT] = 1; e.fl[FL_CARRY] = carry ? 2 * J : 0; }
   } else {

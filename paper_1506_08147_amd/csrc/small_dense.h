@@ -237,15 +237,15 @@ __host__ __device__ void tri_inv_lower(T& t, const double* L, int ldl, double* X
 // sum_{l<k} L[k][l] X[l][j]) / L[k][k], with thread j owning column j of
 // L^-1 stored as row j of Y.  All threads read the same L[k][l] at the same
 // time and neighbouring threads neighbouring entries of Y.
-// Device form: rows of L^-1 in blocks of B (B n <= 13312 doubles of L staged
-// in LDS); thread j carries the block's entries of its column in registers
-// and reads its earlier entries once per block.  Terms are summed in the same
-// order as below (ascending l, the structural zeros l < j skipped).
+// Device form: rows of L^-1 in blocks of B (B n doubles of L staged in LDS;
+// n <= lds_size); thread j carries the block's entries of its column in
+// registers and reads its earlier entries once per block.  Terms are summed
+// in the same order as below (ascending l, the structural zeros l < j skipped).
 template <class T>
-__device__ void tri_inv_lower_t_dev(T& t, const double* L, int ldl, double* Y, int ldy, int n) {
-  constexpr int LS = 16 * 832, BMAX = 16;   // blocks of 16 rows up to n = 832
-  __shared__ double Ls[LS];
-  int B = LS / n;
+__device__ void tri_inv_lower_t_dev(T& t, const double* L, int ldl, double* Y, int ldy, int n, double* Ls,
+                                    int lds_size) {
+  constexpr int BMAX = 16;
+  int B = lds_size / n;
   B = B > BMAX ? BMAX : B;
   for (int k0 = 0; k0 < n; k0 += B) {
     const int kb = n - k0 < B ? n - k0 : B, w = k0 + kb;
@@ -288,9 +288,10 @@ __device__ void tri_inv_lower_t_dev(T& t, const double* L, int ldl, double* Y, i
 }
 
 template <class T>
-__host__ __device__ void tri_inv_lower_t(T& t, const double* L, int ldl, double* Y, int ldy, int n) {
+__host__ __device__ void tri_inv_lower_t(T& t, const double* L, int ldl, double* Y, int ldy, int n,
+                                         double* lds = nullptr, int lds_size = 0) {
   if constexpr (T::is_device) {
-    if (n <= 4096) { tri_inv_lower_t_dev(t, L, ldl, Y, ldy, n); return; }
+    if (n <= lds_size) { tri_inv_lower_t_dev(t, L, ldl, Y, ldy, n, lds, lds_size); return; }
   }
   for (int j = t.tid(); j < n; j += t.nt()) {
     for (int k = 0; k < n; ++k) {
