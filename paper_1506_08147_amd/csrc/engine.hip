@@ -577,7 +577,7 @@ struct dgdft_alb {
     auto P = make_prefix(act, [](int) { return 1; });
     if (P.na == 0) return;
     pbeg(DGDFT_K_RR, 0, 0);
-    hipLaunchKernelGGL(dg_small_copy, dim3(P.na), dim3(256), 0, stream, ed, P.active, P.na, a);
+    hipLaunchKernelGGL(dg_small_copy, dim3(P.na, RR_NY), dim3(256), 0, stream, ed, P.active, P.na, a);
     pend();
     HCHECK(hipGetLastError());
   }
@@ -622,11 +622,12 @@ struct dgdft_alb {
     HCHECK(hipGetLastError());
   }
 
+  // one workgroup per element (ny = 1), or RR_NY
   void rr_one(const std::vector<int>& act, void (*k)(Elem*, const int*, int, int), int threads,
-              int single) {
+              int single, int ny = 1) {
     auto P = make_prefix(act, [&](int) { return 1; });
     pbeg(DGDFT_K_RR, 0, 0);
-    hipLaunchKernelGGL(k, dim3(P.na), dim3(threads), 0, stream, ed, P.active, P.na, single);
+    hipLaunchKernelGGL(k, dim3(P.na, ny), dim3(threads), 0, stream, ed, P.active, P.na, single);
     pend();
     HCHECK(hipGetLastError());
   }
@@ -716,7 +717,7 @@ struct dgdft_alb {
     if (!single && kny) {
       // basis S = [X P W]: keep S^T S, S^T H S as formed; orthonormalise
       // the P block against [X W] in small space (see lobpcg.hip)
-      rr_one(act, dg_rr_prep, 256, single);
+      rr_one(act, dg_rr_prep, 256, single, RR_NY);
       ap = with_p(act);
       if (!ap.empty()) {
         // Z = (2I - M_QQ) M_QP in the X and W rows of SM_U (Q = [X W]):
@@ -746,9 +747,10 @@ struct dgdft_alb {
         sg(ap, sga(1, 0, SM_MC, SM_U, SM_A, Jc, Jc, N, N, N, Jc, 1.0, 0.0));
         sg(ap, sga(0, 0, SM_M, SM_MC, SM_Z, N, Jc, N, N, N, N, 1.0, 0.0));
         sg(ap, sga(1, 0, SM_MC, SM_Z, SM_W0, Jc, Jc, N, N, N, Jc, 1.0, 0.0));
-        rr_one(ap, dg_rr_pscatter, 256, single);
+        rr_one(ap, dg_rr_pscatter, 256, single, RR_NY);
       }
     }
+    rr_one(act, dg_rr_fill, 256, single, RR_NY);
     rr_one(act, dg_rr_reduce, SMALL_THREADS, single);
     // path 0: A = L^-1 A L^-T with SM_T = L^-T
     sgemm(act, single, 1, 0, SM_T, 0, SM_A, 0, SM_U, 0, N, N, N, N, N, N, 1.0, 0.0, 0);
@@ -756,13 +758,13 @@ struct dgdft_alb {
     if (!single) {
       // path 2: A = Hh - sym(E Hh)
       sgemm(act, single, 0, 1, SM_L, 0, SM_H, 0, SM_U, 0, N, N, N, N, N, N, 1.0, 0.0, 2);
-      rr_one(act, dg_rr_form, 256, single);
+      rr_one(act, dg_rr_form, 256, single, RR_NY);
     }
     if (!single) {
       // path 3: E^2, E^3, T = series, A = T Hh T
       sgemm(act, single, 0, 0, SM_L, 0, SM_L, 0, SM_U, 0, N, N, N, N, N, N, 1.0, 0.0, 3);
       sgemm(act, single, 0, 0, SM_L, 0, SM_U, 0, SM_A, 0, N, N, N, N, N, N, 1.0, 0.0, 3);
-      rr_one(act, dg_rr_series, 256, single);
+      rr_one(act, dg_rr_series, 256, single, RR_NY);
       sgemm(act, single, 0, 0, SM_H, 0, SM_T, 0, SM_U, 0, N, N, N, N, N, N, 1.0, 0.0, 3);
       sgemm(act, single, 0, 0, SM_T, 0, SM_U, 0, SM_A, 0, N, N, N, N, N, N, 1.0, 0.0, 3);
     }
@@ -773,10 +775,10 @@ struct dgdft_alb {
     if (!single) sgemm(act, single, 0, 0, SM_T, 0, SM_Z, 0, SM_C, 0, N, Jc, N, N, N, N, 1.0, 0.0, 3);
     if (!single) {
       // path 2: C = Y - E Y / 2
-      rr_one(act, dg_rr_cinit, 256, single);
+      rr_one(act, dg_rr_cinit, 256, single, RR_NY);
       sgemm(act, single, 0, 0, SM_L, 0, SM_Z, 0, SM_C, 0, N, Jc, N, N, N, N, -0.5, 1.0, 2);
     }
-    rr_one(act, dg_rr_post, 256, single);
+    rr_one(act, dg_rr_post, 256, single, RR_NY);
     if (single) return;
     if (!kny) {
       rr_tail_ortho(act);
@@ -789,7 +791,7 @@ struct dgdft_alb {
       sg(ap, sga(0, 0, SM_MC, SM_A, SM_C, N, Jc, Jc, N, Jc, N, 1.0, 1.0));
     }
     // E = C with its X rows zeroed (next to C); P present next; carry flag
-    rr_one(act, dg_rr_e, 256, single);
+    rr_one(act, dg_rr_e, 256, single, RR_NY);
     // [C E]^T M [C E] and [C E]^T Hh [C E] in the basis as formed: the
     // [X' P'] blocks of the next step's S^T S and S^T H S (dg_carry_in)
     const int J2 = 2;
@@ -825,7 +827,7 @@ struct dgdft_alb {
     auto P = make_prefix(act, [](int) { return 1; });
     if (P.na == 0) return;
     pbeg(DGDFT_K_RR, 0, 0);
-    hipLaunchKernelGGL(dg_carry_in, dim3(P.na), dim3(256), 0, stream, ed, P.active, P.na);
+    hipLaunchKernelGGL(dg_carry_in, dim3(P.na, RR_NY), dim3(256), 0, stream, ed, P.active, P.na);
     pend();
     HCHECK(hipGetLastError());
   }

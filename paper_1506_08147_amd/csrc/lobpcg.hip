@@ -74,6 +74,45 @@ dg_teter_energy(Elem* __restrict__ E, const int* __restrict__ active, int na) {
   }
 }
 
+// Passes over the small matrices (order n = kJ) run on RR_NY workgroups per
+// element (grid (elements, RR_NY)), by columns or by 32 x 32 tiles of the lower
+// triangle: one workgroup per element spent 0.1-2 ms on each pass of an order
+// 800 matrix at the latency of its few loads in flight.
+constexpr int RR_NY = 64;
+constexpr int SYT = 32;
+struct SymTile {
+  double v[SYT][SYT + 1];
+};
+
+// f(bi, bj) for this workgroup's tiles, block row bi >= block column bj.
+template <class F>
+__device__ __forceinline__ void for_sym_tiles(int n, F f) {
+  const int nb = cdiv(n, SYT), nt = nb * (nb + 1) / 2;
+  for (int q = blockIdx.y; q < nt; q += gridDim.y) {
+    int bi = (int)((sqrt(8.0 * q + 1.0) - 1.0) * 0.5);
+    while ((bi + 1) * (bi + 2) / 2 <= q) ++bi;
+    while (bi * (bi + 1) / 2 > q) --bi;
+    f(bi, q - bi * (bi + 1) / 2);
+  }
+}
+
+// v[c][r] = A[br SYT + r][bc SYT + c] (256 lanes).
+__device__ __forceinline__ void load_tile(SymTile& t, const double* A, int n, int br, int bc) {
+  const int r = threadIdx.x % SYT, row = br * SYT + r;
+#pragma unroll
+  for (int c = threadIdx.x / SYT; c < SYT; c += 256 / SYT) {
+    const int col = bc * SYT + c;
+    t.v[c][r] = (row < n && col < n) ? gld(A + row + (long long)n * col) : 0.0;
+  }
+}
+
+// f(r, c) over the entries of a tile, lanes along r.
+template <class F>
+__device__ __forceinline__ void for_tile(F f) {
+#pragma unroll
+  for (int c = threadIdx.x / SYT; c < SYT; c += 256 / SYT) f((int)(threadIdx.x % SYT), c);
+}
+
 // Orthonormalising transform of a block Y with Gram G = Y^T Y (J x J, upper
 // triangle in SM_G): T = D^-1 L^-T from a Cholesky of the unit-diagonal
 // D^-1 G D^-1 = L L^T (CholQR), or, if a pivot falls below CHOL_TOL, the
@@ -93,25 +132,24 @@ dg_cholqr(Elem* __restrict__ E, const int* __restrict__ active, int na, int init
   double* Tm = sm(e, SM_T);
   double* vec = sm(e, SM_V);
   double* dm = vec + 6 * n;
-  sym_from_upper(t, G, n, n);
+  static_assert((SMALL_THREADS / 64) * SYM_TILE_LDS <= CH_LDS, "tiles of the symmetric fill");
+  sym_from_upper_tiles(t, G, n, n, lds);
   for (int i = t.tid(); i < n; i += t.nt()) {
     double d = sqrt(fmax(G[i + (long long)n * i], 0.0));
     dm[i] = d > 0.0 ? d : 1.0;
   }
   t.sync();
-  for (int p = t.tid(); p < n * n; p += t.nt()) {
-    int i = p % n, j = p / n;
-    Ls[p] = G[p] / (dm[i] * dm[j]);
-  }
+  const int lane = t.tid() & 63, wv = t.tid() >> 6, nw = t.nt() >> 6;
+  for (int j = wv; j < n; j += nw)
+    for (int i = lane; i < n; i += 64)
+      gst(Ls + i + (long long)n * j, gld(G + i + (long long)n * j) / (dm[i] * dm[j]));
   t.sync();
   int ok = chol_any(t, Ls, n, n, CHOL_TOL, lds);
   if (ok) {
     double* Lt = sm(e, SM_A);
     tri_inv_t_any(t, Ls, n, Lt, n, n, lds);   // Lt = L^-T
-    for (int p = t.tid(); p < n * n; p += t.nt()) {
-      int i = p % n;
-      Tm[p] = Lt[p] / dm[i];
-    }
+    for (int j = wv; j < n; j += nw)
+      for (int i = lane; i < n; i += 64) gst(Tm + i + (long long)n * j, gld(Lt + i + (long long)n * j) / dm[i]);
     if (init == 2 && t.tid() == 0) e.fl[FL_PDROP_NOW] = 0;
     t.sync();
     return;
@@ -182,11 +220,51 @@ constexpr double SERIES_ORTHO = 1e-4;
 // 1.5% less time).
 constexpr double CARRY_RES = 3e-5;
 
+// Lower triangles of Hh and M from their upper ones; beyond the step on X alone
+// also E = M - I (SM_L) and this workgroup's share of ||E||_F^2 (SM_W0[y]).
+extern "C" __global__ void __launch_bounds__(256)
+dg_rr_fill(Elem* __restrict__ E, const int* __restrict__ active, int na, int single) {
+  __shared__ SymTile th, tm;
+  __shared__ double red[4];
+  const Elem& e = E[active[blockIdx.x]];
+  const int n = (single ? 1 : (has_p(e) ? 3 : 2)) * e.J;
+  double* H = sm(e, SM_H);
+  double* M = sm(e, SM_M);
+  double* L = sm(e, SM_L);
+  double ef = 0.0;
+  for_sym_tiles(n, [&](int bi, int bj) {
+    load_tile(th, H, n, bj, bi);
+    load_tile(tm, M, n, bj, bi);
+    __syncthreads();
+    for_tile([&](int r, int c) {
+      const int row = bi * SYT + r, col = bj * SYT + c;
+      if (row < n && col < n && row > col) {
+        const double mv = tm.v[r][c];
+        gst(H + row + (long long)n * col, th.v[r][c]);
+        gst(M + row + (long long)n * col, mv);
+        if (!single) gst(L + row + (long long)n * col, mv);
+        ef += 2.0 * mv * mv;
+      }
+      const int ur = bj * SYT + r, uc = bi * SYT + c;
+      if (!single && ur < n && uc < n && ur <= uc) {
+        const double v = tm.v[c][r] - (ur == uc ? 1.0 : 0.0);
+        gst(L + ur + (long long)n * uc, v);
+        if (ur == uc) ef += v * v;
+      }
+    });
+    __syncthreads();
+  });
+  if (single) return;
+  ef = wave_sum(ef);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = ef;
+  __syncthreads();
+  if (threadIdx.x == 0) sm(e, SM_W0)[blockIdx.y] = (red[0] + red[1]) + (red[2] + red[3]);
+}
+
 extern "C" __global__ void __launch_bounds__(SMALL_THREADS)
 dg_rr_reduce(Elem* __restrict__ E, const int* __restrict__ active, int na, int single) {
   __shared__ double red[32];
   __shared__ double lds[CH_LDS];
-  static_assert((SMALL_THREADS / 64) * SYM_TILE_LDS <= CH_LDS, "tiles of the symmetric fill");
   DevTeam t{red};
   const Elem& e = E[active[blockIdx.x]];
   const int J = e.J;
@@ -203,28 +281,18 @@ dg_rr_reduce(Elem* __restrict__ E, const int* __restrict__ active, int na, int s
   double* vec = sm(e, SM_V);
   double* dm = vec + 6 * n;
   double* w = vec + 7 * n;
-  sym_from_upper_tiles(t, H, n, n, lds);
-  sym_from_upper_tiles(t, M, n, n, lds);
   // a step on X alone (start, final check) leaves nothing to carry
   if (single && t.tid() == 0) e.fl[FL_CARRY] = 0;
   if (!single) {
-    const int lane = t.tid() & 63, wv = t.tid() >> 6, nw = t.nt() >> 6;
+    const double* part = sm(e, SM_W0);
     double ef = 0.0;
-    for (int j = wv; j < n; j += nw)
-      for (int i = lane; i < n; i += 64) {
-        const double v = gld(M + i + (long long)n * j) - (i == j ? 1.0 : 0.0);
-        ef += v * v;
-      }
-    ef = sqrt(t.sum(ef));   // ||E||_F >= ||E||_2
+    for (int q = 0; q < RR_NY; ++q) ef += part[q];
+    ef = sqrt(ef);          // ||E||_F >= ||E||_2; E = M - I is in SM_L (dg_rr_fill)
     if (ef <= SERIES_ORTHO) {
-      for (int j = wv; j < n; j += nw)
-        for (int i = lane; i < n; i += 64)
-          gst(Lm + i + (long long)n * j, gld(M + i + (long long)n * j) - (i == j ? 1.0 : 0.0));   // E
       if (t.tid() == 0) {
         e.fl[FL_RR_PATH] = ef <= NEAR_ORTHO ? 2 : 3;
         e.fl[FL_RR_NSERIES] += 1;
       }
-      t.sync();
       return;
     }
   }
@@ -234,11 +302,14 @@ dg_rr_reduce(Elem* __restrict__ E, const int* __restrict__ active, int na, int s
     dm[i] = d > 0.0 ? d : 1.0;
   }
   t.sync();
-  for (int p = t.tid(); p < n * n; p += t.nt()) {
-    int i = p % n, j = p / n;
-    Lm[p] = M[p] / (dm[i] * dm[j]);
-    A[p] = H[p] / (dm[i] * dm[j]);       // D^-1 Hh D^-1
-  }
+  const int lane = t.tid() & 63, wv = t.tid() >> 6, nw = t.nt() >> 6;
+  for (int j = wv; j < n; j += nw)
+    for (int i = lane; i < n; i += 64) {
+      const long long p = i + (long long)n * j;
+      const double dd = dm[i] * dm[j];
+      gst(Lm + p, gld(M + p) / dd);
+      gst(A + p, gld(H + p) / dd);       // D^-1 Hh D^-1
+    }
   t.sync();
   int ok = chol_any(t, Lm, n, n, CHOL_TOL, lds);
   int nk = n;
@@ -286,27 +357,33 @@ dg_rr_reduce(Elem* __restrict__ E, const int* __restrict__ active, int na, int s
   if (t.tid() == 0) e.fl[FL_RR_PATH] = 1;
 }
 
-// Path 2: A = Hh - (U + U^T)/2 with U = E Hh.
+// Path 2: A = Hh - (U + U^T)/2 with U = E Hh, the lower triangle (all that
+// the tridiagonalisation reads).
 extern "C" __global__ void __launch_bounds__(256)
 dg_rr_form(Elem* __restrict__ E, const int* __restrict__ active, int na, int single) {
+  __shared__ SymTile tu;
   const Elem& e = E[active[blockIdx.x]];
   if (e.fl[FL_RR_PATH] != 2) return;
-  const int J = e.J;
-  const int n = (single ? 1 : (has_p(e) ? 3 : 2)) * J;
+  const int n = (single ? 1 : (has_p(e) ? 3 : 2)) * e.J;
   const double* H = sm(e, SM_H);
   const double* U = sm(e, SM_U);
   double* A = sm(e, SM_A);
-  for (int p = threadIdx.x; p < n * n; p += blockDim.x) {
-    int i = p % n, j = p / n;
-    A[p] = H[p] - 0.5 * (U[p] + U[j + (long long)n * i]);
-  }
+  for_sym_tiles(n, [&](int bi, int bj) {
+    load_tile(tu, U, n, bj, bi);
+    __syncthreads();
+    for_tile([&](int r, int c) {
+      const int row = bi * SYT + r, col = bj * SYT + c;
+      const long long p = row + (long long)n * col;
+      if (row < n && row >= col) gst(A + p, gld(H + p) - 0.5 * (gld(U + p) + tu.v[r][c]));
+    });
+    __syncthreads();
+  });
 }
 
 // [X P] block of S^T S and S^T H S from the last step: with X' = S C and
 // P' = S D, [X' P']^T [X' P'] = [C D]^T M [C D] and likewise for H, which the
 // last step left in SM_MC and SM_HC.  Overwrites the leading kc x kc block of
-// both products (the tiles there were not computed).  One workgroup per
-// element.
+// both products (the tiles there were not computed).
 extern "C" __global__ void __launch_bounds__(256)
 dg_carry_in(Elem* __restrict__ E, const int* __restrict__ active, int na) {
   const Elem& e = E[active[blockIdx.x]];
@@ -317,11 +394,11 @@ dg_carry_in(Elem* __restrict__ E, const int* __restrict__ active, int na) {
   double* H = sm(e, SM_H);
   const double* Mc = sm(e, SM_MC);
   const double* Hc = sm(e, SM_HC);
-  for (int p = threadIdx.x; p < kc * kc; p += 256) {
-    int i = p % kc, j = p / kc;
-    M[i + (long long)n * j] = Mc[i + (long long)ldc * j];
-    H[i + (long long)n * j] = Hc[i + (long long)ldc * j];
-  }
+  for (int j = blockIdx.y; j < kc; j += gridDim.y)
+    for (int i = threadIdx.x; i < kc; i += 256) {
+      gst(M + i + (long long)n * j, gld(Mc + i + (long long)ldc * j));
+      gst(H + i + (long long)n * j, gld(Hc + i + (long long)ldc * j));
+    }
 }
 
 // The eigensolver of the Rayleigh-Ritz step: tridiagonalisation (tri.h: in
@@ -446,10 +523,11 @@ dg_rr_series(Elem* __restrict__ E, const int* __restrict__ active, int na, int s
   const double* E2 = sm(e, SM_U);
   const double* E3 = sm(e, SM_A);
   double* Tm = sm(e, SM_T);
-  for (int p = threadIdx.x; p < n * n; p += blockDim.x) {
-    int i = p % n, j = p / n;
-    Tm[p] = (i == j ? 1.0 : 0.0) - 0.5 * Em[p] + 0.375 * E2[p] - 0.3125 * E3[p];
-  }
+  for (int j = blockIdx.y; j < n; j += gridDim.y)
+    for (int i = threadIdx.x; i < n; i += 256) {
+      const long long p = i + (long long)n * j;
+      gst(Tm + p, (i == j ? 1.0 : 0.0) - 0.5 * gld(Em + p) + 0.375 * gld(E2 + p) - 0.3125 * gld(E3 + p));
+    }
 }
 
 // Path 2: C = Y (the E Y / 2 correction follows on dg_sgemm).
@@ -461,7 +539,7 @@ dg_rr_cinit(Elem* __restrict__ E, const int* __restrict__ active, int na, int si
   const int n = (single ? 1 : (has_p(e) ? 3 : 2)) * J;
   const double* Z = sm(e, SM_Z);
   double* Cm = sm(e, SM_C);
-  for (int p = threadIdx.x; p < n * J; p += blockDim.x) Cm[p] = Z[p];
+  for (int p = blockIdx.y * 256 + threadIdx.x; p < n * J; p += gridDim.y * 256) gst(Cm + p, gld(Z + p));
 }
 
 // Ritz values; path 0: undo the diagonal scaling of C.
@@ -477,9 +555,11 @@ dg_rr_post(Elem* __restrict__ E, const int* __restrict__ active, int na, int sin
   const double* dm = vec + 6 * n;
   const double* w = vec + 7 * n;
   if (path == 0)
-    for (int p = threadIdx.x; p < n * J; p += blockDim.x) Cm[p] /= dm[p % n];
+    for (int j = blockIdx.y; j < J; j += gridDim.y)
+      for (int i = threadIdx.x; i < n; i += 256) Cm[i + (long long)n * j] /= dm[i];
+  if (blockIdx.y > 0) return;
   if (path != 1)
-    for (int j = threadIdx.x; j < J; j += blockDim.x) e.theta[j] = w[j];
+    for (int j = threadIdx.x; j < J; j += 256) e.theta[j] = w[j];
   if (kb == 1 && threadIdx.x == 0) e.fl[FL_HASP_NEXT] = 0;
 }
 
@@ -534,17 +614,17 @@ dg_small_copy(Elem* __restrict__ E, const int* __restrict__ active, int na, CpAr
   auto off = [&](int c) { return (c >= 0 ? c : kb - 1) * J; };
   const double* S = sm(e, a.ms) + (long long)off(a.cs) * lds + off(a.rs);
   double* D = sm(e, a.md) + (long long)off(a.cd) * ldd + off(a.rd);
-  for (int p = threadIdx.x; p < R * Cn; p += blockDim.x) {
-    const int i = p % R, j = p / R;
-    double v;
-    switch (a.mode) {
-      case 0: v = S[i + (long long)lds * j]; break;
-      case 1: v = S[j + (long long)lds * i]; break;
-      case 2: v = i == j ? 1.0 : 0.0; break;
-      default: v = 0.0;
+  for (int j = blockIdx.y; j < Cn; j += gridDim.y)
+    for (int i = threadIdx.x; i < R; i += 256) {
+      double v;
+      switch (a.mode) {
+        case 0: v = gld(S + i + (long long)lds * j); break;
+        case 1: v = gld(S + j + (long long)lds * i); break;
+        case 2: v = i == j ? 1.0 : 0.0; break;
+        default: v = 0.0;
+      }
+      gst(D + i + (long long)ldd * j, a.alpha * v);
     }
-    D[i + (long long)ldd * j] = a.alpha * v;
-  }
 }
 
 // Start of the Rayleigh-Ritz step: full symmetric S^T S and S^T H S from
@@ -553,35 +633,50 @@ dg_small_copy(Elem* __restrict__ E, const int* __restrict__ active, int na, CpAr
 // start of its Schur complement.
 extern "C" __global__ void __launch_bounds__(256)
 dg_rr_prep(Elem* __restrict__ E, const int* __restrict__ active, int na, int single) {
+  __shared__ SymTile th, tm;
   const Elem& e = E[active[blockIdx.x]];
   const int J = e.J;
-  const int n = (has_p(e) ? 3 : 2) * J;
+  const bool p3 = has_p(e);
+  const int n = (p3 ? 3 : 2) * J;
   double* M = sm(e, SM_M);
   double* H = sm(e, SM_H);
   double* Mo = sm(e, SM_MO);
   double* Ho = sm(e, SM_HO);
-  for (int p = threadIdx.x; p < n * n; p += blockDim.x) {
-    const int i = p % n, j = p / n;
-    const long long q = i <= j ? p : j + (long long)n * i;
-    const double mv = M[q], hv = H[q];
-    Mo[p] = mv;
-    Ho[p] = hv;
-  }
-  __syncthreads();
-  for (int p = threadIdx.x; p < n * n; p += blockDim.x) {
-    M[p] = Mo[p];
-    H[p] = Ho[p];
-  }
-  if (has_p(e))
-    for (int p = threadIdx.x; p < J * J; p += blockDim.x) {
-      const int i = p % J, j = p / J;
-      sm(e, SM_G)[p] = M[(J + i) + (long long)n * (J + j)];
-    }
+  double* G = sm(e, SM_G);
+  for_sym_tiles(n, [&](int bi, int bj) {
+    load_tile(th, H, n, bj, bi);
+    load_tile(tm, M, n, bj, bi);
+    __syncthreads();
+    for_tile([&](int r, int c) {
+      // lower entry (row, col) from the transposed tile
+      const int row = bi * SYT + r, col = bj * SYT + c;
+      if (row < n && col < row) {
+        const long long p = row + (long long)n * col;
+        const double hv = th.v[r][c], mv = tm.v[r][c];
+        gst(H + p, hv);
+        gst(Ho + p, hv);
+        gst(M + p, mv);
+        gst(Mo + p, mv);
+        if (p3 && col >= J && row < 2 * J) gst(G + (row - J) + J * (col - J), mv);
+      }
+      // upper entry
+      const int ur = bj * SYT + r, uc = bi * SYT + c;
+      if (uc < n && ur <= uc) {
+        const long long p = ur + (long long)n * uc;
+        const double mv = tm.v[c][r];
+        gst(Ho + p, th.v[c][r]);
+        gst(Mo + p, mv);
+        if (p3 && ur >= J && uc < 2 * J) gst(G + (ur - J) + J * (uc - J), mv);
+      }
+    });
+    __syncthreads();
+  });
 }
 
 // P column block of B^T Hh B and B^T M B: from U_H = Hh B_P (SM_U, n x J),
 // B_P^T U_H (SM_A, J x J), U_M = M B_P (SM_Z) and B_P^T U_M (SM_W0), write
-// column block P, row block P and the P-P block of Hh and M (elements with P).
+// the upper triangles of Hh and M (elements with P): the X-P block, the P-W
+// block (transposed, by tiles) and the P-P block; dg_rr_fill follows.
 // When the step dropped P (B_P = 0), the P-P blocks become M = I and
 // Hh = sigma I with no coupling, sigma = 2 max_i |Hh_ii| + 1 over the X and W
 // rows: every Ritz value of [X W] that the step keeps lies below sigma (the
@@ -591,6 +686,7 @@ dg_rr_prep(Elem* __restrict__ E, const int* __restrict__ active, int na, int sin
 extern "C" __global__ void __launch_bounds__(256)
 dg_rr_pscatter(Elem* __restrict__ E, const int* __restrict__ active, int na, int single) {
   __shared__ double red[4];
+  __shared__ SymTile th, tm;
   const Elem& e = E[active[blockIdx.x]];
   if (!has_p(e)) return;
   const int J = e.J, n = 3 * J;
@@ -611,18 +707,36 @@ dg_rr_pscatter(Elem* __restrict__ E, const int* __restrict__ active, int na, int
     __syncthreads();
     sigma = 2.0 * fmax(fmax(red[0], red[1]), fmax(red[2], red[3])) + 1.0;
   }
-  for (int p = threadIdx.x; p < n * J; p += blockDim.x) {
-    const int i = p % n, j = p / n;
-    if (i >= J && i < 2 * J) continue;
-    H[i + (long long)n * (J + j)] = Uh[p];
-    H[(J + j) + (long long)n * i] = Uh[p];
-    M[i + (long long)n * (J + j)] = Um[p];
-    M[(J + j) + (long long)n * i] = Um[p];
+  for (int j = blockIdx.y; j < J; j += gridDim.y) {
+    const long long c = (long long)n * (J + j);
+    for (int i = threadIdx.x; i < J; i += 256) {
+      gst(H + i + c, gld(Uh + i + (long long)n * j));
+      gst(M + i + c, gld(Um + i + (long long)n * j));
+      if (i <= j) {
+        gst(H + (J + i) + c, dropped ? (i == j ? sigma : 0.0) : gld(Hpp + i + (long long)J * j));
+        gst(M + (J + i) + c, dropped ? (i == j ? 1.0 : 0.0) : gld(Mpp + i + (long long)J * j));
+      }
+    }
   }
-  for (int p = threadIdx.x; p < J * J; p += blockDim.x) {
-    const int i = p % J, j = p / J;
-    H[(J + i) + (long long)n * (J + j)] = dropped ? (i == j ? sigma : 0.0) : Hpp[p];
-    M[(J + i) + (long long)n * (J + j)] = dropped ? (i == j ? 1.0 : 0.0) : Mpp[p];
+  // rows 2J + i of U -> H[J + j][2J + i]
+  const int nb = cdiv(J, SYT);
+  for (int q = blockIdx.y; q < nb * nb; q += gridDim.y) {
+    const int i0 = (q % nb) * SYT, j0 = (q / nb) * SYT;
+    for_tile([&](int r, int c) {
+      const bool in = i0 + r < J && j0 + c < J;
+      const long long p = (2 * J + i0 + r) + (long long)n * (j0 + c);
+      th.v[c][r] = in ? gld(Uh + p) : 0.0;
+      tm.v[c][r] = in ? gld(Um + p) : 0.0;
+    });
+    __syncthreads();
+    for_tile([&](int r, int c) {
+      if (j0 + r < J && i0 + c < J) {
+        const long long p = (J + j0 + r) + (long long)n * (2 * J + i0 + c);
+        gst(H + p, th.v[r][c]);
+        gst(M + p, tm.v[r][c]);
+      }
+    });
+    __syncthreads();
   }
 }
 
@@ -638,7 +752,10 @@ dg_rr_e(Elem* __restrict__ E, const int* __restrict__ active, int na, int single
   const int J = e.J;
   const int n = (has_p(e) ? 3 : 2) * J;
   double* Cm = sm(e, SM_C);
-  for (int p = threadIdx.x; p < n * J; p += blockDim.x) Cm[(long long)n * J + p] = (p % n) < J ? 0.0 : Cm[p];
+  for (int j = blockIdx.y; j < J; j += gridDim.y)
+    for (int i = threadIdx.x; i < n; i += 256)
+      gst(Cm + i + (long long)n * (J + j), i < J ? 0.0 : gld(Cm + i + (long long)n * j));
+  if (blockIdx.y > 0) return;
   double rmax = 0.0;
   for (int i = threadIdx.x; i < e.jc; i += blockDim.x) rmax = fmax(rmax, e.resid[i]);
   for (int o = 32; o > 0; o >>= 1) rmax = fmax(rmax, __shfl_xor(rmax, o, 64));
