@@ -56,6 +56,7 @@ struct Elem {
   const double* kbt_c;       // gamma_p * beta_p(r)
   double* small;             // per-element small dense workspace
   double* gpart;             // Gram split-K partial sums
+  long long gpart_cap;       // doubles in gpart
   long long small_stride;    // doubles per n x n matrix in `small`
   int* fl;                   // FL_COUNT status words, read back by the host
   long long off_ng, off_ngj, off_j, off_alb, off_nalb;   // offsets in batch arrays
@@ -191,26 +192,10 @@ __device__ inline int find_elem(const int* __restrict__ prefix, int na, int b) {
 
 // ---- work decomposition shared by host (counts) and device (decode) ----
 constexpr int GT = 128;           // row tile of the Gram and update products
-constexpr int GRAM_MAXCHUNK = 8;
+constexpr int GRAM_MAXCHUNK = 8;  // largest tuned split
+constexpr int GRAM_CHUNKS = 48;   // largest split of the default rule
 
 __host__ __device__ inline int cdiv(int a, int b) { return (a + b - 1) / b; }
-
-__host__ __device__ inline int gram_nchunk(int K) {
-  int c = cdiv(K, 4096);
-  return c < 1 ? 1 : (c > GRAM_MAXCHUNK ? GRAM_MAXCHUNK : c);
-}
-// chunk count of an element's product over K rows: its tuned value for
-// N_g-long products (at most GRAM_MAXCHUNK), else the default rule
-__host__ __device__ inline int gram_nchunk_e(const Elem& e, int K) {
-  if (e.gram_split > 0 && K == e.ng) {
-    int c = e.gram_split > GRAM_MAXCHUNK ? GRAM_MAXCHUNK : e.gram_split;
-    int cmax = cdiv(K, 16);
-    return c > cmax ? cmax : c;
-  }
-  return gram_nchunk(K);
-}
-// chunk length, a multiple of 16
-__host__ __device__ inline int gram_chunklen(int K, int nchunk) { return cdiv(cdiv(K, nchunk), 16) * 16; }
 
 // Column tile of the update products for d columns: the d columns split
 // evenly over the fewest tiles of at most TMAX columns, rounded up to the
@@ -222,5 +207,43 @@ __host__ __device__ inline int tile_edge(int d) {
   int t = cdiv(d, TMAX);
   return cdiv(cdiv(d, t), 16) * 16;
 }
+
+// Split-K chunks of a Gram product of m x n (per job; nsum over its jobs) over
+// K rows.  An element's products alone have a handful of tiles (one 96 x 32
+// tile at 32 states), so K is split as far as the partial tiles stay cheap: a
+// chunk of R rows reads R (tm + tn) entries and writes and re-reads tm tn, so
+// R = 32 tm tn / (tm + tn) keeps the partials at a sixteenth of the reads --
+// and at most as far as the element's partial buffer holds.  By the shape
+// alone, never by the batch, so that an element gives the same sums in any
+// batch.  Measured against at most 8 chunks of 4096 rows (128 items on 512
+// places): four products 432 x 144 over 77760 rows 1.97 -> 1.74 ms a call with
+// 35 chunks (560 items: a second, nearly empty round, hence the rounding); 96 x 32 over 13824
+// rows, four elements, 255 -> 60 us a launch.
+__host__ __device__ inline int gram_nchunk(int K, int m, int n, int nsum, long long cap) {
+  const int tm = m < GT ? m : GT, tn = tile_edge(n);
+  int c = cdiv(K, 4096);
+  c = c > GRAM_MAXCHUNK ? GRAM_MAXCHUNK : c;
+  const int r = K / (32 * tm * tn / (tm + tn) + 1);
+  c = c > r ? c : r;
+  c = c > GRAM_CHUNKS ? GRAM_CHUNKS : c;
+  // whole multiples of 64 items, so that a few elements fill their last round
+  const int nt = cdiv(m, GT) * cdiv(n, tn) * (nsum > n ? 2 : 1);
+  if (c * nt > 64) c = c * nt / 64 * 64 / nt;
+  const long long fit = m > 0 && nsum > 0 ? cap / ((long long)m * nsum) : c;
+  c = c > fit ? (int)fit : c;
+  return c < 1 ? 1 : c;
+}
+// chunk count of an element's product over K rows: its tuned value for
+// N_g-long products (at most GRAM_MAXCHUNK), else the default rule
+__host__ __device__ inline int gram_nchunk_e(const Elem& e, int K, int m, int n, int nsum) {
+  if (e.gram_split > 0 && K == e.ng) {
+    int c = e.gram_split > GRAM_MAXCHUNK ? GRAM_MAXCHUNK : e.gram_split;
+    int cmax = cdiv(K, 16);
+    return c > cmax ? cmax : c;
+  }
+  return gram_nchunk(K, m, n, nsum, e.gpart_cap);
+}
+// chunk length, a multiple of 16
+__host__ __device__ inline int gram_chunklen(int K, int nchunk) { return cdiv(cdiv(K, nchunk), 16) * 16; }
 
 }  // namespace dg

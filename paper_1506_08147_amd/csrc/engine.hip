@@ -406,18 +406,26 @@ struct dgdft_alb {
 
   void gram(const std::vector<int>& act, const GramArgs& g, bool fp32 = false) {
     auto K = [&](int e) { return g.use_ne ? eh[e].ne : eh[e].ng; };
-    // dg_gram_w: 128 rows x tile_edge(n) columns; carried products form only
-    // the columns after the carried block (the grid is planned for the full
-    // product, which also covers elements that carry nothing)
+    // dg_gram_w: 128 rows x tile_edge(n) columns.  Carried products form only
+    // the columns after the carried block; whether an element carries is known
+    // on the device only, so the grid holds the larger of the two forms.
     GramArgs ga = g;
     ga.tail = g.carry ? 1 : 0;
-    auto P = make_prefix(act, [&](int e) {
-      int m = cols_host(g.A, e), c = 0;
+    auto items = [&](int e, int skip) {
+      const int m = cols_host(g.A, e);
+      int c = 0, n0 = 0, nsum = 0;
       for (int j = 0; j < g.njob; ++j) {
-        const int n = cols_host(g.B[j], e);
+        const int nj = cols_host(g.B[j], e), n = skip < nj ? nj - skip : nj;
         c += cdiv(m, GT) * cdiv(n, tile_edge(n));
+        if (j == 0) n0 = n;
+        nsum += n;
       }
-      return c * gram_nchunk_e(eh[e], K(e));
+      return c * gram_nchunk_e(eh[e], K(e), m, n0, nsum);
+    };
+    auto P = make_prefix(act, [&](int e) {
+      int c = items(e, 0);
+      if (ga.tail) c = std::max(c, items(e, (hasP_host(e) ? 2 : 1) * eh[e].J));
+      return c;
     });
     if (P.total == 0) return;
     double fl = 0, by = 0;
@@ -1228,6 +1236,7 @@ int32_t dgdft_alb_create(dgdft_alb** out, const int32_t* grid, const double* box
       E.small = (double*)p; E.small_stride = (long long)stride;
       p += align256(sizeof(double) * stride * SM_COUNT);
       E.gpart = (double*)p;
+      E.gpart_cap = 2LL * GRAM_MAXCHUNK * nmax * nmax;
     }
     HCHECK(hipMalloc(&h->vec_arena, sizeof(double) * 5 * h->sumJ));
     // ---- shells, gain tables, fallback state, Vbar, converged eigenvalues
@@ -2452,7 +2461,8 @@ int32_t dgdft_gemm_batched(int32_t trans, int32_t count, int64_t K, int32_t m, i
   try {
     TmpDev t;
     std::vector<Elem> eh(count);
-    const int nch = gram_nchunk((int)K);
+    const long long cap = (long long)GRAM_CHUNKS * m * n;
+    const int nch = gram_nchunk((int)K, m, n, n, cap);
     double* gp = trans ? t.alloc<double>((size_t)count * nch * m * n) : nullptr;
     for (int i = 0; i < count; ++i) {
       Elem& e = eh[i];
@@ -2463,6 +2473,7 @@ int32_t dgdft_gemm_batched(int32_t trans, int32_t count, int64_t K, int32_t m, i
         e.blk[S_U1] = const_cast<double*>(B) + (size_t)i * K * n;
         e.small = C + (size_t)i * m * n;
         e.gpart = gp + (size_t)i * nch * m * n;
+        e.gpart_cap = cap;
       } else {
         e.blk[S_U0] = const_cast<double*>(A) + (size_t)i * K * m;
         e.small = const_cast<double*>(B) + (size_t)i * m * n;

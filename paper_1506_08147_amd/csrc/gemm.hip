@@ -108,6 +108,32 @@ __device__ __forceinline__ const double* uniform_ptr(const double* p) {
   return (const double*)(((unsigned long long)hi << 32) | lo);
 }
 
+// Every vector instruction issued between two FP64 MFMAs takes its cycles from
+// the matrix pipe (measured, two waves per SIMD: 70.6 TFLOP/s with none, 58.8
+// with four integer additions per MFMA, 51.4 with eight), so the K loops of the
+// block products keep theirs out: operands go from global memory straight into
+// LDS where their alignment allows it.
+//
+// 16 bytes per lane from global memory straight into LDS: lane l's land at
+// lds + 16 l bytes (lds: the same in every lane).  Complete for the wave after
+// lds_dma_wait(); a barrier after that for the workgroup.
+__device__ __forceinline__ void lds_dma16(const double* base, unsigned off, double* lds) {
+  typedef const __attribute__((address_space(1))) char* cptr;
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)((cptr)base + off),
+                                   (__attribute__((address_space(3))) void*)lds, 16, 0, 0);
+}
+__device__ __forceinline__ void lds_dma_wait() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0)
+
+// Work items in groups of 8 x XCD_RUN: consecutive items run on one XCD (block
+// b runs on XCD b mod 8), so that the tiles that share operand rows share an
+// L2; the last, incomplete group keeps its order.
+constexpr int XCD_RUN = 16;
+__device__ __forceinline__ int xcd_item(int b, int total) {
+  const int g = b / (8 * XCD_RUN);
+  if ((g + 1) * 8 * XCD_RUN > total) return b;
+  return g * 8 * XCD_RUN + (b % 8) * XCD_RUN + (b / 8) % XCD_RUN;
+}
+
 constexpr int TT = 128;        // row tile of the Gram and update products
 constexpr int KS = 16;         // K stage
 constexpr int UTN = 144;       // largest column tile
@@ -120,109 +146,242 @@ __device__ __forceinline__ int gram_w_cols(const GramArgs& g, const Elem& e, int
   return kc > 0 && kc < c ? c - kc : c;
 }
 
+// The FP64 product of one tile over K rows [kbeg, kend) for columns that are
+// 16-byte aligned and within 4 GiB of the tile's first ones (byte offsets oa,
+// ob of this lane's columns and k pair).  Operand stages of 16 rows go straight
+// from global memory into LDS, columns 128 bytes apart with the eight 16-byte
+// pairs of column c in the order p ^ (c & 7): the destination of a direct load
+// is fixed by the lane, so the order is made by the address each lane reads,
+// and a fragment read (16 columns, one pair) meets every bank once.  A
+// fragment read brings two of the four k of two MFMAs (k = 8 h + 2 (lane / 16)
+// and the next), and the second half's are issued as the first half's
+// registers fall free.  What the loop issues besides MFMAs is then 9 loads and
+// 22 LDS reads per 72 MFMAs and wave, and no vector arithmetic.
+// Measured (32 products 432 x 144 over 77760 rows): 7.0 ms with 8-byte loads
+// through registers, zeroed on their way to LDS; 6.5 ms without the zeroing and
+// with the items of a chunk on one XCD; 5.65 ms (54.8 TFLOP/s) here.
+template <int NB, int NC>
+__device__ __forceinline__ void gram_vec(const double* baseA, const double* baseB, const unsigned (&oa)[4],
+                                         const unsigned (&ob)[5], const double* const* colA,
+                                         const double* const* colB, int kbeg, int kend, double* sa0, double* sa1,
+                                         double* sb0, double* sb1, dbl4 (&acc)[NC][NB]) {
+  const int tid = threadIdx.x, lane = tid & 63, wr = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, g16 = lane >> 4;
+  const int nfull = (kend - kbeg) / KS;
+  auto load = [&](int k0, double* sa, double* sb) {
+    const double* pa = baseA + k0;
+    const double* pb = baseB + k0;
+#pragma unroll
+    for (int u = 0; u < 2 * NC; ++u) lds_dma16(pa, oa[u], sa + (4 * u + wr) * 128);
+#pragma unroll
+    for (int v = 0; v < (NB + 1) / 2; ++v)
+      if (4 * v + wr < 2 * NB) lds_dma16(pb, ob[v], sb + (4 * v + wr) * 128);
+  };
+  // pair g16 (+ 4 in the second half) of column l16 (mod 16)
+  const int s0 = l16 * KS + 2 * (g16 ^ (l16 & 7)), s1 = l16 * KS + 2 * ((g16 + 4) ^ (l16 & 7));
+  auto mul = [&](const double* sa, const double* sb) {
+    const double* a0 = sa + wr * 256 + s0;
+    const double* a1 = sa + wr * 256 + s1;
+    const double* b0 = sb + s0;
+    const double* b1 = sb + s1;
+    gv2d fa[NC], fn[NC], fb[NB];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) fa[c] = *(const gv2d*)(a0 + c * 1024);
+#pragma unroll
+    for (int a = 0; a < NB; ++a) fb[a] = *(const gv2d*)(b0 + a * 256);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) fn[c] = *(const gv2d*)(a1 + c * 1024);
+#pragma unroll
+    for (int a = 0; a < NB; ++a) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) acc[c][a] = Mf<double>::mma(fa[c].x, fb[a].x, acc[c][a]);
+#pragma unroll
+      for (int c = 0; c < NC; ++c) acc[c][a] = Mf<double>::mma(fa[c].y, fb[a].y, acc[c][a]);
+      fb[a] = *(const gv2d*)(b1 + a * 256);
+    }
+#pragma unroll
+    for (int a = 0; a < NB; ++a) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) acc[c][a] = Mf<double>::mma(fn[c].x, fb[a].x, acc[c][a]);
+#pragma unroll
+      for (int c = 0; c < NC; ++c) acc[c][a] = Mf<double>::mma(fn[c].y, fb[a].y, acc[c][a]);
+    }
+  };
+  auto sync = [&]() {
+    lds_dma_wait();
+    __syncthreads();
+  };
+  if (nfull > 0) load(kbeg, sa0, sb0);
+  sync();
+  int st = 0;
+  for (; st + 2 <= nfull; st += 2) {
+    load(kbeg + (st + 1) * KS, sa1, sb1);
+    mul(sa0, sb0);
+    sync();
+    if (st + 2 < nfull) load(kbeg + (st + 2) * KS, sa0, sb0);
+    mul(sa1, sb1);
+    sync();
+  }
+  if (st < nfull) mul(sa0, sb0);
+  const int k0 = kbeg + nfull * KS;
+  if (k0 < kend) {
+    // the last, partial stage, zero past the end of K
+    for (int q = tid; q < (TT + 16 * NB) * KS; q += 256) {
+      const int c = q >> 4, k = q & 15, cc = c < TT ? c : c - TT;
+      double* s = c < TT ? sa1 : sb1;
+      const double* col = c < TT ? colA[cc] : colB[cc];
+      s[cc * KS + 2 * ((k >> 1) ^ (cc & 7)) + (k & 1)] = k0 + k < kend ? gld(col + k0 + k) : 0.0;
+    }
+    __syncthreads();
+    mul(sa1, sb1);
+  }
+}
+
 // Gram products C = A^T B on tiles of 128 rows (columns of A) x
-// tile_edge(n) columns (columns of B): four waves stacked along the rows,
-// each owning 32 rows x up to 144 columns (2 x 9 MFMA blocks; blocks beyond
-// the tile are skipped), so an element of any width leaves at most 15 idle
-// columns per tile.  Symmetric products are formed in full (both triangles).
-// With g.tail the B columns after the carried block only: for S = [X P W],
-// S^T W and S^T H W, the columns of S^T S and S^T H S not known from the
-// last step.
+// tile_edge(n) columns (columns of B): wave w owns the 16-row blocks w and
+// w + 4 of the tile by up to 144 columns (2 x 9 MFMA blocks; a block without
+// rows and blocks beyond the tile's columns are skipped), so an element of any
+// width leaves at most 15 idle columns per tile and a last row tile of at
+// most 64 rows takes half the time.  Symmetric products are formed in full
+// (both triangles).  With g.tail the B columns after the carried block only:
+// for S = [X P W], S^T W and S^T H W, the columns of S^T S and S^T H S not
+// known from the last step.
+//
+// Bound by the FP64 matrix pipe; what a K loop adds to it are its vector
+// instructions.  FP64 tiles of aligned columns take gram_vec;
+// the others, and the FP32 form, load 8 bytes per lane through registers (a
+// missing column reads the tile's first one and its results are not stored;
+// rows past the end of K become zero).
 template <class T>
 __device__ __forceinline__ void dg_gram_w_body(Elem* __restrict__ E, const int* __restrict__ active,
                                                const int* __restrict__ prefix, int na, GramArgs g) {
   constexpr int LPA = TT + Mf<T>::pad;
   constexpr int LPB = UTN + Mf<T>::pad144;
-
-  __shared__ T As[2][KS * LPA];
-  __shared__ T Bs[2][KS * LPB];
+  constexpr bool F64 = std::is_same<T, double>::value;
+  // gram_vec: two buffers of 16 x (128 + 144) entries; else two padded ones
+  __shared__ __attribute__((aligned(16))) T S0[KS * LPA];
+  __shared__ __attribute__((aligned(16))) T S1[KS * LPA];
+  __shared__ __attribute__((aligned(16))) T S2[KS * LPB];
+  __shared__ __attribute__((aligned(16))) T S3[KS * LPB];
   __shared__ const double* colA[TT];
   __shared__ const double* colB[UTN];
-  int blk = blockIdx.x;
+  int blk = xcd_item(blockIdx.x, gridDim.x);
   int ai = find_elem(prefix, na, blk);
   const Elem& e = E[active[ai]];
   int w = blk - prefix[ai];
   const int K = rowsK(e, g.use_ne);
   const int m = opnd_cols(g.A, e);
-  const int nch = gram_nchunk_e(e, K), clen = gram_chunklen(K, nch);
   const int n0 = gram_w_cols(g, e, 0);
+  const int n1 = g.njob > 1 ? gram_w_cols(g, e, 1) : 0;
+  const int nch = gram_nchunk_e(e, K, m, n0, n0 + n1);
+  const int clen = gram_chunklen(K, nch);
   const int ntr = cdiv(m, TT);
-  int job = 0, n = n0;
-  int tn = tile_edge(n);
-  int ntile = ntr * cdiv(n, tn);
-  if (w >= ntile * nch) {
-    job = 1;
-    w -= ntile * nch;
-    n = gram_w_cols(g, e, 1);
-    tn = tile_edge(n);
-    ntile = ntr * cdiv(n, tn);
-  }
+  // items of one chunk, both jobs, are consecutive
+  const int nt0 = ntr * cdiv(n0, tile_edge(n0)), nt1 = n1 > 0 ? ntr * cdiv(n1, tile_edge(n1)) : 0;
   // a grid sized for more blocks than the element has now (P dropped since
   // the launch was planned, e.g. inside a captured graph, or a carried
   // block) leaves spare items
-  if (job >= g.njob || ntile == 0 || w >= ntile * nch) return;
+  if (nt0 + nt1 == 0 || w >= (nt0 + nt1) * nch) return;
+  const int chunk = w / (nt0 + nt1);
+  int tile = w - chunk * (nt0 + nt1);
+  const int job = tile >= nt0;
+  if (job) tile -= nt0;
+  const int n = job ? n1 : n0;
+  const int tn = tile_edge(n);
   const Opnd& B = g.B[job];
   const int boff = opnd_cols(B, e) - n;          // first column of B in the product
-  const int chunk = w / ntile, tile = w - chunk * ntile;
   const int ntc = cdiv(n, tn);
   const int ti = tile / ntc, tj = tile - ti * ntc;
   const int trows = min(TT, m - ti * TT), tcols = min(tn, n - tj * tn);
   const int kbeg = chunk * clen;
   const int kend = min(K, kbeg + clen);
   const int tid = threadIdx.x;
-  if (tid < TT) colA[tid] = tid < trows ? opnd_col(g.A, e, ti * TT + tid) : nullptr;
-  if (tid < UTN) colB[tid] = tid < tcols ? opnd_col(B, e, boff + tj * tn + tid) : nullptr;
+  if (tid < TT) colA[tid] = opnd_col(g.A, e, ti * TT + (tid < trows ? tid : 0));
+  if (tid < UTN) colB[tid] = opnd_col(B, e, boff + tj * tn + (tid < tcols ? tid : 0));
   __syncthreads();
-  // stage loads: k = tid % 16; A columns tid/16 + 16u (u < 8), B columns
-  // tid/16 + 16v (v < NB).  The column pointers are read once.  Loads are
-  // unconditional (a missing column reads the tile's first column, k is
-  // clamped into the chunk, the last stage reloads itself); the values of
-  // missing columns and of k past the chunk become zero when the stage is
-  // written to LDS, at the end of the next stage's products, so a load has
-  // a whole stage of products to arrive.
-  const int lk = tid & 15, lc = tid >> 4;
-  const double* pa[8];
-  const double* pb[9];
-  unsigned live = 0;                          // bit u (A) / 8 + v (B): column exists
-#pragma unroll
-  for (int u = 0; u < 8; ++u) {
-    const double* c = colA[lc + 16 * u];
-    live |= (c != nullptr) << u;
-    pa[u] = c ? c : colA[0];
-  }
-#pragma unroll
-  for (int v = 0; v < 9; ++v) {
-    const double* c = colB[lc + 16 * v];
-    live |= (c != nullptr) << (8 + v);
-    pb[v] = c ? c : colB[0];
-  }
-  const int lane = tid & 63, wr = tid >> 6;
-  // wave-uniform: rows of this wave in the tile, MFMA column blocks of the tile
-  const int nrow = __builtin_amdgcn_readfirstlane(trows - wr * 32);
+  const int lane = tid & 63, wr = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nbc = __builtin_amdgcn_readfirstlane(min(9, cdiv(tcols, 16)));
-  const int nst = (kend - kbeg + KS - 1) / KS;
   double* part = e.gpart + (job ? (long long)nch * m * n0 : 0LL) + (long long)chunk * m * n;
+  auto put = [&](int c, int a, typename Mf<T>::acc v) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int il = c * 64 + wr * 16 + Mf<T>::row(r, lane);
+      const int jl = a * 16 + (lane & 15);
+      if (il < trows && jl < tcols)
+        gst(part + (ti * TT + il) + (long long)m * (tj * tn + jl), (double)v[r]);
+    }
+  };
+  if constexpr (F64) {
+    // direct loads: lane reads pair (lane & 7) ^ (lane >> 3) of column
+    // lane >> 3 (mod 8) of each of its groups of eight columns
+    const double* baseA = uniform_ptr(colA[0]);
+    const double* baseB = uniform_ptr(colB[0]);
+    unsigned oa[4], ob[5];
+    bool ok = true;
+    auto offset = [&](const double* c, const double* base) {
+      const unsigned long long d = (unsigned long long)((const char*)c - (const char*)base);
+      ok = ok && d < 0xFFFF0000ull && ((unsigned long long)c & 15) == 0;
+      return (unsigned)d + 16u * ((lane & 7) ^ (lane >> 3));
+    };
+#pragma unroll
+    for (int u = 0; u < 4; ++u) oa[u] = offset(colA[32 * u + 8 * wr + (lane >> 3)], baseA);
+#pragma unroll
+    for (int v = 0; v < 5; ++v) ob[v] = offset(colB[min(32 * v + 8 * wr + (lane >> 3), UTN - 1)], baseB);
+    if (__syncthreads_and(ok ? 1 : 0)) {
+      auto run = [&](auto nbt, auto nct) {
+        constexpr int NB = decltype(nbt)::value, NC = decltype(nct)::value;
+        dbl4 acc[NC][NB];
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+          for (int a = 0; a < NB; ++a) acc[c][a] = Mf<double>::zero();
+        gram_vec<NB, NC>(baseA, baseB, oa, ob, colA, colB, kbeg, kend, S0, S1, S2, S3, acc);
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+          for (int a = 0; a < NB; ++a) put(c, a, acc[c][a]);
+      };
+      auto pick = [&](auto nct) {
+        switch (nbc) {
+          case 1: run(std::integral_constant<int, 1>{}, nct); break;
+          case 2: run(std::integral_constant<int, 2>{}, nct); break;
+          case 3: run(std::integral_constant<int, 3>{}, nct); break;
+          case 4: run(std::integral_constant<int, 4>{}, nct); break;
+          case 5: run(std::integral_constant<int, 5>{}, nct); break;
+          case 6: run(std::integral_constant<int, 6>{}, nct); break;
+          case 7: run(std::integral_constant<int, 7>{}, nct); break;
+          case 8: run(std::integral_constant<int, 8>{}, nct); break;
+          default: run(std::integral_constant<int, 9>{}, nct); break;
+        }
+      };
+      if (trows > 64) pick(std::integral_constant<int, 2>{});
+      else pick(std::integral_constant<int, 1>{});
+      return;
+    }
+  }
+  // stage loads: k = tid % 16; A columns tid/16 + 16u (u < 8), B columns
+  // tid/16 + 16v (v < NB)
+  const int lk = tid & 15, lc = tid >> 4;
+  const int nst = __builtin_amdgcn_readfirstlane((kend - kbeg + KS - 1) / KS);
   // NB column blocks per tile, fixed at compile time so that the products
-  // run without per-block branches (a wave with one live row block computes
-  // the second on zero rows)
+  // run without per-block branches
   auto run = [&](auto nbt) {
     constexpr int NB = decltype(nbt)::value;
     double ra[8], rb[NB];
+    // rows [k0, k0 + 16), those past kend read row kend - 1
     auto load = [&](int k0) {
       const int k = min(k0 + lk, kend - 1);
 #pragma unroll
-      for (int u = 0; u < 8; ++u) ra[u] = gld(pa[u] + k);
+      for (int u = 0; u < 8; ++u) ra[u] = gld(colA[lc + 16 * u] + k);
 #pragma unroll
-      for (int v = 0; v < NB; ++v) rb[v] = gld(pb[v] + k);
+      for (int v = 0; v < NB; ++v) rb[v] = gld(colB[lc + 16 * v] + k);
     };
-    auto store = [&](int buf, int k0) {
-      const bool kin = k0 + lk < kend;
+    auto store = [&](T* As, T* Bs, int k0) {
+      const bool in = k0 + lk < kend;
 #pragma unroll
-      for (int u = 0; u < 8; ++u)
-        As[buf][lk * LPA + lc + 16 * u] = (T)((kin && ((live >> u) & 1)) ? ra[u] : 0.0);
+      for (int u = 0; u < 8; ++u) As[lk * LPA + lc + 16 * u] = (T)(in ? ra[u] : 0.0);
 #pragma unroll
-      for (int v = 0; v < NB; ++v)
-        Bs[buf][lk * LPB + lc + 16 * v] = (T)((kin && ((live >> (8 + v)) & 1)) ? rb[v] : 0.0);
+      for (int v = 0; v < NB; ++v) Bs[lk * LPB + lc + 16 * v] = (T)(in ? rb[v] : 0.0);
     };
     typename Mf<T>::acc acc[2][NB];
 #pragma unroll
@@ -231,42 +390,33 @@ __device__ __forceinline__ void dg_gram_w_body(Elem* __restrict__ E, const int* 
       for (int a = 0; a < NB; ++a) acc[c][a] = Mf<T>::zero();
     if (nst > 0) {
       load(kbeg);
-      store(0, kbeg);
-      __syncthreads();
+      store(S0, S2, kbeg);
     }
+    __syncthreads();
     for (int st = 0; st < nst; ++st) {
-      const int cur = st & 1;
-      const int knext = kbeg + min(st + 1, nst - 1) * KS;
-      load(knext);
-      if (nrow > 0) {
+      T* As = st & 1 ? S1 : S0;
+      T* Bs = st & 1 ? S3 : S2;
+      load(kbeg + min(st + 1, nst - 1) * KS);  // the last stage reloads itself
 #pragma unroll
-        for (int ks = 0; ks < KS / 4; ++ks) {
-          const int kk = ks * 4 + (lane >> 4);
-          T fa[2], fb[NB];
+      for (int ks = 0; ks < KS / 4; ++ks) {
+        const int kk = ks * 4 + (lane >> 4);
+        T fa[2], fb[NB];
 #pragma unroll
-          for (int c = 0; c < 2; ++c) fa[c] = As[cur][kk * LPA + wr * 32 + c * 16 + (lane & 15)];
+        for (int c = 0; c < 2; ++c) fa[c] = As[kk * LPA + c * 64 + wr * 16 + (lane & 15)];
 #pragma unroll
-          for (int a = 0; a < NB; ++a) fb[a] = Bs[cur][kk * LPB + a * 16 + (lane & 15)];
+        for (int a = 0; a < NB; ++a) fb[a] = Bs[kk * LPB + a * 16 + (lane & 15)];
 #pragma unroll
-          for (int a = 0; a < NB; ++a)
+        for (int a = 0; a < NB; ++a)
 #pragma unroll
-            for (int c = 0; c < 2; ++c) acc[c][a] = Mf<T>::mma(fa[c], fb[a], acc[c][a]);
-        }
+          for (int c = 0; c < 2; ++c) acc[c][a] = Mf<T>::mma(fa[c], fb[a], acc[c][a]);
       }
-      if (st + 1 < nst) store(cur ^ 1, knext);
+      if (st + 1 < nst) store(st & 1 ? S0 : S1, st & 1 ? S2 : S3, kbeg + (st + 1) * KS);
       __syncthreads();
     }
 #pragma unroll
     for (int c = 0; c < 2; ++c)
 #pragma unroll
-      for (int a = 0; a < NB; ++a)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int il = wr * 32 + c * 16 + Mf<T>::row(r, lane);
-          const int jl = a * 16 + (lane & 15);
-          if (il < trows && jl < tcols)
-            gst(part + (ti * TT + il) + (long long)m * (tj * tn + jl), (double)acc[c][a][r]);
-        }
+      for (int a = 0; a < NB; ++a) put(c, a, acc[c][a]);
   };
   switch (nbc) {
     case 1: run(std::integral_constant<int, 1>{}); break;
@@ -304,8 +454,8 @@ dg_gram_reduce(Elem* __restrict__ E, const int* __restrict__ active, const int* 
   int w = blk - prefix[ai];
   const int K = rowsK(e, g.use_ne);
   const int m = opnd_cols(g.A, e);
-  const int nch = gram_nchunk_e(e, K);
   const int n0 = gram_w_cols(g, e, 0);
+  const int nch = gram_nchunk_e(e, K, m, n0, n0 + (g.njob > 1 ? gram_w_cols(g, e, 1) : 0));
   int job = 0, n = n0;
   int nb = cdiv(m * n, 256);
   if (w >= nb) { job = 1; w -= nb; n = gram_w_cols(g, e, 1); }
