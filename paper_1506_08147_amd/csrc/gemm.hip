@@ -114,6 +114,13 @@ __device__ __forceinline__ const double* uniform_ptr(const double* p) {
 // block products keep theirs out: operands go from global memory straight into
 // LDS where their alignment allows it.
 //
+// base + a 32-bit byte offset (the scalar-base form of a global load: its
+// address costs no vector instruction).
+__device__ __forceinline__ double gld_off(const double* base, unsigned off) {
+  typedef const __attribute__((address_space(1))) char* cptr;
+  return *(const __attribute__((address_space(1))) double*)((cptr)base + off);
+}
+
 // 16 bytes per lane from global memory straight into LDS: lane l's land at
 // lds + 16 l bytes (lds: the same in every lane).  Complete for the wave after
 // lds_dma_wait(); a barrier after that for the workgroup.
@@ -483,19 +490,133 @@ dg_gram_reduce(Elem* __restrict__ E, const int* __restrict__ active, const int* 
 constexpr int UKS = 16;        // K stage of the update
 constexpr int UPD_NQ = UKS / 2;
 
+// The FP64 products of one tile for an even leading dimension and 16-byte
+// aligned columns: the stage's 16 columns of A (128 rows each, 1 KiB, one
+// direct load of a wave) go from global memory straight into LDS; C, whose
+// leading dimension may be odd, goes through registers into columns of eight
+// 16-byte pairs in the order p ^ (j & 7).  A fragment read brings two of the
+// four k of two MFMAs (k = 8 h + 2 (lane / 16) and the next) for C and two rows
+// (2 (lane % 16) and the next) for A, so a result row pair is one 16-byte store.
+// Column k of A is column k % bcols of block k / bcols.  Rows past the end of
+// the block read its last pair (their results are not stored), columns past
+// kend are zero.
+// Measured (kernel, 16 products of 77760 x 432 by 432 x 144): 3.16 ms with 8-byte
+// loads through registers, zeroed on their way to LDS; 2.77 ms (55.9 TFLOP/s)
+// here; three of 55296 x 519 by 519 x 173: 890 and 700 us.
+template <int NB, class Blk>
+__device__ __forceinline__ void update_vec(Blk ablk, int bcols, long long ld, unsigned rowoff, const double* C,
+                                           int cld, unsigned co, unsigned col, int kbeg, int kend, double* sa0, double* sa1,
+                                           double* sc0, double* sc1, dbl4 (&acc)[NB][2]) {
+  const int tid = threadIdx.x, lane = tid & 63, wr = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, g16 = lane >> 4;
+  const int ck = tid & 15, cj = tid >> 4;
+  kbeg = __builtin_amdgcn_readfirstlane(kbeg);
+  kend = __builtin_amdgcn_readfirstlane(kend);
+  const int nst = (kend - kbeg + UKS - 1) / UKS;
+  const int cdst = cj * UKS + 2 * ((ck >> 1) ^ (cj & 7)) + (ck & 1);
+  double rc[NB];
+  // this wave's next column of A and its place (scalar registers throughout)
+  int k = kbeg + wr, bb = __builtin_amdgcn_readfirstlane(k / bcols), kc = k - bb * bcols;
+  auto load = [&](int st, double* sa) {
+    const int k0 = kbeg + st * UKS;
+    // A: column k0 + wr + 4 q
+#pragma unroll
+    for (int q = 0; q < UKS / 4; ++q) {
+      double* dst = sa + (wr + 4 * q) * TT;
+      if (k < kend) {
+        lds_dma16(ablk(bb) + (long long)kc * ld, rowoff, dst);
+      } else {
+        const gv2d z = {0.0, 0.0};
+        *(gv2d*)(dst + 2 * lane) = z;
+      }
+      k += 4;
+      kc += 4;
+      while (kc >= bcols) {
+        kc -= bcols;
+        ++bb;
+      }
+    }
+    // C: columns cj + 16 v (only those of the last v are clamped)
+    const double* Ck = C + k0;
+    const int back = k0 + UKS <= kend ? 0 : max(0, k0 + ck - (kend - 1));
+#pragma unroll
+    for (int v = 0; v < NB; ++v)
+      rc[v] = v + 1 < NB ? gld_off(Ck + (long long)(16 * v) * cld, co - 8u * back) : gld_off(Ck, col - 8u * back);
+    if (k0 + UKS > kend) {
+#pragma unroll
+      for (int v = 0; v < NB; ++v) rc[v] = back ? 0.0 : rc[v];
+    }
+  };
+  auto store = [&](double* sc) {
+#pragma unroll
+    for (int v = 0; v < NB; ++v) sc[cdst + v * 16 * UKS] = rc[v];
+  };
+  const int s0 = l16 * UKS + 2 * (g16 ^ (l16 & 7)), s1 = l16 * UKS + 2 * ((g16 + 4) ^ (l16 & 7));
+  auto mul = [&](const double* sa, const double* sc) {
+    const double* ap = sa + 2 * g16 * TT + wr * 32 + 2 * l16;
+    const double* c0 = sc + s0;
+    const double* c1 = sc + s1;
+    gv2d fa[2], fn[2], fc[NB];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) fa[j] = *(const gv2d*)(ap + j * TT);
+#pragma unroll
+    for (int a = 0; a < NB; ++a) fc[a] = *(const gv2d*)(c0 + a * 256);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) fn[j] = *(const gv2d*)(ap + (8 + j) * TT);
+#pragma unroll
+    for (int a = 0; a < NB; ++a) {
+      acc[a][0] = Mf<double>::mma(fc[a].x, fa[0].x, acc[a][0]);
+      acc[a][1] = Mf<double>::mma(fc[a].x, fa[0].y, acc[a][1]);
+      acc[a][0] = Mf<double>::mma(fc[a].y, fa[1].x, acc[a][0]);
+      acc[a][1] = Mf<double>::mma(fc[a].y, fa[1].y, acc[a][1]);
+      fc[a] = *(const gv2d*)(c1 + a * 256);
+    }
+#pragma unroll
+    for (int a = 0; a < NB; ++a) {
+      acc[a][0] = Mf<double>::mma(fc[a].x, fn[0].x, acc[a][0]);
+      acc[a][1] = Mf<double>::mma(fc[a].x, fn[0].y, acc[a][1]);
+      acc[a][0] = Mf<double>::mma(fc[a].y, fn[1].x, acc[a][0]);
+      acc[a][1] = Mf<double>::mma(fc[a].y, fn[1].y, acc[a][1]);
+    }
+  };
+  auto sync = [&]() {
+    lds_dma_wait();
+    __syncthreads();
+  };
+  if (nst > 0) {
+    load(0, sa0);
+    store(sc0);
+  }
+  sync();
+  for (int st = 0; st < nst; st += 2) {
+    if (st + 1 < nst) load(st + 1, sa1);
+    mul(sa0, sc0);
+    if (st + 1 >= nst) break;
+    store(sc1);
+    sync();
+    if (st + 2 < nst) load(st + 2, sa0);
+    mul(sa1, sc1);
+    if (st + 2 < nst) store(sc0);
+    sync();
+  }
+}
+
 template <class T>
 __device__ __forceinline__ void dg_update_w_body(Elem* __restrict__ E, const int* __restrict__ active, const int* __restrict__ prefix,
                int na, UpdArgs u) {
   constexpr int LPT = TT + Mf<T>::pad;
   constexpr int LPCT = UTN + Mf<T>::pad144;
+  constexpr bool F64 = std::is_same<T, double>::value;
 
-  __shared__ T As[2][UKS * LPT];
-  __shared__ T Cs[2][UKS * LPCT];
+  __shared__ __attribute__((aligned(16))) T S0[UKS * LPT];
+  __shared__ __attribute__((aligned(16))) T S1[UKS * LPT];
+  __shared__ __attribute__((aligned(16))) T S2[UKS * LPCT];
+  __shared__ __attribute__((aligned(16))) T S3[UKS * LPCT];
   __shared__ double* colY[UTN];
   __shared__ double* colY2[UTN];
   __shared__ const double* colZ[UTN];
   __shared__ const double* abase[6];
-  int blk = blockIdx.x;
+  int blk = xcd_item(blockIdx.x, gridDim.x);
   int ai = find_elem(prefix, na, blk);
   const Elem& e = E[active[ai]];
   int w = blk - prefix[ai];
@@ -566,6 +687,79 @@ __device__ __forceinline__ void dg_update_w_body(Elem* __restrict__ E, const int
   // (scalars copied out of the argument block: the products below are a
   // lambda, and a reference to the by-value argument would put it on the stack)
   const double alpha = u.alpha, beta = u.beta;
+  if constexpr (F64) {
+    // 16-byte alignment of every column that is read or written in pairs
+    bool ok = (ld & 1) == 0 && ld < (1LL << 28);
+    if (tid < UTN)
+      ok = ok && (((unsigned long long)colY[tid] | (unsigned long long)colY2[tid] | (unsigned long long)colZ[tid]) & 15) == 0;
+    const int nab = __builtin_amdgcn_readfirstlane(A.ncols >= 0 ? 1 : cdiv(kA, e.J));
+    for (int q = 0; q < nab; ++q) ok = ok && ((unsigned long long)ablk(q) & 15) == 0;
+    if (__syncthreads_and(ok ? 1 : 0)) {
+      const unsigned rowoff = 8u * (unsigned)min((long long)row0 + 2 * lane, ld - 2);
+      const int l16 = lane & 15, g16 = lane >> 4;
+      auto vec = [&](auto nbt) {
+        constexpr int NB = decltype(nbt)::value;
+        dbl4 acc[NB][2];
+#pragma unroll
+        for (int a = 0; a < NB; ++a)
+#pragma unroll
+          for (int c = 0; c < 2; ++c) acc[a][c] = Mf<double>::zero();
+        const int row = row0 + wr * 32 + 2 * l16;
+        // rows row, row + 1 of column j: alpha acc + beta Z
+        auto put = [&](double* y, const double* z, double b, double v0, double v1) {
+          v0 *= alpha;
+          v1 *= alpha;
+          if (row + 1 < K) {
+            if (b != 0.0) {
+              const double2 o = gld((const double2*)(z + row));
+              v0 += b * o.x;
+              v1 += b * o.y;
+            }
+            gst((double2*)(y + row), make_double2(v0, v1));
+          } else if (row < K) {
+            if (b != 0.0) v0 += b * gld(z + row);
+            gst(y + row, v0);
+          }
+        };
+        const int ck = tid & 15, cj = tid >> 4;
+        const int cldu = __builtin_amdgcn_readfirstlane(cld);
+        const unsigned co = 8u * (unsigned)(ck + cld * min(cj, tcols - 1));
+        const unsigned col = 8u * (unsigned)(ck + cld * min(cj + 16 * (NB - 1), tcols - 1));
+        // with split: columns J .. kA - 1 of A, Y2 = alpha [P W] C[J:], then 0 .. J - 1
+        const int kall = __builtin_amdgcn_readfirstlane(kA);
+        const int k1 = __builtin_amdgcn_readfirstlane(u.split ? J : kA);
+        for (int seg = u.split ? 0 : 1; seg < 2; ++seg) {
+          update_vec<NB>(ablk, bcols, ld, rowoff, uniform_ptr(C + (long long)cld * col0), cldu, co, col, seg ? 0 : k1, seg ? k1 : kall, S0, S1,
+                         S2, S3, acc);
+          double* const* yc = seg ? colY : colY2;
+          const double b = seg ? beta : 0.0;
+#pragma unroll
+          for (int a = 0; a < NB; ++a)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const int jl = a * 16 + 4 * r + g16;
+              double* y = yc[jl];
+              if (!y) continue;
+              const double* zc = colZ[jl];
+              put(y, zc ? zc : y, b, acc[a][0][r], acc[a][1][r]);
+            }
+          __syncthreads();                     // the last stage is read before the next segment's first
+        }
+      };
+      switch (nbc) {
+        case 1: vec(std::integral_constant<int, 1>{}); break;
+        case 2: vec(std::integral_constant<int, 2>{}); break;
+        case 3: vec(std::integral_constant<int, 3>{}); break;
+        case 4: vec(std::integral_constant<int, 4>{}); break;
+        case 5: vec(std::integral_constant<int, 5>{}); break;
+        case 6: vec(std::integral_constant<int, 6>{}); break;
+        case 7: vec(std::integral_constant<int, 7>{}); break;
+        case 8: vec(std::integral_constant<int, 8>{}); break;
+        default: vec(std::integral_constant<int, 9>{}); break;
+      }
+      return;
+    }
+  }
   auto run = [&](auto nbt) {
     constexpr int NB = decltype(nbt)::value;
     double ra[UPD_NQ], rc[NB];
@@ -594,13 +788,15 @@ __device__ __forceinline__ void dg_update_w_body(Elem* __restrict__ E, const int
       }
     };
     auto store = [&](int buf, int k0, int ke) {
+      T* As = buf ? S1 : S0;
+      T* Cs = buf ? S3 : S2;
 #pragma unroll
       for (int q = 0; q < UPD_NQ; ++q)
-        As[buf][(ak + 2 * q) * LPT + ar] = (T)((rin && k0 + ak + 2 * q < ke) ? ra[q] : 0.0);
+        As[(ak + 2 * q) * LPT + ar] = (T)((rin && k0 + ak + 2 * q < ke) ? ra[q] : 0.0);
       const bool kin = k0 + ck < ke;
 #pragma unroll
       for (int v = 0; v < NB; ++v)
-        Cs[buf][ck * LPCT + cj + 16 * v] = (T)((kin && cj + 16 * v < tcols) ? rc[v] : 0.0);
+        Cs[ck * LPCT + cj + 16 * v] = (T)((kin && cj + 16 * v < tcols) ? rc[v] : 0.0);
     };
     typename Mf<T>::acc acc[NB][2];
 #pragma unroll
@@ -614,6 +810,8 @@ __device__ __forceinline__ void dg_update_w_body(Elem* __restrict__ E, const int
     }
     for (int st = 0; st < nst; ++st) {
       const int cur = st & 1;
+      const T* As = cur ? S1 : S0;
+      const T* Cs = cur ? S3 : S2;
       const int sn = min(st + 1, nst - 1);     // the last stage reloads itself
       load(kbeg(sn), kend(sn));
 #pragma unroll
@@ -621,9 +819,9 @@ __device__ __forceinline__ void dg_update_w_body(Elem* __restrict__ E, const int
         const int kk = ks * 4 + (lane >> 4);
         T fc[NB], fa[2];
 #pragma unroll
-        for (int a = 0; a < NB; ++a) fc[a] = Cs[cur][kk * LPCT + a * 16 + (lane & 15)];
+        for (int a = 0; a < NB; ++a) fc[a] = Cs[kk * LPCT + a * 16 + (lane & 15)];
 #pragma unroll
-        for (int c = 0; c < 2; ++c) fa[c] = As[cur][kk * LPT + wr * 32 + c * 16 + (lane & 15)];
+        for (int c = 0; c < 2; ++c) fa[c] = As[kk * LPT + wr * 32 + c * 16 + (lane & 15)];
 #pragma unroll
         for (int a = 0; a < NB; ++a)
 #pragma unroll
