@@ -51,9 +51,9 @@ struct Elem {
   const int* grp_np;         // projectors in group g (<= KB_GMAX)
   const int* grp_idx;        // flat grid index per support point
   const double* grp_val;     // per point, grp_np values (beta = sqrt(dV) b)
-  const int* kbt_ptr;        // ng+1: projector entries touching point r
-  const int* kbt_p;          // projector id
-  const double* kbt_c;       // gamma_p * beta_p(r)
+  const int* kbt_ptr;        // ng+1: support points of groups at grid point r
+  const int* kbt_pq;         // per entry: 16 (first projector) + projectors
+  const double* kbt_val;     // per entry: KB_GMAX values, as in grp_val
   double* small;             // per-element small dense workspace
   double* gpart;             // Gram split-K partial sums
   long long gpart_cap;       // doubles in gpart

@@ -347,7 +347,7 @@ struct dgdft_alb {
                 bool fp32 = false) {
     // ncols_fixed < 0: all J columns
     auto nc = [&](int e) { return ncols_fixed < 0 ? eh[e].J : ncols_fixed; };
-    launch_kbproj(act, in_slot, col0, ncols_fixed, 0);
+    launch_kbproj(act, in_slot, col0, ncols_fixed, 2);
     const XYSets xs = xy_sets(act, [&](int e) { return cdiv(nc(e), 2); });
     double pts = 0;   // grid points x column pairs
     for (int e : act) pts += (double)cdiv(nc(e), 2) * eh[e].ng;
@@ -363,13 +363,13 @@ struct dgdft_alb {
     HCHECK(hipGetLastError());
   }
 
-  void launch_kbproj(const std::vector<int>& act, int slot, int col0, int ncols_fixed, int to_projx) {
+  void launch_kbproj(const std::vector<int>& act, int slot, int col0, int ncols_fixed, int dst) {
     auto nc = [&](int e) { return ncols_fixed < 0 ? eh[e].J : ncols_fixed; };
-    auto P = make_prefix(act, [&](int e) { return eh[e].n_grp * nc(e); });
+    auto P = make_prefix(act, [&](int e) { return eh[e].n_grp * cdiv(nc(e), KB_COLS); });
     if (P.total == 0) return;
     pbeg(DGDFT_K_KB_PROJECT, 0, 0);
     hipLaunchKernelGGL(dg_kb_project, dim3(P.total), dim3(256), 0, stream, ed, P.active, P.prefix,
-                       P.na, slot, col0, ncols_fixed, to_projx);
+                       P.na, slot, col0, ncols_fixed, dst);
     pend();
     HCHECK(hipGetLastError());
   }
@@ -1469,10 +1469,12 @@ static Status set_potential_impl(dgdft_alb* h, const double* V, const dgdft_kb* 
     for (double v : val)
       if (!std::isfinite(v)) return fail(DGDFT_EINVAL, "KB val contains non-finite values");
   }
-  // layout per element: groups, points, values (KB_GMAX per point), transposed CSR
+  // layout per element: groups, points, values (KB_GMAX per point), and the
+  // points' lists of groups
   struct Lay {
-    std::vector<int> gptr, gp0, gnp, gidx, tptr, tp;
-    std::vector<double> gval, tc;
+    std::vector<int> gptr, gp0, gnp, gidx, tptr;
+    std::vector<int> tpq;
+    std::vector<double> gval, tval;
   };
   std::vector<Lay> lay(n);
   size_t kb_bytes = 0, proj_doubles = 0;
@@ -1506,26 +1508,26 @@ static Status set_potential_impl(dgdft_alb* h, const double* V, const dgdft_kb* 
       L.gptr.push_back((int)L.gidx.size());
       p = q;
     }
-    // transposed CSR: entries (projector, gamma_p * beta_p(r)) per grid point
+    // transposed: per grid point the projectors and values of its groups
     if (P > 0) {
       L.tptr.assign(E.ng + 1, 0);
-      for (int p = 0; p < P; ++p)
-        for (long long k = ptr[pbase + p]; k < ptr[pbase + p + 1]; ++k) L.tptr[idx[k] + 1]++;
+      for (int r : L.gidx) L.tptr[r + 1]++;
       for (int r = 0; r < E.ng; ++r) L.tptr[r + 1] += L.tptr[r];
-      L.tp.resize(L.tptr[E.ng]);
-      L.tc.resize(L.tptr[E.ng]);
+      L.tpq.resize(L.tptr[E.ng]);
+      L.tval.resize((size_t)L.tptr[E.ng] * KB_GMAX);
       std::vector<int> fillpos(L.tptr.begin(), L.tptr.end() - 1);
-      for (int p = 0; p < P; ++p)
-        for (long long k = ptr[pbase + p]; k < ptr[pbase + p + 1]; ++k) {
-          int at = fillpos[idx[k]]++;
-          L.tp[at] = p;
-          L.tc[at] = gam[pbase + p] * sq * val[k];
+      for (size_t g = 0; g < L.gp0.size(); ++g)
+        for (int k = L.gptr[g]; k < L.gptr[g + 1]; ++k) {
+          const int at = fillpos[L.gidx[k]]++;
+          L.tpq[at] = 16 * L.gp0[g] + L.gnp[g];
+          std::copy_n(L.gval.begin() + (size_t)k * KB_GMAX, KB_GMAX, L.tval.begin() + (size_t)at * KB_GMAX);
         }
     }
     kb_bytes += align256(sizeof(int) * L.gptr.size()) + 2 * align256(sizeof(int) * L.gp0.size()) +
                 align256(sizeof(int) * L.gidx.size()) + align256(sizeof(double) * L.gval.size()) +
-                align256(sizeof(int) * L.tptr.size()) + align256(sizeof(int) * L.tp.size()) +
-                align256(sizeof(double) * L.tc.size()) + align256(sizeof(double) * P);
+                align256(sizeof(int) * L.tptr.size()) + align256(sizeof(int) * L.tpq.size()) +
+                align256(sizeof(double) * L.tval.size()) +
+                align256(sizeof(double) * P);
     proj_doubles += 2 * (size_t)P * E.J;
     pbase += P;
   }
@@ -1565,10 +1567,10 @@ static Status set_potential_impl(dgdft_alb* h, const double* V, const dgdft_kb* 
     E.grp_val = (const double*)put(L.gval.data(), sizeof(double) * L.gval.size());
     if (P > 0) {
       E.kbt_ptr = (const int*)put(L.tptr.data(), sizeof(int) * L.tptr.size());
-      E.kbt_p = (const int*)put(L.tp.data(), sizeof(int) * L.tp.size());
-      E.kbt_c = (const double*)put(L.tc.data(), sizeof(double) * L.tc.size());
+      E.kbt_pq = (const int*)put(L.tpq.data(), sizeof(int) * L.tpq.size());
+      E.kbt_val = (const double*)put(L.tval.data(), sizeof(double) * L.tval.size());
     } else {
-      E.kbt_ptr = nullptr; E.kbt_p = nullptr; E.kbt_c = nullptr;
+      E.kbt_ptr = nullptr; E.kbt_pq = nullptr; E.kbt_val = nullptr;
     }
     E.gamma = (const double*)put(gam.data() + pbase, sizeof(double) * P);
     E.proj = pj; pj += (size_t)P * E.J;

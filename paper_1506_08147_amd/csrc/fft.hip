@@ -511,12 +511,15 @@ dg_fft_z32_m(Elem* __restrict__ E, const int* __restrict__ active, const int* __
   fft_z_body<FFT_XY_SMALL, FFT_TINY_THREADS>(buf, E, active, prefix, na, col0, ncols, mode);
 }
 
+// Projectors whose coefficients (for two columns) an xy inverse pass keeps in LDS.
+constexpr int KB_LDS = 256;
+
 // Pass 3: inverse xy transform and epilogue.  Work item (pair q, plane z).
 // mode 0 (operator): out = T x + V x + KB, reading x from block `in_slot`
-//   and the projections beta^T x from e.proj (n_proj x ncols).
+//   and the projections gamma beta^T x from e.proj (n_proj x ncols).
 // mode 1 (plain): out = result (preconditioner; out may equal in).
 template <int MAXPTS, int NT, class C>
-__device__ __forceinline__ void fft_xy_inv_body(C* buf, Elem* __restrict__ E,
+__device__ __forceinline__ void fft_xy_inv_body(C* buf, double* cproj, Elem* __restrict__ E,
                                                 const int* __restrict__ active,
                                                 const int* __restrict__ prefix, int na, int in_slot,
                                                 int out_slot, int col0, int ncols, int mode) {
@@ -526,9 +529,23 @@ __device__ __forceinline__ void fft_xy_inv_body(C* buf, Elem* __restrict__ E,
   int w = b - prefix[ai];
   int q = w / e.n3, z = w - q * e.n3;
   int n1 = e.n1, n2 = e.n2, np = n1 * n2;
+  const double sc = 1.0 / (double)e.ng;
+  const int nc = ncols < 0 ? e.J : ncols;
+  int ca = col0 + 2 * q, cb = ca + 1;
+  bool hasb = cb < col0 + nc;
+  long long off = (long long)z * np;
+  double* OA = bp(e, out_slot) + (long long)ca * e.ld + off;
+  double* OB = bp(e, out_slot) + (long long)cb * e.ld + off;
   const C* Z = zpair<C>(e, q) + (long long)z * np;
+  constexpr int NL = (MAXPTS + NT - 1) / NT;
+  // the columns' projections times gamma, for the operator's epilogue
+  if (mode == 0 && e.n_proj <= KB_LDS)
+    for (int t = threadIdx.x; t < e.n_proj; t += NT) {
+      const double* g = e.proj + (long long)(ca - col0) * e.n_proj + t;
+      cproj[t] = gld(g);
+      cproj[KB_LDS + t] = hasb ? gld(g + e.n_proj) : 0.0;
+    }
   {
-    constexpr int NL = (MAXPTS + NT - 1) / NT;
     C rz[NL];
 #pragma unroll
     for (int u = 0; u < NL; ++u) {
@@ -544,47 +561,88 @@ __device__ __forceinline__ void fft_xy_inv_body(C* buf, Elem* __restrict__ E,
   __syncthreads();
   fft_lines<MAXPTS, NT>(buf, n2, n1, 1, n1, e.rad[1], e.nrad[1], twiddles<C>(e, 1), 1.0);
   fft_lines<MAXPTS, NT>(buf, n1, n2, n1, 1, e.rad[0], e.nrad[0], twiddles<C>(e, 0), 1.0);
-  const double sc = 1.0 / (double)e.ng;
-  const int nc = ncols < 0 ? e.J : ncols;
-  int ca = col0 + 2 * q, cb = ca + 1;
-  bool hasb = cb < col0 + nc;
-  long long off = (long long)z * np;
-  double* OA = bp(e, out_slot) + (long long)ca * e.ld + off;
-  double* OB = bp(e, out_slot) + (long long)cb * e.ld + off;
   if (mode == 0) {
+    const double* ga = e.proj + (long long)(ca - col0) * e.n_proj;
+    const double* gb = hasb ? ga + e.n_proj : ga;
+    const double* cA = e.n_proj <= KB_LDS ? cproj : ga;
+    const double* cB = e.n_proj <= KB_LDS ? cproj + KB_LDS : gb;
     const double* IA = bp(e, in_slot) + (long long)ca * e.ld + off;
-    const double* IB = bp(e, in_slot) + (long long)cb * e.ld + off;
+    const double* IB = hasb ? IA + e.ld : IA;
     const double* V = e.V + off;
-    const int* kp = e.kbt_ptr;
-    const double* pa = e.proj + (long long)(ca - col0) * e.n_proj;
-    const double* pb = e.proj + (long long)(cb - col0) * e.n_proj;
-    const int* kbp = e.kbt_p;
-    const double* kbc = e.kbt_c;
-    for (int p = threadIdx.x; p < np; p += NT) {
-      const C r = buf[p];
-      double v = gld(V + p);
-      double ya = sc * r.x + v * gld(IA + p);
-      double yb = hasb ? sc * r.y + v * gld(IB + p) : 0.0;
-      if (kp) {
-        // entries of this point four at a time, so that their loads overlap
-        int g = (int)(off + p);
-        int t = gld(kp + g);
-        const int t1 = gld(kp + g + 1);
-        for (; t + 4 <= t1; t += 4) {
-          int p0 = gld(kbp + t), p1 = gld(kbp + t + 1), p2 = gld(kbp + t + 2), p3 = gld(kbp + t + 3);
-          double c0 = gld(kbc + t), c1 = gld(kbc + t + 1), c2 = gld(kbc + t + 2), c3 = gld(kbc + t + 3);
-          ya += c0 * gld(pa + p0) + c1 * gld(pa + p1) + c2 * gld(pa + p2) + c3 * gld(pa + p3);
-          if (hasb) yb += c0 * gld(pb + p0) + c1 * gld(pb + p1) + c2 * gld(pb + p2) + c3 * gld(pb + p3);
+    const int* kp = e.kbt_ptr ? e.kbt_ptr + off : nullptr;
+    // NP points of a lane at a time, the next ones' loads in flight meanwhile;
+    // of the groups at a point (sum_p gamma_p beta_p(r) (beta_p^T x)), the l-th
+    // of all NP points at a time.  One point and one group at a time, their
+    // chains of loads (range, entry, values) were most of this pass: with 120
+    // projectors on 48^3 (272 columns), 368 us of which the transform is 150; 340 us this way.
+    constexpr int NP = 3;
+    double nv[NP], na[NP], nb[NP];
+    int n0[NP], n1[NP];
+    auto fetch = [&](int u0) {
+#pragma unroll
+      for (int j = 0; j < NP; ++j) {
+        const int p = threadIdx.x + (u0 + j) * NT, pc = p < np ? p : 0;
+        nv[j] = gld(V + pc);
+        na[j] = gld(IA + pc);
+        nb[j] = gld(IB + pc);
+        n0[j] = kp ? gld(kp + pc) : 0;
+        n1[j] = kp ? gld(kp + pc + 1) : 0;
+      }
+    };
+    fetch(0);
+#pragma unroll 1
+    for (int u0 = 0; u0 < NL; u0 += NP) {
+      double ya[NP], yb[NP];
+      int k0[NP], k1[NP];
+#pragma unroll
+      for (int j = 0; j < NP; ++j) {
+        const int p = threadIdx.x + (u0 + j) * NT;
+        const C r = buf[p < np ? p : 0];
+        ya[j] = sc * r.x + nv[j] * na[j];
+        yb[j] = sc * r.y + nv[j] * nb[j];
+        k0[j] = n0[j];
+        k1[j] = p < np ? n1[j] : n0[j];
+      }
+      if (u0 + NP < NL) fetch(u0 + NP);
+      for (;;) {
+        bool more = false;
+#pragma unroll
+        for (int j = 0; j < NP; ++j) more = more || k0[j] < k1[j];
+        if (!more) break;
+        int pq[NP];
+        double2 v0[NP], v1[NP];
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+          const int t = k0[j] < k1[j] ? k0[j] : 0;
+          const double2* vs = (const double2*)(e.kbt_val + (long long)t * KB_GMAX);
+          pq[j] = gld(e.kbt_pq + t);
+          v0[j] = gld(vs);
+          v1[j] = gld(vs + 1);
         }
-        for (; t < t1; ++t) {
-          int pr = gld(kbp + t);
-          double c = gld(kbc + t);
-          ya += c * gld(pa + pr);
-          if (hasb) yb += c * gld(pb + pr);
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+          if (k0[j] >= k1[j]) continue;
+          const int q0 = pq[j] >> 4, nq = pq[j] & 15;
+          auto add = [&](int k, double v) {
+            ya[j] += v * cA[q0 + k];
+            yb[j] += v * cB[q0 + k];
+          };
+          add(0, v0[j].x);
+          if (nq > 1) add(1, v0[j].y);
+          if (nq > 2) add(2, v1[j].x);
+          if (nq > 3) add(3, v1[j].y);
+          for (int k = 4; k < nq; ++k) add(k, gld(e.kbt_val + (long long)k0[j] * KB_GMAX + k));
+          ++k0[j];
         }
       }
-      gst(OA + p, ya);
-      if (hasb) gst(OB + p, yb);
+#pragma unroll
+      for (int j = 0; j < NP; ++j) {
+        const int p = threadIdx.x + (u0 + j) * NT;
+        if (p < np) {
+          gst(OA + p, ya[j]);
+          if (hasb) gst(OB + p, yb[j]);
+        }
+      }
     }
   } else {
     for (int p = threadIdx.x; p < np; p += NT) {
@@ -599,21 +657,24 @@ extern "C" __global__ void __launch_bounds__(FFT_THREADS, 4)
 dg_fft_xy_inv_l(Elem* __restrict__ E, const int* __restrict__ active, const int* __restrict__ prefix,
                 int na, int in_slot, int out_slot, int col0, int ncols, int mode) {
   __shared__ double2 buf[FFT_MAXPTS];
-  fft_xy_inv_body<FFT_MAXPTS, FFT_THREADS>(buf, E, active, prefix, na, in_slot, out_slot, col0, ncols, mode);
+  __shared__ double cproj[2 * KB_LDS];
+  fft_xy_inv_body<FFT_MAXPTS, FFT_THREADS>(buf, cproj, E, active, prefix, na, in_slot, out_slot, col0, ncols, mode);
 }
 
 extern "C" __global__ void __launch_bounds__(FFT_THREADS, 4)
 dg_fft_xy_inv32_l(Elem* __restrict__ E, const int* __restrict__ active, const int* __restrict__ prefix,
                   int na, int in_slot, int out_slot, int col0, int ncols, int mode) {
   __shared__ float2 buf[FFT_MAXPTS];
-  fft_xy_inv_body<FFT_MAXPTS, FFT_THREADS>(buf, E, active, prefix, na, in_slot, out_slot, col0, ncols, mode);
+  __shared__ double cproj[2 * KB_LDS];
+  fft_xy_inv_body<FFT_MAXPTS, FFT_THREADS>(buf, cproj, E, active, prefix, na, in_slot, out_slot, col0, ncols, mode);
 }
 
 extern "C" __global__ void __launch_bounds__(FFT_TINY_THREADS)
 dg_fft_xy_inv_s(Elem* __restrict__ E, const int* __restrict__ active, const int* __restrict__ prefix,
                 int na, int in_slot, int out_slot, int col0, int ncols, int mode) {
   __shared__ double2 buf[FFT_XY_TINY];
-  fft_xy_inv_body<FFT_XY_TINY, FFT_TINY_THREADS>(buf, E, active, prefix, na, in_slot, out_slot, col0, ncols,
+  __shared__ double cproj[2 * KB_LDS];
+  fft_xy_inv_body<FFT_XY_TINY, FFT_TINY_THREADS>(buf, cproj, E, active, prefix, na, in_slot, out_slot, col0, ncols,
                                                  mode);
 }
 
@@ -621,7 +682,8 @@ extern "C" __global__ void __launch_bounds__(FFT_TINY_THREADS)
 dg_fft_xy_inv32_s(Elem* __restrict__ E, const int* __restrict__ active, const int* __restrict__ prefix,
                   int na, int in_slot, int out_slot, int col0, int ncols, int mode) {
   __shared__ float2 buf[FFT_XY_TINY];
-  fft_xy_inv_body<FFT_XY_TINY, FFT_TINY_THREADS>(buf, E, active, prefix, na, in_slot, out_slot, col0, ncols,
+  __shared__ double cproj[2 * KB_LDS];
+  fft_xy_inv_body<FFT_XY_TINY, FFT_TINY_THREADS>(buf, cproj, E, active, prefix, na, in_slot, out_slot, col0, ncols,
                                                  mode);
 }
 
@@ -629,7 +691,8 @@ extern "C" __global__ void __launch_bounds__(FFT_TINY_THREADS)
 dg_fft_xy_inv_m(Elem* __restrict__ E, const int* __restrict__ active, const int* __restrict__ prefix,
                 int na, int in_slot, int out_slot, int col0, int ncols, int mode) {
   __shared__ double2 buf[FFT_XY_SMALL];
-  fft_xy_inv_body<FFT_XY_SMALL, FFT_TINY_THREADS>(buf, E, active, prefix, na, in_slot, out_slot, col0, ncols,
+  __shared__ double cproj[2 * KB_LDS];
+  fft_xy_inv_body<FFT_XY_SMALL, FFT_TINY_THREADS>(buf, cproj, E, active, prefix, na, in_slot, out_slot, col0, ncols,
                                                   mode);
 }
 
@@ -637,48 +700,84 @@ extern "C" __global__ void __launch_bounds__(FFT_TINY_THREADS)
 dg_fft_xy_inv32_m(Elem* __restrict__ E, const int* __restrict__ active, const int* __restrict__ prefix,
                   int na, int in_slot, int out_slot, int col0, int ncols, int mode) {
   __shared__ float2 buf[FFT_XY_SMALL];
-  fft_xy_inv_body<FFT_XY_SMALL, FFT_TINY_THREADS>(buf, E, active, prefix, na, in_slot, out_slot, col0, ncols,
+  __shared__ double cproj[2 * KB_LDS];
+  fft_xy_inv_body<FFT_XY_SMALL, FFT_TINY_THREADS>(buf, cproj, E, active, prefix, na, in_slot, out_slot, col0, ncols,
                                                   mode);
 }
 
 // ---------------------------------------------------------------------------
-// KB projections: out[p + n_proj*(c - col0)] = beta_p^T x_c for projector
-// groups sharing one support.  Work item (group g, column c).
+// KB projections of projector groups sharing one support, for KB_COLS columns
+// at a time: a point's index and values are read once for all of them (one
+// column per workgroup read 76 bytes of projector for 8 of column).  Work item
+// (group g, column block).  Into e.proj (dst 0), e.projx (1), or e.proj times
+// gamma (2, what the operator's epilogue sums).
+// Measured: 272 columns, 48^3, 120 projectors 103 -> 62 us; 136 columns of
+// 144x12x12 36 -> 26.
+constexpr int KB_COLS = 4;
+
+template <int NP>
+__device__ __forceinline__ void kb_project_body(const Elem& e, const double* x, int nc, int s0, int s1,
+                                                double (*red)[4]) {
+  double acc[KB_COLS][NP];
+#pragma unroll
+  for (int c = 0; c < KB_COLS; ++c)
+#pragma unroll
+    for (int k = 0; k < NP; ++k) acc[c][k] = 0.0;
+  const double* xc[KB_COLS];
+#pragma unroll
+  for (int c = 0; c < KB_COLS; ++c) xc[c] = x + (long long)(c < nc ? c : 0) * e.ld;
+  for (int s = s0 + threadIdx.x; s < s1; s += 256) {
+    const int i = gld(e.grp_idx + s);
+    const double2* vv = (const double2*)(e.grp_val + (long long)s * KB_GMAX);
+    double v[NP], xv[KB_COLS];
+#pragma unroll
+    for (int k = 0; k < NP / 2; ++k) {
+      const double2 w = gld(vv + k);
+      v[2 * k] = w.x;
+      v[2 * k + 1] = w.y;
+    }
+#pragma unroll
+    for (int c = 0; c < KB_COLS; ++c) xv[c] = gld(xc[c] + i);
+#pragma unroll
+    for (int c = 0; c < KB_COLS; ++c)
+#pragma unroll
+      for (int k = 0; k < NP; ++k) acc[c][k] += v[k] * xv[c];
+  }
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+#pragma unroll
+  for (int c = 0; c < KB_COLS; ++c)
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+      double v = acc[c][k];
+      for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+      if (lane == 0) red[c * KB_GMAX + k][wv] = v;
+    }
+}
+
 extern "C" __global__ void __launch_bounds__(256)
 dg_kb_project(Elem* __restrict__ E, const int* __restrict__ active, const int* __restrict__ prefix,
-              int na, int slot, int col0, int ncols, int to_projx) {
-  __shared__ double red[KB_GMAX][4];
+              int na, int slot, int col0, int ncols, int dst) {
+  __shared__ double red[KB_COLS * KB_GMAX][4];
   int b = blockIdx.x;
   int ai = find_elem(prefix, na, b);
   const Elem& e = E[active[ai]];
   int w = b - prefix[ai];
-  const int nc = ncols < 0 ? e.J : ncols;
-  int g = w / nc, c = col0 + (w - g * nc);
-  int p0 = e.grp_p0[g], npg = e.grp_np[g];
-  int s0 = e.grp_ptr[g], s1 = e.grp_ptr[g + 1];
-  const double* x = bp(e, slot) + (long long)c * e.ld;
-  double acc[KB_GMAX];
-#pragma unroll
-  for (int k = 0; k < KB_GMAX; ++k) acc[k] = 0.0;
-  for (int s = s0 + threadIdx.x; s < s1; s += 256) {
-    double xv = gld(x + gld(e.grp_idx + s));
-    const double* vv = e.grp_val + (long long)s * KB_GMAX;
-#pragma unroll
-    for (int k = 0; k < KB_GMAX; ++k) acc[k] += gld(vv + k) * xv;
-  }
-  int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-#pragma unroll
-  for (int k = 0; k < KB_GMAX; ++k) {
-    double v = acc[k];
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    if (lane == 0) red[k][wv] = v;
-  }
+  const int nc = ncols < 0 ? e.J : ncols, nb = cdiv(nc, KB_COLS);
+  const int g = w / nb, c0 = (w - g * nb) * KB_COLS, cn = min(KB_COLS, nc - c0);
+  const int p0 = e.grp_p0[g], npg = e.grp_np[g];
+  const int s0 = e.grp_ptr[g], s1 = e.grp_ptr[g + 1];
+  const double* x = bp(e, slot) + (long long)(col0 + c0) * e.ld;
+  if (npg <= 4) kb_project_body<4>(e, x, cn, s0, s1, red);
+  else kb_project_body<KB_GMAX>(e, x, cn, s0, s1, red);
   __syncthreads();
-  if (threadIdx.x < npg) {
-    int k = threadIdx.x;
-    double s = red[k][0] + red[k][1] + red[k][2] + red[k][3];
-    double* out = to_projx ? e.projx : e.proj;
-    out[(p0 + k) + (long long)e.n_proj * (c - col0)] = s;
+  if (threadIdx.x < KB_COLS * KB_GMAX) {
+    const int c = threadIdx.x / KB_GMAX, k = threadIdx.x % KB_GMAX;
+    if (c < cn && k < npg) {
+      const double* r = red[threadIdx.x];
+      double s = r[0] + r[1] + r[2] + r[3];
+      if (dst == 2) s *= e.gamma[p0 + k];
+      (dst == 1 ? e.projx : e.proj)[(p0 + k) + (long long)e.n_proj * (c0 + c)] = s;
+    }
   }
 }
 
