@@ -193,6 +193,7 @@ __device__ inline int find_elem(const int* __restrict__ prefix, int na, int b) {
 // ---- work decomposition shared by host (counts) and device (decode) ----
 constexpr int GT = 128;           // row tile of the Gram and update products
 constexpr int GRAM_MAXCHUNK = 8;  // largest tuned split
+constexpr int RESID_THREADS = 1024;   // lanes of dg_resid
 constexpr int GRAM_CHUNKS = 48;   // largest split of the default rule
 
 __host__ __device__ inline int cdiv(int a, int b) { return (a + b - 1) / b; }

@@ -498,11 +498,11 @@ struct dgdft_alb {
     if (which <= 1) pbeg(DGDFT_K_RESID, 0, (which == 0 ? 32.0 : 24.0) * pts);
     switch (which) {
       case 0:
-        hipLaunchKernelGGL(dg_resid, dim3(P.total), dim3(256), 0, stream, ed, P.active, P.prefix, P.na,
+        hipLaunchKernelGGL(dg_resid, dim3(P.total), dim3(RESID_THREADS), 0, stream, ed, P.active, P.prefix, P.na,
                            a0, a1, a2, 1);
         break;
       case 1:
-        hipLaunchKernelGGL(dg_resid, dim3(P.total), dim3(256), 0, stream, ed, P.active, P.prefix, P.na,
+        hipLaunchKernelGGL(dg_resid, dim3(P.total), dim3(RESID_THREADS), 0, stream, ed, P.active, P.prefix, P.na,
                            a0, a1, a2, 0);
         break;
       case 2:
@@ -2180,7 +2180,7 @@ int32_t dgdft_alb_precondition(dgdft_alb* h, int32_t elem, const double* R, cons
     h->op_apply(one, S_U0, S_U2, 0, ncols);
     {
       auto P = h->make_prefix(one, [&](int) { return ncols; });
-      hipLaunchKernelGGL(dg_resid, dim3(P.total), dim3(256), 0, h->stream, h->ed, P.active, P.prefix,
+      hipLaunchKernelGGL(dg_resid, dim3(P.total), dim3(RESID_THREADS), 0, h->stream, h->ed, P.active, P.prefix,
                          P.na, (int)S_U0, (int)S_U2, (int)S_U2, 0);
     }
     h->launch_kbproj(one, S_U0, 0, ncols, 1);
