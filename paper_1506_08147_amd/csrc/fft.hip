@@ -711,8 +711,8 @@ dg_fft_xy_inv32_m(Elem* __restrict__ E, const int* __restrict__ active, const in
 // column per workgroup read 76 bytes of projector for 8 of column).  Work item
 // (group g, column block).  Into e.proj (dst 0), e.projx (1), or e.proj times
 // gamma (2, what the operator's epilogue sums).
-// Measured: 272 columns, 48^3, 120 projectors 103 -> 62 us; 136 columns of
-// 144x12x12 36 -> 26.
+// Measured: 272 columns, 48^3, 120 projectors 103 -> 62 us; 144 columns of
+// 36x36x60 36 -> 26.
 constexpr int KB_COLS = 4;
 
 template <int NP>

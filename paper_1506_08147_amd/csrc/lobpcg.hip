@@ -30,7 +30,7 @@ __device__ __forceinline__ double wave_sum(double v) {
 // One pass over the columns, so memory should bound it; but a call can have
 // fewer columns than the card has CUs, and then the loads in flight of one
 // workgroup do.  Hence RESID_THREADS lanes with RESID_NP points each at a time,
-// all loads ahead of the arithmetic.  Measured: 136 columns of 144x12x12 (one
+// all loads ahead of the arithmetic.  Measured: 144 columns of 36x36x60 (one
 // workgroup on about half of the CUs), 256 lanes with one point at a time
 // 196 us, this 51 us.
 constexpr int RESID_NP = 4;
@@ -1046,6 +1046,13 @@ dg_kb_differs(const double* __restrict__ g, const double* __restrict__ gc, long 
   for (long long k = i; k < nnz; k += stride)
     d |= (ix[k] != ixc[k]) | (__double_as_longlong(v[k]) != __double_as_longlong(vc[k]));
   if (d) atomicOr(flag, 1);
+}
+
+// The user slots of one element (one lane).
+extern "C" __global__ void dg_bind_user(Elem* e, double* a, double* b, double* c) {
+  e->blk[S_U0] = a;
+  e->blk[S_U1] = b;
+  e->blk[S_U2] = c;
 }
 
 // Any non-finite value in a[0..n) sets *flag.
