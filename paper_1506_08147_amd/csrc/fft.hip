@@ -711,8 +711,8 @@ dg_fft_xy_inv32_m(Elem* __restrict__ E, const int* __restrict__ active, const in
 // column per workgroup read 76 bytes of projector for 8 of column).  Work item
 // (group g, column block).  Into e.proj (dst 0), e.projx (1), or e.proj times
 // gamma (2, what the operator's epilogue sums).
-// Measured: 272 columns, 48^3, 120 projectors 103 -> 62 us; 144 columns of
-// 36x36x60 36 -> 26.
+// Measured: 272 columns, 48^3, 120 projectors 103 -> 58 us; 144 columns of
+// 36x36x60 36 -> 24; 7 columns of 20x30x18 11.7 -> 9.2.
 constexpr int KB_COLS = 4;
 
 template <int NP>
@@ -743,15 +743,26 @@ __device__ __forceinline__ void kb_project_body(const Elem& e, const double* x, 
 #pragma unroll
       for (int k = 0; k < NP; ++k) acc[c][k] += v[k] * xv[c];
   }
+  // wave sums of all accumulators together: each exchange halves what a lane
+  // still holds (N - 1 exchanges and a few, against 6 N one at a time; the
+  // additions and their order are the same)
+  constexpr int N = KB_COLS * NP;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  double* v = &acc[0][0];
+  int q = 0, o = 32;
 #pragma unroll
-  for (int c = 0; c < KB_COLS; ++c)
+  for (int h = N / 2; h > 0; h >>= 1, o >>= 1) {
+    const bool up = lane & o;
+    q = 2 * q + up;
 #pragma unroll
-    for (int k = 0; k < NP; ++k) {
-      double v = acc[c][k];
-      for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-      if (lane == 0) red[c * KB_GMAX + k][wv] = v;
+    for (int k = 0; k < h; ++k) {
+      const double give = up ? v[k] : v[k + h];
+      v[k] = (up ? v[k + h] : v[k]) + __shfl_xor(give, o, 64);
     }
+  }
+#pragma unroll
+  for (int r = 32 / N; r > 0; r >>= 1, o >>= 1) v[0] += __shfl_xor(v[0], o, 64);
+  if ((lane & (64 / N - 1)) == 0) red[(q / NP) * KB_GMAX + q % NP][wv] = v[0];
 }
 
 extern "C" __global__ void __launch_bounds__(256)
