@@ -1050,18 +1050,26 @@ __device__ __forceinline__ double bg_colscale(const BgArgs& a, int bi, int j) {
 // BM x BN output tile per workgroup (64 or 32 each, so that thin operands
 // do not pay for a 64-wide tile); four waves in a 2 x 2 grid, each with
 // (BM/32) x (BN/32) MFMA blocks of 16 x 16; 16-deep K stages double-buffered
-// through LDS.
+// through LDS.  The products of the DG step are thin (K of 12 to 120, or
+// n_alb^2 outputs of a long sum), so memory bounds them and what counts is that
+// all loads of a stage are in flight together: they are unconditional at
+// clamped indices, and zeros and the weights ks go in on the way to LDS.  The
+// MFMA takes op(B)^T as its first operand, so that a store covers 16 rows of a
+// column of C.  Measured (8 elements of the slab, 64 ALBs, 69120 points; loads
+// under their bounds checks, each waiting for its weight, and 4 rows a store ->
+// this): Phi^T diag(w) Phi 316 -> 156 us with its reduction, psi to the LGL
+// points along x, y, z 299, 245, 379 -> 289, 283, 319 us, Phi 300 -> 269 us.  The
+// register limits are what four or five workgroups on a CU need (164 registers
+// and two of them: 170, 364 and 298 us).
 template <int BM, int BN>
 __device__ __forceinline__ void bgemm_tile(const BgArgs& a) {
   constexpr int MB = BM / 32, NB = BN / 32;
   __shared__ double As[2][16 * (BM + 1)];
   __shared__ double Bs[2][16 * (BN + 1)];
-  const int ntm = cdiv(a.M, BM), ntn = cdiv(a.N, BN);
-  const long long blk = blockIdx.x;
-  const int t = (int)(blk % (ntm * ntn));
-  const long long rest = blk / (ntm * ntn);
-  const int bi = (int)(rest % a.batch), kc = (int)(rest / a.batch);
-  const int i0 = (t % ntm) * BM, j0 = (t / ntm) * BN;
+  const unsigned ntm = cdiv(a.M, BM), tiles = ntm * cdiv(a.N, BN), blk = blockIdx.x;
+  const unsigned rest = blk / tiles, t = blk - rest * tiles;
+  const int kc = (int)(rest / (unsigned)a.batch), bi = (int)(rest - (unsigned)kc * a.batch);
+  const int tj = (int)(t / ntm), i0 = (int)(t - tj * ntm) * BM, j0 = tj * BN;
   const double* A = a.A + a.sa * bi;
   const double* B = a.B + a.sb * bi;
   const double* ksv = a.ks ? a.ks + a.sks * bi : nullptr;
@@ -1073,52 +1081,59 @@ __device__ __forceinline__ void bgemm_tile(const BgArgs& a) {
   for (int x = 0; x < MB; ++x)
 #pragma unroll
     for (int y = 0; y < NB; ++y) acc[x][y] = (dbl4){0.0, 0.0, 0.0, 0.0};
-  // stage k0 -> registers; op(A) tile (ii, kk) contiguous along ii when
-  // ta == 0, along kk when ta == 1; op(B) tile (kb, jj) along kb when tb == 0,
-  // along jj when tb == 1
-  double ra[BM / 16], rb[BN / 16];
+  // op(A) tile (ii, kk) contiguous along ii when ta == 0, along kk when
+  // ta == 1; op(B) tile (kb, jj) along kb when tb == 0, along jj when tb == 1
+  const long long lka = a.ta ? 1 : a.lda, lkb = a.tb ? a.ldb : 1;   // strides along k
+  int ai[BM / 16], ak[BM / 16], bj[BN / 16], bk[BN / 16];
+  const double *pa[BM / 16], *pb[BN / 16];
+#pragma unroll
+  for (int q = 0; q < BM / 16; ++q) {
+    const int el = tid + 256 * q;
+    ai[q] = a.ta ? el >> 4 : el % BM;
+    ak[q] = a.ta ? el & 15 : el / BM;
+    pa[q] = A + (long long)min(i0 + ai[q], a.M - 1) * (a.ta ? a.lda : 1) + lka * (kbeg + ak[q]);
+  }
+#pragma unroll
+  for (int q = 0; q < BN / 16; ++q) {
+    const int el = tid + 256 * q;
+    bj[q] = a.tb ? el % BN : el >> 4;
+    bk[q] = a.tb ? el / BN : el & 15;
+    pb[q] = B + (long long)min(j0 + bj[q], a.N - 1) * (a.tb ? 1 : a.ldb) + lkb * (kbeg + bk[q]);
+  }
+  // stage k0 -> registers; past kend the last row of the chunk is read again
+  double ra[BM / 16], rb[BN / 16], rk[BM / 16];
   auto load = [&](int k0) {
+    const bool tail = k0 + 16 > kend;
 #pragma unroll
     for (int q = 0; q < BM / 16; ++q) {
-      int el = tid + 256 * q;
-      int ii = a.ta ? el >> 4 : el % BM, kk = a.ta ? el & 15 : el / BM;
-      double av = 0.0;
-      if (i0 + ii < a.M && k0 + kk < kend) {
-        av = a.ta ? A[(k0 + kk) + (long long)a.lda * (i0 + ii)] : A[(i0 + ii) + (long long)a.lda * (k0 + kk)];
-        if (ksv) av *= ksv[k0 + kk];
-      }
-      ra[q] = av;
+      const int over = tail ? max(0, k0 + ak[q] - (kend - 1)) : 0;
+      ra[q] = gld(pa[q] - (tail ? lka * over : 0));
+      rk[q] = ksv ? gld(ksv + k0 + ak[q] - over) : 1.0;
+      pa[q] += 16 * lka;
     }
 #pragma unroll
     for (int q = 0; q < BN / 16; ++q) {
-      int el = tid + 256 * q;
-      int jj = a.tb ? el % BN : el >> 4, kb = a.tb ? el / BN : el & 15;
-      double bv = 0.0;
-      if (j0 + jj < a.N && k0 + kb < kend)
-        bv = a.tb ? B[(j0 + jj) + (long long)a.ldb * (k0 + kb)] : B[(k0 + kb) + (long long)a.ldb * (j0 + jj)];
-      rb[q] = bv;
+      const int over = tail ? max(0, k0 + bk[q] - (kend - 1)) : 0;
+      rb[q] = gld(pb[q] - (tail ? lkb * over : 0));
+      pb[q] += 16 * lkb;
     }
   };
-  auto store = [&](int buf) {
+  auto store = [&](int buf, int k0) {
 #pragma unroll
     for (int q = 0; q < BM / 16; ++q) {
-      int el = tid + 256 * q;
-      int ii = a.ta ? el >> 4 : el % BM, kk = a.ta ? el & 15 : el / BM;
-      As[buf][kk * (BM + 1) + ii] = ra[q];
+      const double v = ksv ? ra[q] * rk[q] : ra[q];
+      As[buf][ak[q] * (BM + 1) + ai[q]] = (i0 + ai[q] < a.M && k0 + ak[q] < kend) ? v : 0.0;
     }
 #pragma unroll
-    for (int q = 0; q < BN / 16; ++q) {
-      int el = tid + 256 * q;
-      int jj = a.tb ? el % BN : el >> 4, kb = a.tb ? el / BN : el & 15;
-      Bs[buf][kb * (BN + 1) + jj] = rb[q];
-    }
+    for (int q = 0; q < BN / 16; ++q)
+      Bs[buf][bk[q] * (BN + 1) + bj[q]] = (j0 + bj[q] < a.N && k0 + bk[q] < kend) ? rb[q] : 0.0;
   };
   // double-buffered: stage s + 1 is read from global memory into registers
   // while stage s is multiplied out of LDS; one barrier per stage
   const int nst = kend > kbeg ? (kend - kbeg + 15) / 16 : 0;
   if (nst > 0) {
     load(kbeg);
-    store(0);
+    store(0, kbeg);
   }
   __syncthreads();
   for (int st = 0; st < nst; ++st) {
@@ -1136,9 +1151,9 @@ __device__ __forceinline__ void bgemm_tile(const BgArgs& a) {
       for (int x = 0; x < MB; ++x)
 #pragma unroll
         for (int y = 0; y < NB; ++y)
-          acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[x], fb[y], acc[x][y], 0, 0, 0);
+          acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(fb[y], fa[x], acc[x][y], 0, 0, 0);
     }
-    if (st + 1 < nst) store(cur ^ 1);
+    if (st + 1 < nst) store(cur ^ 1, kbeg + 16 * (st + 1));
     __syncthreads();
   }
   double* C = a.C + a.sc * bi;
@@ -1149,23 +1164,23 @@ __device__ __forceinline__ void bgemm_tile(const BgArgs& a) {
     for (int y = 0; y < NB; ++y)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        int i = i0 + wi * (BM / 2) + x * 16 + 4 * r + (lane >> 4);
-        int j = j0 + wj * (BN / 2) + y * 16 + (lane & 15);
+        int i = i0 + wi * (BM / 2) + x * 16 + (lane & 15);
+        int j = j0 + wj * (BN / 2) + y * 16 + 4 * r + (lane >> 4);
         if (i < a.M && j < a.N) {
           if (a.ksplit > 1) {
-            P[i + (long long)a.M * j] = acc[x][y][r];
+            gst(P + i + (long long)a.M * j, acc[x][y][r]);
           } else {
             double* c = C + i + (long long)a.ldc * j;
             double v = a.alpha * bg_colscale(a, bi, j) * acc[x][y][r];
-            *c = a.beta != 0.0 ? v + a.beta * *c : v;
+            gst(c, a.beta != 0.0 ? v + a.beta * gld(c) : v);
           }
         }
       }
 }
 
-extern "C" __global__ void __launch_bounds__(256) dg_bgemm(BgArgs a) { bgemm_tile<64, 64>(a); }
-extern "C" __global__ void __launch_bounds__(256) dg_bgemm_m32(BgArgs a) { bgemm_tile<32, 64>(a); }
-extern "C" __global__ void __launch_bounds__(256) dg_bgemm_n32(BgArgs a) { bgemm_tile<64, 32>(a); }
+extern "C" __global__ void __launch_bounds__(256, 4) dg_bgemm(BgArgs a) { bgemm_tile<64, 64>(a); }
+extern "C" __global__ void __launch_bounds__(256, 5) dg_bgemm_m32(BgArgs a) { bgemm_tile<32, 64>(a); }
+extern "C" __global__ void __launch_bounds__(256, 5) dg_bgemm_n32(BgArgs a) { bgemm_tile<64, 32>(a); }
 extern "C" __global__ void __launch_bounds__(256) dg_bgemm_s32(BgArgs a) { bgemm_tile<32, 32>(a); }
 
 // C_b = alpha * cs-scaled sum over chunks of the partials + beta C_b; one
@@ -1178,8 +1193,18 @@ dg_bgemm_reduce(BgArgs a) {
   const int bi = (int)(p / mn);
   const long long ij = p - (long long)bi * mn;
   const int i = (int)(ij % a.M), j = (int)(ij / a.M);
+  const double* part = a.part + (long long)bi * mn + ij;
+  const long long step = (long long)a.batch * mn;
   double s = 0.0;
-  for (int kc = 0; kc < a.ksplit; ++kc) s += a.part[((long long)kc * a.batch + bi) * mn + ij];
+  int kc = 0;
+  for (; kc + 8 <= a.ksplit; kc += 8) {   // eight loads in flight, one order of sums
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = gld(part + (kc + u) * step);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s += v[u];
+  }
+  for (; kc < a.ksplit; ++kc) s += gld(part + kc * step);
   double* c = a.C + a.sc * bi + i + (long long)a.ldc * j;
   double v = a.alpha * bg_colscale(a, bi, j) * s;
   *c = a.beta != 0.0 ? v + a.beta * *c : v;
