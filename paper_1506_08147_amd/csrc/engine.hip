@@ -379,8 +379,9 @@ struct dgdft_alb {
     HCHECK(hipGetLastError());
   }
 
+  // ncols_fixed < 0: all J columns (-1) or the first n_alb (-2)
   void launch_kbproj(const std::vector<int>& act, int slot, int col0, int ncols_fixed, int dst) {
-    auto nc = [&](int e) { return ncols_fixed < 0 ? eh[e].J : ncols_fixed; };
+    auto nc = [&](int e) { return ncols_fixed == -2 ? eh[e].nalb : ncols_fixed < 0 ? eh[e].J : ncols_fixed; };
     auto P = make_prefix(act, [&](int e) { return eh[e].n_grp * cdiv(nc(e), KB_COLS); });
     if (P.total == 0) return;
     pbeg(DGDFT_K_KB_PROJECT, 0, 0);
@@ -2850,7 +2851,7 @@ int32_t dgdft_alb_density(dgdft_alb* h, const double* albs, const double* P, dou
   try {
     h->ring_reset();
     std::vector<int> all = all_elems(h->n);
-    auto Pf = h->make_prefix(all, [&](int e) { return cdiv(h->eh[e].ne, 256); });
+    auto Pf = h->make_prefix(all, [&](int e) { return cdiv(h->eh[e].ne, DEN_ROWS); });
     hipLaunchKernelGGL(dg_density, dim3(Pf.total), dim3(256), 0, h->stream, h->ed, Pf.active, Pf.prefix,
                        Pf.na, albs, P, rho);
     HCHECK(hipGetLastError());
@@ -2887,7 +2888,7 @@ int32_t dgdft_alb_dg_volume(dgdft_alb* h, const double* eigvecs, const double* a
     }
     const size_t J = E.J, na = E.nalb, m1 = z.m[0], m2 = z.m[1];
     z.ME = m1 * m2 * z.m[2];
-    z.a = std::max({(size_t)E.ne * J, m1 * E.n2 * E.n3 * J, z.ME * J});
+    z.a = std::max({(size_t)E.ng, (size_t)E.ne * J, m1 * E.n2 * E.n3 * J, z.ME * J});
     z.b = std::max(m1 * m2 * E.n3 * J, z.ME * na);
   }
   auto same = [&](int a, int b) {
@@ -2911,8 +2912,8 @@ int32_t dgdft_alb_dg_volume(dgdft_alb* h, const double* eigvecs, const double* a
     auto take = [&](size_t n) { double* q = base ? base + off : nullptr; off += al(n); return q; };
     P.bufA = take(G * z.a);
     P.bufB = take(G * z.b);
-    P.vX = take((size_t)z.m[0] * E.n2 * E.n3);
-    P.vY = take((size_t)z.m[0] * z.m[1] * E.n3);
+    P.vX = take(G * (size_t)z.m[0] * E.n2 * E.n3);
+    P.vY = take(G * (size_t)z.m[0] * z.m[1] * E.n3);
     P.vL = take(G * z.ME);
     P.wq = take(z.ME);
     P.vw = take(G * z.ME);
@@ -2985,7 +2986,7 @@ int32_t dgdft_alb_dg_volume(dgdft_alb* h, const double* eigvecs, const double* a
       const double* phi = albs + E.off_alb;
       double* oe = out + E.off_nl;
       const long long ne = E.ne;
-      hipLaunchKernelGGL(dg_lgl_tables, dim3(3), dim3(256), 0, h->stream, (const Elem*)h->ed, e0, t);
+      hipLaunchKernelGGL(dg_lgl_tables, dim3(3, LGL_NY), dim3(256), 0, h->stream, (const Elem*)h->ed, e0, t);
       HCHECK(hipGetLastError());
       // T = dV psi_E^T phi sigma^-2  (J x n_alb per element)
       hipLaunchKernelGGL(dg_box_cols, dim3(cdiv(E.ne, 256), J, G), dim3(256), 0, h->stream,
@@ -3003,15 +3004,16 @@ int32_t dgdft_alb_dg_volume(dgdft_alb* h, const double* eigvecs, const double* a
       // Phi = Psi_LGL T  (ME x n_alb per element) into bufB
       gemm(0, 0, ME, na, J, bufA, ME, (long long)ME * J, Tu, J, (long long)J * na, bufB, ME,
            (long long)ME * na, G, 1.0, 0.0, nullptr, 0, nullptr, 0, 0);
-      // V at the LGL points, per element
-      for (int g = 0; g < G; ++g) {
-        gemm(0, 0, m1, n2 * n3, n1, t.I[0], m1, 0, h->eh[e0 + g].V, n1, 0, vX, m1, 0, 1, 1.0, 0.0,
-             nullptr, 0, nullptr, 0, 0);
-        gemm(0, 1, m1, m2, n2, vX, m1, (long long)m1 * n2, t.I[1], m2, 0, vY, m1, m12, n3, 1.0,
-             0.0, nullptr, 0, nullptr, 0, 0);
-        gemm(0, 1, m1 * m2, m3, n3, vY, m1 * m2, 0, t.I[2], m3, 0, vL + (long long)g * ME, m1 * m2,
-             0, 1, 1.0, 0.0, nullptr, 0, nullptr, 0, 0);
-      }
+      // V at the LGL points, of all elements of the run together (bufA is free)
+      hipLaunchKernelGGL(dg_take_v, dim3(cdiv(E.ng, 1024), G), dim3(256), 0, h->stream, (const Elem*)h->ed, e0,
+                         bufA);
+      HCHECK(hipGetLastError());
+      gemm(0, 0, m1, n2 * n3, n1, t.I[0], m1, 0, bufA, n1, E.ng, vX, m1, (long long)m1 * n2 * n3, G, 1.0, 0.0,
+           nullptr, 0, nullptr, 0, 0);
+      gemm(0, 1, m1, m2, n2, vX, m1, (long long)m1 * n2, t.I[1], m2, 0, vY, m1, m12, n3 * G, 1.0, 0.0,
+           nullptr, 0, nullptr, 0, 0);
+      gemm(0, 1, m1 * m2, m3, n3, vY, m1 * m2, m12 * n3, t.I[2], m3, 0, vL, m1 * m2, ME, G, 1.0, 0.0, nullptr, 0,
+           nullptr, 0, 0);
       hipLaunchKernelGGL(dg_lgl_weights, dim3(cdiv(ME, 256), G), dim3(256), 0, h->stream, t,
                          (const double*)vL, wq, vw);
       HCHECK(hipGetLastError());
@@ -3050,13 +3052,14 @@ int32_t dgdft_alb_nonlocal_block(dgdft_alb* h, const double* albs, double* out, 
   try {
     h->ring_reset();
     std::vector<int> all = all_elems(h->n);
-    auto P1 = h->make_prefix(all, [&](int e) { return h->eh[e].J; });
-    hipLaunchKernelGGL(dg_scatter_box, dim3(P1.total), dim3(256), 0, h->stream, h->ed, P1.active,
-                       P1.prefix, P1.na, albs, (int)S_W);
+    auto P1 = h->make_prefix(all, [&](int e) { return h->eh[e].nalb; });
+    if (P1.total > 0)
+      hipLaunchKernelGGL(dg_scatter_box, dim3(P1.total), dim3(SCATTER_THREADS), 0, h->stream, h->ed, P1.active,
+                         P1.prefix, P1.na, albs, (int)S_W);
     HCHECK(hipGetLastError());
-    h->launch_kbproj(all, S_W, 0, -1, 0);
+    h->launch_kbproj(all, S_W, 0, -2, 0);
     auto P2 = h->make_prefix(all, [](int) { return 1; });
-    hipLaunchKernelGGL(dg_nl_block, dim3(P2.na), dim3(256), 0, h->stream, h->ed, P2.active, P2.na, out);
+    hipLaunchKernelGGL(dg_nl_block, dim3(P2.na, NL_NY), dim3(256), 0, h->stream, h->ed, P2.active, P2.na, out);
     HCHECK(hipGetLastError());
     HCHECK(hipStreamSynchronize(h->stream));
     return DGDFT_OK;

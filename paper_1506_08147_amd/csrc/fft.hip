@@ -773,7 +773,7 @@ dg_kb_project(Elem* __restrict__ E, const int* __restrict__ active, const int* _
   int ai = find_elem(prefix, na, b);
   const Elem& e = E[active[ai]];
   int w = b - prefix[ai];
-  const int nc = ncols < 0 ? e.J : ncols, nb = cdiv(nc, KB_COLS);
+  const int nc = ncols == -2 ? e.nalb : ncols < 0 ? e.J : ncols, nb = cdiv(nc, KB_COLS);
   const int g = w / nb, c0 = (w - g * nb) * KB_COLS, cn = min(KB_COLS, nc - c0);
   const int p0 = e.grp_p0[g], npg = e.grp_np[g];
   const int s0 = e.grp_ptr[g], s1 = e.grp_ptr[g + 1];
