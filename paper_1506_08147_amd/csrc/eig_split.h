@@ -13,8 +13,8 @@
 // what bounds it is the latency of that chain; in one workgroup per matrix
 // (16 waves on one of 256 compute units) the chains of a matrix also queued
 // behind one another.  Measured, 16 matrices of order 816, lowest 272: all
-// four stages in one workgroup per matrix 28.5 ms, here 5.1 ms (bisect 1.3,
-// invit 1.8, cluster 0.1, back 1.9).
+// four stages in one workgroup per matrix 28.5 ms, here 4.4 ms (bisect 1.3,
+// invit 1.1, cluster 0.1, back 1.9).
 #pragma once
 #include "small_dense.h"
 
@@ -152,7 +152,9 @@ __device__ __forceinline__ void eig_bisect_body(const EigView& m, int wg, double
 // T - lambda I is fused with the forward substitution and carries its
 // recurrences in registers; only U (as 1 / pivot and two superdiagonals) and
 // x go through memory, interleaved over the lanes, and are read back CH rows
-// ahead of the recurrence.  lds: 2 n doubles + the 64 x 17 output tile.
+// ahead of the recurrence, as are d and e from LDS; no lane branches on its
+// pivot.  Measured, k of n: 272 of 816 (16 matrices) 1.78 -> 1.06 ms against a
+// branch per pivot and reads inside the recurrence, 32 of 96 (4) 168 -> 105 us.  lds: 2 n doubles + the 64 x 17 output tile.
 constexpr int EIG_INV_TILE = 64 * 17;
 __device__ __forceinline__ void eig_invit_body(const EigView& m, int wg, double* lds, double* red) {
   const int n = m.n, k = m.k;
@@ -169,69 +171,66 @@ __device__ __forceinline__ void eig_invit_body(const EigView& m, int wg, double*
   const TriBounds b = tri_bounds(t, d, e, n);
   const int lane = threadIdx.x;
   const int j = wg * EIG_INV_COLS + lane;
-  const int jc = j < k ? j : k - 1;        // idle lanes repeat the last vector, storing nothing
-  const bool live = j < k;
+  const int jc = j < k ? j : k - 1;        // idle lanes repeat the last vector and its stores
   const double lam = gld(m.w + jc);
-  const double eps = 2.220446049250313e-16, tiny = eps * b.tnorm + 1e-290;
+  const double eps = 2.220446049250313e-16, tiny = eps * b.tnorm + 1e-290, rtiny = recip(tiny);
   const long long nk = (long long)n * k;
   double* W0 = m.work + 3 * (long long)n + jc;
   auto at = [&](int a, int i) { return W0 + a * nk + (long long)i * k; };
   constexpr int CH = 8;
   double sc = 1.0;                         // scale of the stored x
   for (int it = 0; it < 3; ++it) {
-    double xb[CH], xf[CH];
+    // rows i0 .. i0 + CH - 1 of the start vector, d and e, a chunk ahead
+    double xf[CH], df[CH], ef[CH];
     auto fetch = [&](int i0) {
 #pragma unroll
       for (int c = 0; c < CH; ++c) {
         const int i = i0 + c < n ? i0 + c : n - 1;
         xf[c] = it == 0 ? start_value(((unsigned long long)jc << 32) + i) : gld(at(3, i));
+        df[c] = d[i];
+        ef[c] = e[i];
       }
     };
     fetch(0);
-    double ddi = d[0] - lam, dui = n > 1 ? e[0] : 0.0, xi = xf[0] * sc;
+    double ddi = df[0] - lam, dui = ef[0], xi = xf[0] * sc, bb = ef[0];
     fetch(1);
-    for (int i0 = 1; i0 < n; i0 += CH) {
-#pragma unroll
-      for (int c = 0; c < CH; ++c) xb[c] = xf[c];
-      if (i0 + CH < n) fetch(i0 + CH);
+    auto chunk = [&](int i0, int rows) {
+      double xb[CH], db[CH], eb[CH];
 #pragma unroll
       for (int c = 0; c < CH; ++c) {
-        const int i = i0 + c - 1;          // eliminates row i + 1
-        if (i >= n - 1) continue;
-        const double bb = e[i];
-        double ddn = d[i + 1] - lam, dun = i < n - 2 ? e[i + 1] : 0.0, xn = xb[c] * sc;
-        double piv, u1, u2, xo;
-        if (fabs(ddi) >= fabs(bb) || fabs(bb) < 1e-290) {
-          if (fabs(ddi) < 1e-290) ddi = tiny;
-          const double f = bb * recip(ddi);
-          piv = ddi; u1 = dui; u2 = 0.0; xo = xi;
-          ddn = fma(-f, dui, ddn);
-          xi = fma(-f, xi, xn);
-          dui = dun;
-        } else {
-          const double f = ddi * recip(bb);
-          piv = bb; u1 = ddn; u2 = dun; xo = xn;
-          ddn = fma(-f, ddn, dui);
-          xi = fma(-f, xn, xi);
-          dui = -f * dun;
-        }
-        ddi = ddn;
-        if (fabs(piv) < tiny) piv = piv < 0 ? -tiny : tiny;
-        if (live) {
-          gst(at(0, i), recip(piv));
-          gst(at(1, i), u1);
-          gst(at(2, i), u2);
-          gst(at(3, i), xo);
-        }
+        xb[c] = xf[c] * sc;
+        db[c] = df[c] - lam;
+        eb[c] = ef[c];
       }
-    }
+      fetch(i0 + CH);
+#pragma unroll
+      for (int c = 0; c < CH; ++c) {
+        if (c >= rows) break;
+        const int i = i0 + c - 1;          // eliminates row i + 1
+        const double ddn = db[c], dun = eb[c], xn = xb[c];   // e[n - 1] = 0
+        // row i or i + 1 as the pivot row, without a branch: lanes differ
+        const bool swap = !(fabs(ddi) >= fabs(bb) || fabs(bb) < 1e-290);
+        if (!swap && fabs(ddi) < 1e-290) ddi = tiny;
+        const double piv = swap ? bb : ddi, u1 = swap ? ddn : dui, u2 = swap ? dun : 0.0, xo = swap ? xn : xi;
+        const double rp = recip(piv), f = (swap ? ddi : bb) * rp;
+        ddi = fma(-f, u1, swap ? dui : ddn);
+        xi = fma(-f, xo, swap ? xi : xn);
+        dui = swap ? -f * dun : dun;
+        gst(at(0, i), fabs(piv) < tiny ? (piv < 0 ? -rtiny : rtiny) : rp);
+        gst(at(1, i), u1);
+        gst(at(2, i), u2);
+        gst(at(3, i), xo);
+        bb = dun;
+      }
+    };
+    int i0 = 1;
+    for (; i0 + CH <= n; i0 += CH) chunk(i0, CH);
+    if (i0 < n) chunk(i0, n - i0);
     if (fabs(ddi) < tiny) ddi = ddi < 0 ? -tiny : tiny;
-    if (live) {
-      gst(at(0, n - 1), recip(ddi));
-      gst(at(1, n - 1), 0.0);
-      gst(at(2, n - 1), 0.0);
-      gst(at(3, n - 1), xi);
-    }
+    gst(at(0, n - 1), recip(ddi));
+    gst(at(1, n - 1), 0.0);
+    gst(at(2, n - 1), 0.0);
+    gst(at(3, n - 1), xi);
     // the lane's own stores are read back below
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
@@ -248,7 +247,7 @@ __device__ __forceinline__ void eig_invit_body(const EigView& m, int wg, double*
       }
     };
     bfetch(n - 1);
-    for (int i0 = n - 1; i0 >= 0; i0 -= CH) {
+    auto bchunk = [&](int i0, int rows) {
 #pragma unroll
       for (int c = 0; c < CH; ++c) {
         r[c] = rf[c];
@@ -256,30 +255,40 @@ __device__ __forceinline__ void eig_invit_body(const EigView& m, int wg, double*
         u2[c] = u2f[c];
         v[c] = vf[c];
       }
-      if (i0 >= CH) bfetch(i0 - CH);
+      bfetch(i0 - CH);
 #pragma unroll
       for (int c = 0; c < CH; ++c) {
-        if (i0 - c < 0) continue;
+        if (c >= rows) break;
         const double s = fma(-u2[c], x2, fma(-u1[c], x1, v[c])) * r[c];
-        if (live) gst(at(3, i0 - c), s);
+        gst(at(3, i0 - c), s);
         smax = fmax(smax, fabs(s));
         x2 = x1;
         x1 = s;
       }
-    }
+    };
+    int ib = n - 1;
+    for (; ib >= CH - 1; ib -= CH) bchunk(ib, CH);
+    if (ib >= 0) bchunk(ib, ib + 1);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
     const double is = 1.0 / smax;
-    double nr[CH];
+    double nr[CH], nf[CH];
 #pragma unroll
-    for (int c = 0; c < CH; ++c) nr[c] = 0.0;
-    for (int i0 = 0; i0 < n; i0 += CH)
+    for (int c = 0; c < CH; ++c) {
+      nr[c] = 0.0;
+      nf[c] = gld(at(3, c < n ? c : n - 1));
+    }
+    for (int q = 0; q < n; q += CH) {
+      double nv[CH];
+#pragma unroll
+      for (int c = 0; c < CH; ++c) {
+        nv[c] = nf[c] * is;
+        nf[c] = gld(at(3, q + CH + c < n ? q + CH + c : n - 1));
+      }
 #pragma unroll
       for (int c = 0; c < CH; ++c)
-        if (i0 + c < n) {
-          const double v = gld(at(3, i0 + c)) * is;
-          nr[c] = fma(v, v, nr[c]);
-        }
+        if (q + c < n) nr[c] = fma(nv[c], nv[c], nr[c]);
+    }
     double s = 0.0;
 #pragma unroll
     for (int c = 0; c < CH; ++c) s += nr[c];
