@@ -13,7 +13,7 @@
 // what bounds it is the latency of that chain; in one workgroup per matrix
 // (16 waves on one of 256 compute units) the chains of a matrix also queued
 // behind one another.  Measured, 16 matrices of order 816, lowest 272: all
-// four stages in one workgroup per matrix 28.5 ms, here 4.4 ms (bisect 1.3,
+// four stages in one workgroup per matrix 28.5 ms, here 4.2 ms (bisect 1.2,
 // invit 1.1, cluster 0.1, back 1.9).
 #pragma once
 #include "small_dense.h"
@@ -30,8 +30,8 @@ struct EigView {
 
 constexpr int EIG_MAXN = 832;              // orders handled here
 constexpr int EIG_BIS_THREADS = 256;
-constexpr int EIG_BIS_G = 16;              // lanes per eigenvalue
-constexpr int EIG_BIS_P = 2;               // points per lane
+constexpr int EIG_BIS_G = 32;              // lanes per eigenvalue
+constexpr int EIG_BIS_P = 1;               // points per lane
 constexpr int EIG_BIS_COLS = EIG_BIS_THREADS / EIG_BIS_G;
 constexpr int EIG_INV_COLS = 64;           // vectors per (one-wave) workgroup
 constexpr int EIG_CL_THREADS = 1024;
@@ -77,8 +77,12 @@ __device__ __forceinline__ TriBounds tri_bounds(T& t, const double* d, const dou
 }
 
 // Eigenvalues [wg EIG_BIS_COLS, + EIG_BIS_COLS): G lanes per eigenvalue, each
-// with P points of the interval (their Sturm recurrences overlap), so a round
-// divides the interval by G P + 1 = 33 (a double's 53 bits in 11 rounds).
+// with P points of the interval, so a round divides the interval by G P + 1 =
+// 33 (a double's 53 bits in 11 rounds).  G = 32, P = 1 against 16 and 2 (the
+// same points): the second recurrence of a lane filled issue slots that the
+// extra waves fill as well, and where there are few waves it only lengthened
+// the step.  Lowest 32 of 96, 4 matrices: 95 -> 70 us; 272 of 816, 16 matrices:
+// 1.29 -> 1.21 ms, with d and e^2 read from LDS ahead of the recurrence.
 // lds: 2 n doubles.
 __device__ __forceinline__ void eig_bisect_body(const EigView& m, int wg, double* lds, double* red) {
   const int n = m.n, k = m.k;
@@ -117,15 +121,39 @@ __device__ __forceinline__ void eig_bisect_body(const EigView& m, int wg, double
       if (fabs(q[p]) < pivmin) q[p] = -pivmin;
       c[p] = q[p] < 0.0;
     }
-    for (int i = 1; i < n; ++i) {
-      const double di = d[i], ei = e2[i - 1];
+    auto step = [&](double di, double ei) {
 #pragma unroll
       for (int p = 0; p < P; ++p) {
         q[p] = fma(-ei, recip(q[p]), di - x[p]);
         if (fabs(q[p]) < pivmin) q[p] = -pivmin;
         c[p] += q[p] < 0.0;
       }
+    };
+    // d and e^2 a chunk ahead of the recurrence
+    constexpr int CH = 8;
+    double df[CH], ef[CH];
+    auto fetch = [&](int i0) {
+#pragma unroll
+      for (int u = 0; u < CH; ++u) {
+        const int i = i0 + u < n ? i0 + u : n - 1;
+        df[u] = d[i];
+        ef[u] = e2[i > 0 ? i - 1 : 0];
+      }
+    };
+    int i = 1;
+    fetch(i);
+    for (; i + CH <= n; i += CH) {
+      double dc[CH], ec[CH];
+#pragma unroll
+      for (int u = 0; u < CH; ++u) {
+        dc[u] = df[u];
+        ec[u] = ef[u];
+      }
+      fetch(i + CH);
+#pragma unroll
+      for (int u = 0; u < CH; ++u) step(dc[u], ec[u]);
     }
+    for (; i < n; ++i) step(d[i], e2[i - 1]);
     // points whose count is at most j lie below the eigenvalue
     int cnt = 0;
 #pragma unroll
