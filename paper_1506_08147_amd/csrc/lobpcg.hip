@@ -233,7 +233,7 @@ dg_cholqr(Elem* __restrict__ E, const int* __restrict__ active, int na, int init
 //      A = L^-1 D^-1 Hh D^-1 L^-T, C = D^-1 L^-T Y (L^-T kept in SM_T);
 //   1  M not numerically SPD: reduction to the eigenvectors of the scaled M
 //      above CHOL_TOL times the largest, finished inside dg_rr_reduce.
-// (Y, theta): lowest J eigenpairs of A from dg_rr_eig.
+// (Y, theta): lowest J eigenpairs of A from the eigensolver stages.
 constexpr double NEAR_ORTHO = 1e-8;
 constexpr double SERIES_ORTHO = 1e-4;
 // The [X P] Gram blocks formed from small matrices are used while the
