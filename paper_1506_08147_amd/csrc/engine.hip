@@ -686,14 +686,16 @@ struct dgdft_alb {
   // others (which start with it and end before it) on stream s2.
   static void eig_tri(const EigSrc& src, int count, const EigOrders& o, hipStream_t s, hipStream_t s2) {
     if (o.reg) hipLaunchKernelGGL(dg_tri_reg, dim3(count), dim3(TRI_REG_THREADS), 0, s2, src);
-    for (int k = 0; k + 2 <= std::max(o.step, o.wide); ++k) {
-      if (k + 2 <= o.wide)
+    for (int k = 0; k + TRI_REG_MAX < std::max(o.step, o.wide); ++k) {
+      if (k + TRI_REG_MAX < o.wide)
         hipLaunchKernelGGL(dg_tri_step, dim3(count * TRI_NWG_MAX), dim3(TRI_STEP_THREADS), tri_step_lds(o.wide), s,
                            src, k);
-      if (k + 2 <= o.step)
+      if (k + TRI_REG_MAX < o.step)
         hipLaunchKernelGGL(dg_tri_step_s, dim3(count * TRI_NWG_S), dim3(TRI_STEP_THREADS_S), tri_step_lds(o.step),
                            s2, src, k);
     }
+    if (o.wide) hipLaunchKernelGGL(dg_tri_tail, dim3(count), dim3(TRI_REG_THREADS), 0, s, src, 1);
+    if (o.step) hipLaunchKernelGGL(dg_tri_tail, dim3(count), dim3(TRI_REG_THREADS), 0, s2, src, 0);
     HCHECK(hipGetLastError());
   }
   static void eig_solve(const EigSrc& src, int count, const EigOrders& o, hipStream_t s) {

@@ -100,13 +100,6 @@ __device__ __forceinline__ int rowsK(const Elem& e, int use_ne) { return use_ne 
 // are loaded from global memory into registers while stage s is multiplied
 // out of LDS (double buffered, one barrier per stage).  Column pointers of
 // the block operands are resolved once per workgroup into an LDS table.
-// A pointer that is the same in every lane, moved to scalar registers.
-__device__ __forceinline__ const double* uniform_ptr(const double* p) {
-  const unsigned long long v = (unsigned long long)p;
-  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v);
-  const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
-  return (const double*)(((unsigned long long)hi << 32) | lo);
-}
 
 // Every vector instruction issued between two FP64 MFMAs takes its cycles from
 // the matrix pipe (measured, two waves per SIMD: 70.6 TFLOP/s with none, 58.8

@@ -21,6 +21,14 @@ __device__ __forceinline__ void gst(T* p, T v) {
   *(__attribute__((address_space(1))) T*)p = v;
 }
 
+// A pointer that is the same in every lane, moved to scalar registers.
+__device__ __forceinline__ const double* uniform_ptr(const double* p) {
+  const unsigned long long v = (unsigned long long)p;
+  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v);
+  const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
+  return (const double*)(((unsigned long long)hi << 32) | lo);
+}
+
 // HIP's double2 / float2 are structures, whose copies the compiler lowers
 // through generic pointers: go through the native two-element vector.
 typedef __attribute__((ext_vector_type(2))) double gv2d;

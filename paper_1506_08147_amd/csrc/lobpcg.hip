@@ -505,6 +505,15 @@ dg_tri_reg(EigSrc s) {
   tri_reg(m, lds);
 }
 
+// After the last dg_tri_step (wide) or dg_tri_step_s of a matrix.
+extern "C" __global__ void __launch_bounds__(TRI_REG_THREADS)
+dg_tri_tail(EigSrc s, int wide) {
+  __shared__ double lds[TRI_REG_LDS];
+  const EigView m = eig_view(s, blockIdx.x);
+  if (m.n <= TRI_REG_MAX || (m.n > TRI_STEP_SPLIT) != (wide != 0)) return;
+  tri_tail(m, lds);
+}
+
 // tri_nwg(nmax) workgroups per matrix and tri_step_lds(nmax) bytes of LDS, nmax
 // the largest order of the launch's class.
 extern "C" __global__ void __launch_bounds__(TRI_STEP_THREADS)

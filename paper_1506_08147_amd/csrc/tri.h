@@ -5,15 +5,16 @@
 //   tri_reg    orders up to TRI_REG_MAX: one workgroup holds the whole matrix
 //              in its registers
 //   tri_step   larger orders: tri_nwg(n) workgroups per matrix, one launch per
-//              Householder step
+//              Householder step, until TRI_REG_MAX rows are left
+//   tri_tail   those rows, as in tri_reg
 //
 // A step is a matrix-vector product of the trailing block and its rank-2
 // update, each needing the one before: what bounds the reduction is the
 // latency of a step, not its arithmetic ((4/3) n^3 flops in all).  Measured,
 // with the stages of eig_split.h, against one workgroup per matrix up to order
 // 512 and 8 workgroups of 256 lanes above: 32 matrices of order 432 18.4 ->
-// 8.6 ms, 16 of order 816 38.6 -> 17.9 ms (a step there takes 7 us at its end
-// and 30 us at its beginning, where it moves 85 MB: 3.9 TB/s); orders up to 96
+// 7.2 ms, 16 of order 816 38.6 -> 16.1 ms (a step there takes
+// 30 us at its beginning, where it moves 85 MB: 3.9 TB/s); orders up to 96
 // 1.5 -> 0.17 ms.
 #pragma once
 #include "eig_split.h"
@@ -32,14 +33,19 @@ constexpr int TRI_REG_LDS = (TRI_REG_WAVES + 4) * TRI_REG_MAX + 8;
 // waves apply the pending rank-2 update and form their share of A v in one
 // pass over their registers; the shares are summed by row.  The update
 // of step k - 1 is v q^T + q v^T with q = p - K v kept as (p, K, v).
+// work: d, e, tau at a stride of wld.
+// The caller fills vb[1] and pb with the pending update of a step before the
+// first (or zeros), K with its v . p tau / 2, and synchronises.
 template <int RC, int CC>
-__device__ __forceinline__ void tri_reg_body(double* A, int n, double* work, double* lds) {
+__device__ __forceinline__ void tri_reg_body(double* A0, int ld, int n, double* work, int wld, double K,
+                                             double* lds) {
   constexpr int NW = TRI_REG_WAVES, LD = TRI_REG_MAX;
   double* part = lds;                 // [NW][LD] shares of A v
   double* vb = lds + NW * LD;         // [2][LD] reflectors, zero outside their rows
   double* pb = vb + 2 * LD;           // [LD] tau A v of the last step
   double* sc = pb + 2 * LD;           // tau and the sums of v . p by wave
-  double *d = work, *e = work + n, *tau = work + 2 * n;
+  double* A = const_cast<double*>(uniform_ptr(A0));
+  double *d = const_cast<double*>(uniform_ptr(work)), *e = d + wld, *tau = e + wld;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
   double a[RC][CC];
@@ -48,11 +54,8 @@ __device__ __forceinline__ void tri_reg_body(double* A, int n, double* work, dou
 #pragma unroll
     for (int r = 0; r < RC; ++r) {
       const int i = lane + 64 * r, j = wv + NW * c;
-      a[r][c] = (i < n && j < n) ? gld(A + (i >= j ? i + n * j : j + n * i)) : 0.0;
+      a[r][c] = (i < n && j < n) ? gld(A + (i >= j ? i + ld * j : j + ld * i)) : 0.0;
     }
-  for (int i = tid; i < 4 * LD; i += TRI_REG_THREADS) vb[i] = 0.0;   // vb and pb
-  __syncthreads();
-  double K = 0.0;
   for (int k = 0; k + 2 < n; ++k) {
     double* vo = vb + ((k & 1) ^ 1) * LD;
     double* v = vb + (k & 1) * LD;
@@ -89,7 +92,7 @@ __device__ __forceinline__ void tri_reg_body(double* A, int n, double* work, dou
         const int i = lane + 64 * r;
         const double vi = i <= k || s2 == 0.0 ? 0.0 : (i == k + 1 ? v0 : x[r]);
         v[i] = vi;
-        if (i > k && i < n) gst(A + i + n * k, vi);
+        if (i > k && i < n) gst(A + i + ld * k, vi);
       }
       if (lane == 0) {
         sc[0] = tk;
@@ -162,16 +165,24 @@ __device__ __forceinline__ void tri_reg_body(double* A, int n, double* work, dou
   }
 }
 
+// vb and pb to zero (no barrier)
+__device__ __forceinline__ void tri_reg_clear(double* lds) {
+  for (int i = threadIdx.x; i < 4 * TRI_REG_MAX; i += TRI_REG_THREADS) lds[TRI_REG_WAVES * TRI_REG_MAX + i] = 0.0;
+}
+
 __device__ __forceinline__ void tri_reg(const EigView& m, double* lds) {
   if (m.n < 1) return;
-  if (m.n <= 64) tri_reg_body<1, 4>(m.A, m.n, m.work, lds);
-  else if (m.n <= 128) tri_reg_body<2, 8>(m.A, m.n, m.work, lds);
-  else tri_reg_body<3, 12>(m.A, m.n, m.work, lds);
+  const int n = m.n;
+  tri_reg_clear(lds);
+  __syncthreads();
+  if (n <= 64) tri_reg_body<1, 4>(m.A, n, n, m.work, n, 0.0, lds);
+  else if (n <= 128) tri_reg_body<2, 8>(m.A, n, n, m.work, n, 0.0, lds);
+  else tri_reg_body<3, 12>(m.A, n, n, m.work, n, 0.0, lds);
 }
 
 // ---------------------------------------------------------------------------
 // Step k of the reduction by workgroup w of a matrix's tri_nwg(n) (launches
-// k = 0 .. n - 2).  A launch never waits for another workgroup: every
+// k = 0 .. n - TRI_REG_MAX - 1; tri_tail does the rest).  A launch never waits for another workgroup: every
 // workgroup of a matrix recomputes the small per-step vectors itself from
 // what the previous launch left in device memory (double-buffered by the
 // parity of k).  Thread i owns row k + i throughout:
@@ -183,7 +194,7 @@ __device__ __forceinline__ void tri_reg(const EigView& m, double* lds) {
 //   C  the workgroup's columns j = w, w + NWG, ... of the trailing block:
 //      pending update applied and stored, column sums (rows i >= j) and row
 //      sums (columns j < i) of A v.
-// Launch n - 2 applies the last pending update to the 2 x 2 tail.  The 16
+// The 16
 // waves (8 up to order TRI_STEP_SPLIT) form four row groups (64-row chunks h,
 // h + 4, ...) by four (two) column groups, U columns a pass.  Everything a launch reads that does not depend
 // on its own sums -- the vectors of A, column k and the first columns of C
@@ -288,19 +299,6 @@ __device__ __forceinline__ void tri_step_body(double* A, int n, int k, int w, do
   }
   // ---- B: column k -> reflector k
   ai -= vi * qo0 + qi * vo0;
-  if (k == n - 2) {                                            // 2 x 2 tail
-    if (w == 0 && i < 2) {
-      if (i == 0) {
-        d[k] = ai;
-        e[k + 1] = 0.0;
-        tau[k] = 0.0;
-      } else {
-        e[k] = ai;
-        d[k + 1] = gld(A + (long long)(k + 1) + (long long)n * (k + 1)) - 2.0 * vi * qi;
-      }
-    }
-    return;
-  }
   {
     const double t = wave_sum_dpp(i >= 2 && i < mo ? ai * ai : 0.0);
     if (lane == 0) sc[16 + wv] = t;
@@ -396,7 +394,7 @@ __device__ __forceinline__ void tri_step_body(double* A, int n, int k, int w, do
 
 template <bool WIDE>
 __device__ __forceinline__ void tri_step(const EigView& m, int k, int w, double* lds) {
-  if (m.n <= TRI_REG_MAX || (m.n > TRI_STEP_SPLIT) != WIDE || k > m.n - 2 || w >= tri_nwg(m.n)) return;
+  if ((m.n > TRI_STEP_SPLIT) != WIDE || k >= m.n - TRI_REG_MAX || w >= tri_nwg(m.n)) return;
   if constexpr (WIDE) {
     if (m.n <= 768) tri_step_body<3, 3, 16, TRI_STEP_THREADS>(m.A, m.n, k, w, m.work, lds);
     else tri_step_body<4, 2, 16, TRI_STEP_THREADS>(m.A, m.n, k, w, m.work, lds);
@@ -404,6 +402,39 @@ __device__ __forceinline__ void tri_step(const EigView& m, int k, int w, double*
     if (m.n <= 256) tri_step_body<1, 6, TRI_NWG_S, TRI_STEP_THREADS_S>(m.A, m.n, k, w, m.work, lds);
     else tri_step_body<2, 3, TRI_NWG_S, TRI_STEP_THREADS_S>(m.A, m.n, k, w, m.work, lds);
   }
+}
+
+// The last TRI_REG_MAX rows after the launches of tri_step, in the registers of
+// one workgroup, starting from the update that the last of them left pending: a
+// step here takes 2.7 us, a launch there at least 7.  Measured, all stages: 32
+// matrices of order 432 8.36 -> 7.23 ms, 16 of order 816 17.0 -> 16.1 ms.
+__device__ __forceinline__ void tri_tail(const EigView& m, double* lds) {
+  constexpr int LD = TRI_REG_MAX;
+  const int n = m.n, k = n - LD, nwg = tri_nwg(n), i = threadIdx.x;   // k >= 1
+  const long long opar = (k & 1) ^ 1;
+  const double* pcol = m.work + 3 * (long long)n + opar * n;
+  const double* prow = m.work + 5 * (long long)n + opar * nwg * n;
+  const double* vbuf = m.work + (5 + 2 * nwg) * (long long)n + opar * n;
+  double* vb = lds + TRI_REG_WAVES * LD;
+  double* pb = vb + 2 * LD;
+  double* sc = pb + 2 * LD;
+  tri_reg_clear(lds);
+  __syncthreads();
+  const double tko = gld(m.work + 2 * (long long)n + k - 1);
+  if (i < LD) {
+    const double vi = gld(vbuf + i);
+    double s = gld(pcol + i);
+    for (int q = 0; q < nwg; ++q) s += gld(prow + (long long)q * n + i);
+    const double pp = tko * s;
+    vb[LD + i] = vi;
+    pb[i] = pp;
+    gst(m.A + (long long)(k + i) + (long long)n * (k - 1), vi);
+    const double t = wave_sum_dpp(vi * pp);
+    if ((i & 63) == 0) sc[1 + (i >> 6)] = t;
+  }
+  __syncthreads();
+  const double K = 0.5 * tko * (sc[1] + sc[2] + sc[3]);
+  tri_reg_body<3, 12>(m.A + (long long)k * (n + 1), n, LD, m.work + k, n, K, lds);
 }
 
 }  // namespace dg
