@@ -295,7 +295,9 @@ int32_t dgdft_alb_orthonormalise(dgdft_alb* h, int32_t elem, const double* G, do
  *   - handles with guard columns (opts.n_guard > 0) and opts.tol >= 1e-7:
  *     Knyazev's form,
  *     D = C with its first J rows zeroed (P' = [P W] [C_P; C_W], neither
- *     normalised nor orthogonal to X' = S C).  For kb = 3, where the
+ *     normalised nor orthogonal to X' = S C).  (Inside a solve, a step
+ *     without P goes on with P' = W, which spans what W C_W does and is
+ *     orthonormal.)  For kb = 3, where the
  *     solver's X and W blocks are orthonormal and mutually orthogonal, the
  *     P block is first orthonormalised against [X W] through a scaled
  *     Cholesky of its Schur complement M_PP - M_XP^T M_XP - M_WP^T M_WP;

@@ -736,8 +736,8 @@ struct dgdft_alb {
   }
 
   // Rayleigh-Ritz step (see lobpcg.hip): per-element factorisations and
-  // decisions one workgroup each, products on dg_sgemm.
-  void rr_step(const std::vector<int>& act, int single) {
+  // decisions one workgroup each, products on dg_sgemm.  w_dir: see dg_rr_e.
+  void rr_step(const std::vector<int>& act, int single, int w_dir) {
     const int N = 0, Jc = 1;
     std::vector<int> ap;
     const bool kny = knyazev();
@@ -817,8 +817,8 @@ struct dgdft_alb {
       cp(ap, cpa(SM_C, 0, 0, N, SM_C, 1, 0, N, Jc, Jc, 3));
       sg(ap, sga(0, 0, SM_MC, SM_A, SM_C, N, Jc, Jc, N, Jc, N, 1.0, 1.0));
     }
-    // E = C with its X rows zeroed (next to C); P present next; carry flag
-    rr_one(act, dg_rr_e, 256, single, RR_NY);
+    // E = C with its X rows zeroed, or [0; I] (next to C); P present next; carry flag
+    rr_one(act, dg_rr_e, 256, w_dir, RR_NY);
     // [C E]^T M [C E] and [C E]^T Hh [C E] in the basis as formed: the
     // [X' P'] blocks of the next step's S^T S and S^T H S (dg_carry_in)
     const int J2 = 2;
@@ -904,7 +904,7 @@ struct dgdft_alb {
         break;
       case 1:
         pend();
-        rr_step(act, arg);
+        rr_step(act, arg, 1);
         return;
       case 2:
         hipLaunchKernelGGL(dg_teter_energy, dim3(P.na), dim3(256), 0, stream, ed, P.active, P.na);
@@ -1760,7 +1760,7 @@ static void log_step(dgdft_alb* h, const std::vector<int>& act_all) {
 // guard columns the search direction keeps Knyazev's form: the P block is
 // orthonormalised in small space inside the Rayleigh-Ritz step and
 // P' = [P W2] [C_P; C_W], X' = X C_X + P' are formed in one pass (and
-// likewise H X', H P'); without, the next direction is orthonormalised in
+// likewise H X', H P'; P' = W2 in a step without P); without, the next direction is orthonormalised in
 // small space and [X' P'] = S [C D].
 static void iterate(dgdft_alb* h, const std::vector<int>& act) {
   h->launch_kbproj(act, VS_X, 0, -1, 1);
@@ -1832,7 +1832,8 @@ static void iterate(dgdft_alb* h, const std::vector<int>& act) {
   u3.A[0] = g3.A;
   u3.A[1] = g3.B[1];
   if (kny) {
-    // P' = [P W2] C[J:], X' = X C[:J] + P' (and the same with H)
+    // P' = [P W2] C[J:], X' = X C[:J] + P' (and the same with H); without
+    // P: P' = W2, X' = X C[:J] + W2 C[J:]
     u3.Y[0] = dgdft_alb::opnd({VS_XN});
     u3.Y[1] = dgdft_alb::opnd({VS_HXN});
     u3.Y2[0] = dgdft_alb::opnd({VS_PN});
@@ -2290,7 +2291,7 @@ int32_t dgdft_alb_rayleigh_ritz(dgdft_alb* h, int32_t elem, int32_t kb, const do
     HCHECK(hipMemcpyAsync(sm(E, SM_H), Hh, sizeof(double) * nn, hipMemcpyDeviceToDevice, h->stream));
     HCHECK(hipMemcpyAsync(sm(E, SM_M), M, sizeof(double) * nn, hipMemcpyDeviceToDevice, h->stream));
     std::vector<int> one{elem};
-    h->rr_step(one, kb == 1);
+    h->rr_step(one, kb == 1, 0);
     HCHECK(hipMemcpyAsync(theta, E.theta, sizeof(double) * J, hipMemcpyDeviceToDevice, h->stream));
     HCHECK(hipMemcpyAsync(Cout, sm(E, SM_C), sizeof(double) * (size_t)n * J, hipMemcpyDeviceToDevice,
                           h->stream));

@@ -779,16 +779,29 @@ dg_rr_pscatter(Elem* __restrict__ E, const int* __restrict__ active, int na, int
 // P present in the next step, and whether its [X P] Gram blocks are carried:
 // while the largest residual of the wanted states is at least CARRY_RES, or
 // always with guard columns.
+//
+// w_dir (the solver): a step on [X W] takes P' = W, E = [0; I].  C_W is square
+// there, so W C_W and W span the same space, but the columns of W are
+// orthonormal while those of W C_W are nearly dependent (C_W carries the spread
+// of H on W): the next step's Schur complement of the P block then had
+// eigenvalues down to 6e-9 of its scaled diagonal, and rounding in S^T S and
+// S^T H S grew by their reciprocal.  Measured on 36x36x60 with 144 columns, ALBs
+// after three iterations against a Householder-orthonormalised form of the same
+// iteration: smallest eigenvalue 5.7e-9 -> 5.1e-4, worst element 5e-10 .. 9e-10
+// -> 4e-12.
 extern "C" __global__ void __launch_bounds__(256)
-dg_rr_e(Elem* __restrict__ E, const int* __restrict__ active, int na, int single) {
+dg_rr_e(Elem* __restrict__ E, const int* __restrict__ active, int na, int w_dir) {
   __shared__ double red[4];
   const Elem& e = E[active[blockIdx.x]];
   const int J = e.J;
   const int n = (has_p(e) ? 3 : 2) * J;
+  const bool keep_w = w_dir && !has_p(e);
   double* Cm = sm(e, SM_C);
   for (int j = blockIdx.y; j < J; j += gridDim.y)
-    for (int i = threadIdx.x; i < n; i += 256)
-      gst(Cm + i + (long long)n * (J + j), i < J ? 0.0 : gld(Cm + i + (long long)n * j));
+    for (int i = threadIdx.x; i < n; i += 256) {
+      const double c = gld(Cm + i + (long long)n * j);
+      gst(Cm + i + (long long)n * (J + j), i < J ? 0.0 : !keep_w ? c : i - J == j ? 1.0 : 0.0);
+    }
   if (blockIdx.y > 0) return;
   double rmax = 0.0;
   for (int i = threadIdx.x; i < e.jc; i += blockDim.x) rmax = fmax(rmax, e.resid[i]);
