@@ -244,6 +244,31 @@ __host__ __device__ inline int gram_nchunk_e(const Elem& e, int K, int m, int n,
   }
   return gram_nchunk(K, m, n, nsum, e.gpart_cap);
 }
+// work items of an element's products of m x n0 and (n1 > 0) m x n1
+__host__ __device__ inline int gram_items(const Elem& e, int K, int m, int n0, int n1) {
+  const int t0 = cdiv(n0, tile_edge(n0)), t1 = n1 > 0 ? cdiv(n1, tile_edge(n1)) : 0;
+  return cdiv(m, GT) * (t0 + t1) * gram_nchunk_e(e, K, m, n0, n0 + n1);
+}
+// Items a launch of the products A^T B[0..njob) over K rows needs for an element
+// with (hasP) or without P; with tail, carried or not.  Only the device knows
+// whether a block is carried, and inside a captured graph also whether P is
+// present (any_p); fewer columns mean more chunks, hence by no means fewer items.
+inline int gram_grid_items(const Elem& e, int K, const Opnd& A, const Opnd* B, int njob, int tail, int hasP,
+                           bool any_p) {
+  int items = 0;
+  for (int p = any_p ? 0 : hasP; p <= (any_p ? 1 : hasP); ++p)
+    for (int carried = 0; carried <= (tail ? 1 : 0); ++carried) {
+      const int m = host_opnd_cols(A, p, e.J), skip = carried ? (p ? 2 : 1) * e.J : 0;
+      int n[2] = {0, 0};
+      for (int j = 0; j < njob; ++j) {
+        n[j] = host_opnd_cols(B[j], p, e.J);
+        if (skip < n[j]) n[j] -= skip;
+      }
+      const int c = gram_items(e, K, m, n[0], n[1]);
+      items = c > items ? c : items;
+    }
+  return items;
+}
 // chunk length, a multiple of 16
 __host__ __device__ inline int gram_chunklen(int K, int nchunk) { return cdiv(cdiv(K, nchunk), 16) * 16; }
 

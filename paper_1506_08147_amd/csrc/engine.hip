@@ -424,25 +424,11 @@ struct dgdft_alb {
   void gram(const std::vector<int>& act, const GramArgs& g, bool fp32 = false) {
     auto K = [&](int e) { return g.use_ne ? eh[e].ne : eh[e].ng; };
     // dg_gram_w: 128 rows x tile_edge(n) columns.  Carried products form only
-    // the columns after the carried block; whether an element carries is known
-    // on the device only, so the grid holds the larger of the two forms.
+    // the columns after the carried block.
     GramArgs ga = g;
     ga.tail = g.carry ? 1 : 0;
-    auto items = [&](int e, int skip) {
-      const int m = cols_host(g.A, e);
-      int c = 0, n0 = 0, nsum = 0;
-      for (int j = 0; j < g.njob; ++j) {
-        const int nj = cols_host(g.B[j], e), n = skip < nj ? nj - skip : nj;
-        c += cdiv(m, GT) * cdiv(n, tile_edge(n));
-        if (j == 0) n0 = n;
-        nsum += n;
-      }
-      return c * gram_nchunk_e(eh[e], K(e), m, n0, nsum);
-    };
     auto P = make_prefix(act, [&](int e) {
-      int c = items(e, 0);
-      if (ga.tail) c = std::max(c, items(e, (hasP_host(e) ? 2 : 1) * eh[e].J));
-      return c;
+      return gram_grid_items(eh[e], K(e), g.A, g.B, g.njob, ga.tail, hasP_host(e), capturing);
     });
     if (P.total == 0) return;
     double fl = 0, by = 0;

@@ -278,10 +278,9 @@ __device__ __forceinline__ void dg_gram_w_body(Elem* __restrict__ E, const int* 
   const int ntr = cdiv(m, TT);
   // items of one chunk, both jobs, are consecutive
   const int nt0 = ntr * cdiv(n0, tile_edge(n0)), nt1 = n1 > 0 ? ntr * cdiv(n1, tile_edge(n1)) : 0;
-  // a grid sized for more blocks than the element has now (P dropped since
-  // the launch was planned, e.g. inside a captured graph, or a carried
-  // block) leaves spare items
-  if (nt0 + nt1 == 0 || w >= (nt0 + nt1) * nch) return;
+  // a grid sized for another state of the element (with P, or without a
+  // carried block; see gram_grid_items) leaves spare items
+  if (nt0 + nt1 == 0 || w >= gram_items(e, K, m, n0, n1)) return;
   const int chunk = w / (nt0 + nt1);
   int tile = w - chunk * (nt0 + nt1);
   const int job = tile >= nt0;
