@@ -836,6 +836,19 @@ struct dgdft_alb {
     sgemm(act, single, 1, 0, SM_C, 0, SM_U, 0, SM_HC, 0, J2, J2, N, N, N, J2, 1.0, 0.0, -1);
   }
 
+  void keep_w(const std::vector<int>& act) {
+    std::vector<int> first;
+    for (int e : act)
+      if (!hasP_host(e)) first.push_back(e);
+    if (first.empty()) return;
+    auto P = make_prefix(first, [&](int e) { return eh[e].J; });
+    pbeg(DGDFT_K_OTHER, 0, 0);
+    hipLaunchKernelGGL(dg_keep_w, dim3(P.total), dim3(256), 0, stream, ed, P.active, P.prefix, P.na, (int)S_W2,
+                       (int)VS_PN, (int)S_HW, (int)VS_HPN);
+    pend();
+    HCHECK(hipGetLastError());
+  }
+
   void carry_in(const std::vector<int>& act) {
     auto P = make_prefix(act, [](int) { return 1; });
     if (P.na == 0) return;
@@ -1819,7 +1832,7 @@ static void iterate(dgdft_alb* h, const std::vector<int>& act) {
   u3.A[1] = g3.B[1];
   if (kny) {
     // P' = [P W2] C[J:], X' = X C[:J] + P' (and the same with H); without
-    // P: P' = W2, X' = X C[:J] + W2 C[J:]
+    // P: P' = W2 (keep_w), X' = X C[:J] + W2 C[J:]
     u3.Y[0] = dgdft_alb::opnd({VS_XN});
     u3.Y[1] = dgdft_alb::opnd({VS_HXN});
     u3.Y2[0] = dgdft_alb::opnd({VS_PN});
@@ -1832,6 +1845,7 @@ static void iterate(dgdft_alb* h, const std::vector<int>& act) {
   }
   u3.njob = 2; u3.cmat = SM_C; u3.ncol = -1; u3.alpha = 1.0; u3.beta = 0.0;
   h->update(act, u3);
+  if (kny) h->keep_w(act);
   h->per_elem(act, 3, 0);
   // the device carries the blocks while the largest residual (polled before
   // this iteration) is at least CARRY_RES, or always with guard columns

@@ -84,7 +84,7 @@ struct UpdArgs {
   // split = 1: the inner index runs over columns J..kA-1 of A first, the
   // partial product (alpha, no beta) is written to Y2, then columns 0..J-1
   // complete Y: with A = [X P W], Y2 = [P W] C[J:] and Y = X C[:J] + Y2 in
-  // one pass over the blocks; without P (A = [X W]) Y2 = W (see dg_rr_e)
+  // one pass over the blocks
   int split;
   Opnd Y2[2];
   // C = sm(cmat) from row crow0 J, column ccol0 J, with leading dimension kA
@@ -679,7 +679,6 @@ __device__ __forceinline__ void dg_update_w_body(Elem* __restrict__ E, const int
   // (scalars copied out of the argument block: the products below are a
   // lambda, and a reference to the by-value argument would put it on the stack)
   const double alpha = u.alpha, beta = u.beta;
-  const bool keep_w = u.split && !has_p(e);
   if constexpr (F64) {
     // 16-byte alignment of every column that is read or written in pairs
     bool ok = (ld & 1) == 0 && ld < (1LL << 28);
@@ -734,8 +733,7 @@ __device__ __forceinline__ void dg_update_w_body(Elem* __restrict__ E, const int
               double* y = yc[jl];
               if (!y) continue;
               const double* zc = colZ[jl];
-              if (!seg && keep_w) put(y, ablk(1) + (long long)(col0 + jl) * ld, 1.0, 0.0, 0.0);
-              else put(y, zc ? zc : y, b, acc[a][0][r], acc[a][1][r]);
+              put(y, zc ? zc : y, b, acc[a][0][r], acc[a][1][r]);
             }
           __syncthreads();                     // the last stage is read before the next segment's first
         }
@@ -826,14 +824,12 @@ __device__ __forceinline__ void dg_update_w_body(Elem* __restrict__ E, const int
         for (int a = 0; a < NB; ++a)
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            const int jl = a * 16 + Mf<T>::row(r, lane);
-            double* y2 = colY2[jl];
+            double* y2 = colY2[a * 16 + Mf<T>::row(r, lane)];
             if (!y2) continue;
-            const double* wc = ablk(1) + (long long)(col0 + jl) * ld;
 #pragma unroll
             for (int c = 0; c < 2; ++c) {
               int row = row0 + wr * 32 + c * 16 + (lane & 15);
-              if (row < K) gst(y2 + row, keep_w ? gld(wc + row) : alpha * (double)acc[a][c][r]);
+              if (row < K) gst(y2 + row, alpha * (double)acc[a][c][r]);
             }
           }
       }

@@ -816,6 +816,38 @@ dg_rr_e(Elem* __restrict__ E, const int* __restrict__ active, int na, int w_dir)
   }
 }
 
+// P' = W and H P' = H W of such a step (see dg_rr_e): blocks w -> pn, hw -> hpn,
+// over what the update product left there.  A pass of its own: as a branch of
+// the update kernel it took registers from every product (2306 -> 2370 ms of the
+// updates of 200 uneven elements; this pass runs once per solve, 0.2 ms for four
+// elements of 36x36x60 with 144 columns).  Work item (element, column).
+extern "C" __global__ void __launch_bounds__(256)
+dg_keep_w(Elem* __restrict__ E, const int* __restrict__ active, const int* __restrict__ prefix, int na, int w,
+          int pn, int hw, int hpn) {
+  const int ai = find_elem(prefix, na, blockIdx.x);
+  const Elem& e = E[active[ai]];
+  const long long c = (long long)(blockIdx.x - prefix[ai]) * e.ld;
+  const double *x = bp(e, w) + c, *hx = bp(e, hw) + c;
+  double *y = bp(e, pn) + c, *hy = bp(e, hpn) + c;
+  for (int i0 = threadIdx.x; i0 < e.ng; i0 += 4 * 256) {
+    double a[4], b[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int i = min(i0 + u * 256, e.ng - 1);
+      a[u] = gld(x + i);
+      b[u] = gld(hx + i);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int i = i0 + u * 256;
+      if (i < e.ng) {
+        gst(y + i, a[u]);
+        gst(hy + i, b[u]);
+      }
+    }
+  }
+}
+
 // Orthonormalised form of the next search direction (blocks without guard
 // columns): after dg_sgemm formed A = D^T M D (J x J) for D = E - C (C^T M E)
 // with E = C with its X rows zeroed (SM_Z): scaled Cholesky of A; D <- D Dg^-1
