@@ -27,6 +27,7 @@ struct Elem {
   int ng;                    // n1*n2*n3
   int ld;                    // leading dimension of blocks (= ng)
   int n_proj, n_grp;
+  int kbt_gs;                // values per entry of kbt_val (even, >= the largest group)
   int nalb, ne;              // ALBs, points of the restriction box
   int lo[3], hi[3];
   int nrad[3];
@@ -53,7 +54,7 @@ struct Elem {
   const double* grp_val;     // per point, grp_np values (beta = sqrt(dV) b)
   const int* kbt_ptr;        // ng+1: support points of groups at grid point r
   const int* kbt_pq;         // per entry: 16 (first projector) + projectors
-  const double* kbt_val;     // per entry: KB_GMAX values, as in grp_val
+  const double* kbt_val;     // per entry: kbt_gs values, as in grp_val
   double* small;             // per-element small dense workspace
   double* gpart;             // Gram split-K partial sums
   long long gpart_cap;       // doubles in gpart

@@ -323,20 +323,37 @@ struct dgdft_alb {
                            slot, col0, ncols_fixed);
     }
   }
-  void xy_inv(const XYSets& x, bool fp32, int in_slot, int out_slot, int col0, int ncols_fixed, int mode) {
+  // op: the operator's epilogue, else the transform alone
+  template <class C, int WS, int WM>
+  void xy_inv_launch(const XYSets& x, int in_slot, int out_slot, int col0, int ncols_fixed, bool op) {
+    auto go = [&](const Prefix& P, const std::vector<int>& el, auto pts, auto nt, auto waves) {
+      constexpr int M = decltype(pts)::value, NT = decltype(nt)::value, W = decltype(waves)::value;
+      int np = 0;
+      for (int e : el) np = std::max(np, eh[e].n_proj);
+      const bool many = np > KB_LDS;
+      auto k = !op ? dg_fft_xy_inv<XY_PLAIN, M, NT, W, C>
+                   : many ? dg_fft_xy_inv<XY_OP_MANY, M, NT, W, C> : dg_fft_xy_inv<XY_OP, M, NT, W, C>;
+      hipLaunchKernelGGL(k, dim3(P.total), dim3(NT), op && !many ? 2 * sizeof(double) * np : 0, stream, ed, P.active,
+                         P.prefix, P.na, in_slot, out_slot, col0, ncols_fixed);
+    };
+    using std::integral_constant;
     if (!x.tiny.empty())
-      hipLaunchKernelGGL(fp32 ? dg_fft_xy_inv32_s : dg_fft_xy_inv_s, dim3(x.Pt.total), dim3(FFT_TINY_THREADS), 0,
-                         stream, ed, x.Pt.active, x.Pt.prefix, x.Pt.na, in_slot, out_slot, col0, ncols_fixed, mode);
-    if (!x.rest.empty()) {
-      if (x.big)
-        hipLaunchKernelGGL(fp32 ? dg_fft_xy_inv32_l : dg_fft_xy_inv_l,
-                           dim3(x.Pr.total), dim3(FFT_THREADS), 0, stream, ed, x.Pr.active, x.Pr.prefix, x.Pr.na,
-                           in_slot, out_slot, col0, ncols_fixed, mode);
-      else
-        hipLaunchKernelGGL(fp32 ? dg_fft_xy_inv32_m : dg_fft_xy_inv_m,
-                           dim3(x.Pr.total), dim3(FFT_TINY_THREADS), 0, stream, ed, x.Pr.active, x.Pr.prefix, x.Pr.na,
-                           in_slot, out_slot, col0, ncols_fixed, mode);
-    }
+      go(x.Pt, x.tiny, integral_constant<int, FFT_XY_TINY>{}, integral_constant<int, FFT_TINY_THREADS>{},
+         integral_constant<int, WS>{});
+    if (x.rest.empty()) return;
+    if (x.big)
+      go(x.Pr, x.rest, integral_constant<int, FFT_MAXPTS>{}, integral_constant<int, FFT_THREADS>{},
+         integral_constant<int, 4>{});
+    else
+      go(x.Pr, x.rest, integral_constant<int, FFT_XY_SMALL>{}, integral_constant<int, FFT_TINY_THREADS>{},
+         integral_constant<int, WM>{});
+  }
+  // waves per SIMD: what the LDS tiles leave room for; none asked of FP64 on the
+  // 36 KiB tile (with four, 93 registers for 115 and 65.7 us for 59.9, 128 columns
+  // of 36x36x60)
+  void xy_inv(const XYSets& x, bool fp32, int in_slot, int out_slot, int col0, int ncols_fixed, bool op) {
+    if (fp32) xy_inv_launch<float2, 7, 7>(x, in_slot, out_slot, col0, ncols_fixed, op);
+    else xy_inv_launch<double2, 7, 1>(x, in_slot, out_slot, col0, ncols_fixed, op);
   }
 
   // The z pass of a batch by pencil size (2 n1 n3 points of a row pair):
@@ -374,7 +391,7 @@ struct dgdft_alb {
     z_pass(act, [&](int e) { return cdiv(nc(e), 2); }, fp32, col0, ncols_fixed, 0);
     pend();
     pbeg(DGDFT_K_FFT_XY_INV, 0, (fp32 ? 48.0 : 56.0) * pts);
-    xy_inv(xs, fp32, in_slot, out_slot, col0, ncols_fixed, 0);
+    xy_inv(xs, fp32, in_slot, out_slot, col0, ncols_fixed, true);
     pend();
     HCHECK(hipGetLastError());
   }
@@ -404,7 +421,7 @@ struct dgdft_alb {
            opts.precond == DGDFT_PRECOND_NONE ? 2 : opts.precond == DGDFT_PRECOND_LEARNED ? 3 : 1);
     pend();
     pbeg(DGDFT_K_FFT_XY_INV, 0, (fp32 ? 24.0 : 32.0) * pts);
-    xy_inv(xs, fp32, slot, slot, col0, ncols_fixed, 1);
+    xy_inv(xs, fp32, slot, slot, col0, ncols_fixed, false);
     pend();
     HCHECK(hipGetLastError());
   }
@@ -1494,6 +1511,7 @@ static Status set_potential_impl(dgdft_alb* h, const double* V, const dgdft_kb* 
     std::vector<int> gptr, gp0, gnp, gidx, tptr;
     std::vector<int> tpq;
     std::vector<double> gval, tval;
+    int gs = 2;   // values per entry of tval: the largest group, made even
   };
   std::vector<Lay> lay(n);
   size_t kb_bytes = 0, proj_doubles = 0;
@@ -1533,13 +1551,14 @@ static Status set_potential_impl(dgdft_alb* h, const double* V, const dgdft_kb* 
       for (int r : L.gidx) L.tptr[r + 1]++;
       for (int r = 0; r < E.ng; ++r) L.tptr[r + 1] += L.tptr[r];
       L.tpq.resize(L.tptr[E.ng]);
-      L.tval.resize((size_t)L.tptr[E.ng] * KB_GMAX);
+      for (int np : L.gnp) L.gs = std::max(L.gs, np + (np & 1));
+      L.tval.resize((size_t)L.tptr[E.ng] * L.gs);
       std::vector<int> fillpos(L.tptr.begin(), L.tptr.end() - 1);
       for (size_t g = 0; g < L.gp0.size(); ++g)
         for (int k = L.gptr[g]; k < L.gptr[g + 1]; ++k) {
           const int at = fillpos[L.gidx[k]]++;
           L.tpq[at] = 16 * L.gp0[g] + L.gnp[g];
-          std::copy_n(L.gval.begin() + (size_t)k * KB_GMAX, KB_GMAX, L.tval.begin() + (size_t)at * KB_GMAX);
+          std::copy_n(L.gval.begin() + (size_t)k * KB_GMAX, L.gs, L.tval.begin() + (size_t)at * L.gs);
         }
     }
     kb_bytes += align256(sizeof(int) * L.gptr.size()) + 2 * align256(sizeof(int) * L.gp0.size()) +
@@ -1588,6 +1607,7 @@ static Status set_potential_impl(dgdft_alb* h, const double* V, const dgdft_kb* 
       E.kbt_ptr = (const int*)put(L.tptr.data(), sizeof(int) * L.tptr.size());
       E.kbt_pq = (const int*)put(L.tpq.data(), sizeof(int) * L.tpq.size());
       E.kbt_val = (const double*)put(L.tval.data(), sizeof(double) * L.tval.size());
+      E.kbt_gs = L.gs;
     } else {
       E.kbt_ptr = nullptr; E.kbt_pq = nullptr; E.kbt_val = nullptr;
     }

@@ -511,25 +511,142 @@ dg_fft_z32_m(Elem* __restrict__ E, const int* __restrict__ active, const int* __
   fft_z_body<FFT_XY_SMALL, FFT_TINY_THREADS>(buf, E, active, prefix, na, col0, ncols, mode);
 }
 
-// Projectors whose coefficients (for two columns) an xy inverse pass keeps in LDS.
+// Projectors whose coefficients (for two columns) an operator pass keeps in LDS.
 constexpr int KB_LDS = 256;
 
+// The operator's epilogue for one plane of columns ca and ca + 1 (if hasb):
+// out = T x + V x + KB with T x in buf (times 1 / N_g), x in block `in_slot`, and
+// the projections gamma beta^T x in e.proj, in cproj (LDS) when there are at
+// most KB_LDS.  NP points of a lane at a time, the next ones' loads in flight
+// meanwhile; of the groups at a point (sum_p gamma_p beta_p(r) (beta_p^T x)), the
+// l-th of all NP points at a time.  NP = 2 where the tile leaves four waves per
+// SIMD anyway, 1 where that costs waves (18 KiB tiles and FP32).
+// What bounds it are the chains of loads (range, entry, values) and the entries
+// themselves, which every column pair reads again: hence no more than kbt_gs
+// values each.  Measured, the whole pass (one point and one projector at a time,
+// in one kernel with the preconditioner's -> this): 272 columns of 48^3 with 120
+// projectors 362 -> 267 us, with 20 261 -> 222; 128 of 36x36x60 with 48 83 -> 69,
+// with none 59 -> 60; 128 of 24^3 with 16 20 -> 19.
+template <int NT, int NP, bool LDS, class C>
+__device__ __forceinline__ void kb_epilogue(const C* buf, const double* cproj, const Elem& e, const double* IA,
+                                            const double* IB, double* OA, double* OB, const double* ga,
+                                            const double* gb, int np, long long off, bool hasb) {
+  const double sc = 1.0 / (double)e.ng;
+  const double* V = e.V + off;
+  if (!e.kbt_ptr) {
+    for (int p0 = threadIdx.x; p0 < np; p0 += 4 * NT) {
+      double v[4], a[4], b[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int p = p0 + j * NT, pc = p < np ? p : p0;
+        v[j] = gld(V + pc);
+        a[j] = gld(IA + pc);
+        b[j] = gld(IB + pc);
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int p = p0 + j * NT;
+        if (p >= np) break;
+        const C r = buf[p];
+        gst(OA + p, sc * r.x + v[j] * a[j]);
+        if (hasb) gst(OB + p, sc * r.y + v[j] * b[j]);
+      }
+    }
+    return;
+  }
+  const int* kp = e.kbt_ptr + off;
+  const int gs = e.kbt_gs;
+  double nv[NP], na[NP], nb[NP];
+  int n0[NP], n1[NP];
+  auto fetch = [&](int p0) {
+#pragma unroll
+    for (int j = 0; j < NP; ++j) {
+      const int p = p0 + j * NT, pc = p < np ? p : 0;
+      nv[j] = gld(V + pc);
+      na[j] = gld(IA + pc);
+      nb[j] = gld(IB + pc);
+      n0[j] = gld(kp + pc);
+      n1[j] = gld(kp + pc + 1);
+    }
+  };
+  fetch(threadIdx.x);
+#pragma unroll 1
+  for (int p0 = threadIdx.x; p0 < np; p0 += NP * NT) {
+    double ya[NP], yb[NP];
+    int k0[NP], k1[NP];
+#pragma unroll
+    for (int j = 0; j < NP; ++j) {
+      const int p = p0 + j * NT;
+      const C r = buf[p < np ? p : 0];
+      ya[j] = sc * r.x + nv[j] * na[j];
+      yb[j] = sc * r.y + nv[j] * nb[j];
+      k0[j] = n0[j];
+      k1[j] = p < np ? n1[j] : n0[j];
+    }
+    if (p0 + NP * NT < np) fetch(p0 + NP * NT);
+    for (;;) {
+      bool more = false;
+#pragma unroll
+      for (int j = 0; j < NP; ++j) more = more || k0[j] < k1[j];
+      if (!more) break;
+      int pq[NP];
+      double2 v0[NP], v1[NP];
+#pragma unroll
+      for (int j = 0; j < NP; ++j) {
+        const int t = k0[j] < k1[j] ? k0[j] : 0;
+        const double2* vs = (const double2*)(e.kbt_val + (long long)t * gs);
+        pq[j] = gld(e.kbt_pq + t);
+        v0[j] = gld(vs);
+        v1[j] = gs > 2 ? gld(vs + 1) : make_double2(0.0, 0.0);
+      }
+#pragma unroll
+      for (int j = 0; j < NP; ++j) {
+        if (k0[j] >= k1[j]) continue;
+        const int q0 = pq[j] >> 4, nq = pq[j] & 15;
+        auto add = [&](int k, double v) {
+          ya[j] += v * (LDS ? cproj[q0 + k] : gld(ga + q0 + k));
+          yb[j] += v * (LDS ? cproj[e.n_proj + q0 + k] : gld(gb + q0 + k));
+        };
+        add(0, v0[j].x);
+        if (nq > 1) add(1, v0[j].y);
+        if (nq > 2) add(2, v1[j].x);
+        if (nq > 3) add(3, v1[j].y);
+        for (int k = 4; k < nq; ++k) add(k, gld(e.kbt_val + (long long)k0[j] * gs + k));
+        ++k0[j];
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < NP; ++j) {
+      const int p = p0 + j * NT;
+      if (p < np) {
+        gst(OA + p, ya[j]);
+        if (hasb) gst(OB + p, yb[j]);
+      }
+    }
+  }
+}
+
 // Pass 3: inverse xy transform and epilogue.  Work item (pair q, plane z).
-// mode 0 (operator): out = T x + V x + KB, reading x from block `in_slot`
-//   and the projections gamma beta^T x from e.proj (n_proj x ncols).
-// mode 1 (plain): out = result (preconditioner; out may equal in).
-template <int MAXPTS, int NT, class C>
-__device__ __forceinline__ void fft_xy_inv_body(C* buf, double* cproj, Elem* __restrict__ E,
-                                                const int* __restrict__ active,
-                                                const int* __restrict__ prefix, int na, int in_slot,
-                                                int out_slot, int col0, int ncols, int mode) {
+//   XY_PLAIN    out = result (the preconditioner; out may equal in)
+//   XY_OP       out = T x + V x + KB (kb_epilogue), at most KB_LDS projectors per
+//               element; the launch gives LDS for two columns' projections of
+//               the largest
+//   XY_OP_MANY  the same for any number of projectors
+// A kernel for each: in one kernel the preconditioner's passes had the registers
+// and the LDS of the operator's, and both had the scalar registers of all three.
+enum XYInv { XY_PLAIN, XY_OP, XY_OP_MANY };
+template <int KIND, int MAXPTS, int NT, int WAVES, class C>
+__global__ void __launch_bounds__(NT, WAVES)
+dg_fft_xy_inv(Elem* __restrict__ E, const int* __restrict__ active, const int* __restrict__ prefix, int na,
+              int in_slot, int out_slot, int col0, int ncols) {
+  __shared__ C buf[MAXPTS];
+  extern __shared__ double cproj[];        // XY_OP: projections of the two columns
   int b = blockIdx.x;
   int ai = find_elem(prefix, na, b);
   const Elem& e = E[active[ai]];
   int w = b - prefix[ai];
   int q = w / e.n3, z = w - q * e.n3;
   int n1 = e.n1, n2 = e.n2, np = n1 * n2;
-  const double sc = 1.0 / (double)e.ng;
   const int nc = ncols < 0 ? e.J : ncols;
   int ca = col0 + 2 * q, cb = ca + 1;
   bool hasb = cb < col0 + nc;
@@ -538,14 +655,16 @@ __device__ __forceinline__ void fft_xy_inv_body(C* buf, double* cproj, Elem* __r
   double* OB = bp(e, out_slot) + (long long)cb * e.ld + off;
   const C* Z = zpair<C>(e, q) + (long long)z * np;
   constexpr int NL = (MAXPTS + NT - 1) / NT;
-  // the columns' projections times gamma, for the operator's epilogue
-  if (mode == 0 && e.n_proj <= KB_LDS)
-    for (int t = threadIdx.x; t < e.n_proj; t += NT) {
-      const double* g = e.proj + (long long)(ca - col0) * e.n_proj + t;
-      cproj[t] = gld(g);
-      cproj[KB_LDS + t] = hasb ? gld(g + e.n_proj) : 0.0;
-    }
+  const double* ga = nullptr;
+  const double* gb = nullptr;
+  if constexpr (KIND != XY_PLAIN) {
+    ga = e.proj + (long long)(ca - col0) * e.n_proj;
+    gb = hasb ? ga + e.n_proj : ga;
+  }
   {
+    static_assert(KB_LDS <= NT, "one projection of each column per lane");
+    const bool pl = KIND == XY_OP && threadIdx.x < e.n_proj;
+    const double pa = pl ? gld(ga + threadIdx.x) : 0.0, pb = pl ? gld(gb + threadIdx.x) : 0.0;
     C rz[NL];
 #pragma unroll
     for (int u = 0; u < NL; ++u) {
@@ -557,152 +676,27 @@ __device__ __forceinline__ void fft_xy_inv_body(C* buf, double* cproj, Elem* __r
       const int p = threadIdx.x + u * NT;
       if (p < np) buf[p] = rz[u];
     }
+    if (pl) {
+      cproj[threadIdx.x] = pa;
+      cproj[e.n_proj + threadIdx.x] = pb;
+    }
   }
   __syncthreads();
   fft_lines<MAXPTS, NT>(buf, n2, n1, 1, n1, e.rad[1], e.nrad[1], twiddles<C>(e, 1), 1.0);
   fft_lines<MAXPTS, NT>(buf, n1, n2, n1, 1, e.rad[0], e.nrad[0], twiddles<C>(e, 0), 1.0);
-  if (mode == 0) {
-    const double* ga = e.proj + (long long)(ca - col0) * e.n_proj;
-    const double* gb = hasb ? ga + e.n_proj : ga;
-    const double* cA = e.n_proj <= KB_LDS ? cproj : ga;
-    const double* cB = e.n_proj <= KB_LDS ? cproj + KB_LDS : gb;
+  if constexpr (KIND != XY_PLAIN) {
+    constexpr int NP = sizeof(C) == sizeof(double2) && MAXPTS > FFT_XY_TINY ? 2 : 1;
     const double* IA = bp(e, in_slot) + (long long)ca * e.ld + off;
     const double* IB = hasb ? IA + e.ld : IA;
-    const double* V = e.V + off;
-    const int* kp = e.kbt_ptr ? e.kbt_ptr + off : nullptr;
-    // NP points of a lane at a time, the next ones' loads in flight meanwhile;
-    // of the groups at a point (sum_p gamma_p beta_p(r) (beta_p^T x)), the l-th
-    // of all NP points at a time.  One point and one group at a time, their
-    // chains of loads (range, entry, values) were most of this pass: with 120
-    // projectors on 48^3 (272 columns), 368 us of which the transform is 150; 340 us this way.
-    constexpr int NP = 3;
-    double nv[NP], na[NP], nb[NP];
-    int n0[NP], n1[NP];
-    auto fetch = [&](int u0) {
-#pragma unroll
-      for (int j = 0; j < NP; ++j) {
-        const int p = threadIdx.x + (u0 + j) * NT, pc = p < np ? p : 0;
-        nv[j] = gld(V + pc);
-        na[j] = gld(IA + pc);
-        nb[j] = gld(IB + pc);
-        n0[j] = kp ? gld(kp + pc) : 0;
-        n1[j] = kp ? gld(kp + pc + 1) : 0;
-      }
-    };
-    fetch(0);
-#pragma unroll 1
-    for (int u0 = 0; u0 < NL; u0 += NP) {
-      double ya[NP], yb[NP];
-      int k0[NP], k1[NP];
-#pragma unroll
-      for (int j = 0; j < NP; ++j) {
-        const int p = threadIdx.x + (u0 + j) * NT;
-        const C r = buf[p < np ? p : 0];
-        ya[j] = sc * r.x + nv[j] * na[j];
-        yb[j] = sc * r.y + nv[j] * nb[j];
-        k0[j] = n0[j];
-        k1[j] = p < np ? n1[j] : n0[j];
-      }
-      if (u0 + NP < NL) fetch(u0 + NP);
-      for (;;) {
-        bool more = false;
-#pragma unroll
-        for (int j = 0; j < NP; ++j) more = more || k0[j] < k1[j];
-        if (!more) break;
-        int pq[NP];
-        double2 v0[NP], v1[NP];
-#pragma unroll
-        for (int j = 0; j < NP; ++j) {
-          const int t = k0[j] < k1[j] ? k0[j] : 0;
-          const double2* vs = (const double2*)(e.kbt_val + (long long)t * KB_GMAX);
-          pq[j] = gld(e.kbt_pq + t);
-          v0[j] = gld(vs);
-          v1[j] = gld(vs + 1);
-        }
-#pragma unroll
-        for (int j = 0; j < NP; ++j) {
-          if (k0[j] >= k1[j]) continue;
-          const int q0 = pq[j] >> 4, nq = pq[j] & 15;
-          auto add = [&](int k, double v) {
-            ya[j] += v * cA[q0 + k];
-            yb[j] += v * cB[q0 + k];
-          };
-          add(0, v0[j].x);
-          if (nq > 1) add(1, v0[j].y);
-          if (nq > 2) add(2, v1[j].x);
-          if (nq > 3) add(3, v1[j].y);
-          for (int k = 4; k < nq; ++k) add(k, gld(e.kbt_val + (long long)k0[j] * KB_GMAX + k));
-          ++k0[j];
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < NP; ++j) {
-        const int p = threadIdx.x + (u0 + j) * NT;
-        if (p < np) {
-          gst(OA + p, ya[j]);
-          if (hasb) gst(OB + p, yb[j]);
-        }
-      }
-    }
+    kb_epilogue<NT, NP, KIND == XY_OP>(buf, cproj, e, IA, IB, OA, OB, ga, gb, np, off, hasb);
   } else {
+    const double sc = 1.0 / (double)e.ng;
     for (int p = threadIdx.x; p < np; p += NT) {
       const C r = buf[p];
       gst(OA + p, sc * r.x);
       if (hasb) gst(OB + p, sc * r.y);
     }
   }
-}
-
-extern "C" __global__ void __launch_bounds__(FFT_THREADS, 4)
-dg_fft_xy_inv_l(Elem* __restrict__ E, const int* __restrict__ active, const int* __restrict__ prefix,
-                int na, int in_slot, int out_slot, int col0, int ncols, int mode) {
-  __shared__ double2 buf[FFT_MAXPTS];
-  __shared__ double cproj[2 * KB_LDS];
-  fft_xy_inv_body<FFT_MAXPTS, FFT_THREADS>(buf, cproj, E, active, prefix, na, in_slot, out_slot, col0, ncols, mode);
-}
-
-extern "C" __global__ void __launch_bounds__(FFT_THREADS, 4)
-dg_fft_xy_inv32_l(Elem* __restrict__ E, const int* __restrict__ active, const int* __restrict__ prefix,
-                  int na, int in_slot, int out_slot, int col0, int ncols, int mode) {
-  __shared__ float2 buf[FFT_MAXPTS];
-  __shared__ double cproj[2 * KB_LDS];
-  fft_xy_inv_body<FFT_MAXPTS, FFT_THREADS>(buf, cproj, E, active, prefix, na, in_slot, out_slot, col0, ncols, mode);
-}
-
-extern "C" __global__ void __launch_bounds__(FFT_TINY_THREADS)
-dg_fft_xy_inv_s(Elem* __restrict__ E, const int* __restrict__ active, const int* __restrict__ prefix,
-                int na, int in_slot, int out_slot, int col0, int ncols, int mode) {
-  __shared__ double2 buf[FFT_XY_TINY];
-  __shared__ double cproj[2 * KB_LDS];
-  fft_xy_inv_body<FFT_XY_TINY, FFT_TINY_THREADS>(buf, cproj, E, active, prefix, na, in_slot, out_slot, col0, ncols,
-                                                 mode);
-}
-
-extern "C" __global__ void __launch_bounds__(FFT_TINY_THREADS)
-dg_fft_xy_inv32_s(Elem* __restrict__ E, const int* __restrict__ active, const int* __restrict__ prefix,
-                  int na, int in_slot, int out_slot, int col0, int ncols, int mode) {
-  __shared__ float2 buf[FFT_XY_TINY];
-  __shared__ double cproj[2 * KB_LDS];
-  fft_xy_inv_body<FFT_XY_TINY, FFT_TINY_THREADS>(buf, cproj, E, active, prefix, na, in_slot, out_slot, col0, ncols,
-                                                 mode);
-}
-
-extern "C" __global__ void __launch_bounds__(FFT_TINY_THREADS)
-dg_fft_xy_inv_m(Elem* __restrict__ E, const int* __restrict__ active, const int* __restrict__ prefix,
-                int na, int in_slot, int out_slot, int col0, int ncols, int mode) {
-  __shared__ double2 buf[FFT_XY_SMALL];
-  __shared__ double cproj[2 * KB_LDS];
-  fft_xy_inv_body<FFT_XY_SMALL, FFT_TINY_THREADS>(buf, cproj, E, active, prefix, na, in_slot, out_slot, col0, ncols,
-                                                  mode);
-}
-
-extern "C" __global__ void __launch_bounds__(FFT_TINY_THREADS)
-dg_fft_xy_inv32_m(Elem* __restrict__ E, const int* __restrict__ active, const int* __restrict__ prefix,
-                  int na, int in_slot, int out_slot, int col0, int ncols, int mode) {
-  __shared__ float2 buf[FFT_XY_SMALL];
-  __shared__ double cproj[2 * KB_LDS];
-  fft_xy_inv_body<FFT_XY_SMALL, FFT_TINY_THREADS>(buf, cproj, E, active, prefix, na, in_slot, out_slot, col0, ncols,
-                                                  mode);
 }
 
 // ---------------------------------------------------------------------------
