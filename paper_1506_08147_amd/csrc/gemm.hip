@@ -681,7 +681,8 @@ __device__ __forceinline__ void dg_update_w_body(Elem* __restrict__ E, const int
   const double alpha = u.alpha, beta = u.beta;
   if constexpr (F64) {
     // 16-byte alignment of every column that is read or written in pairs
-    bool ok = (ld & 1) == 0 && ld < (1LL << 28);
+    // and 32-bit byte offsets (of a row of A, and of C over a tile's columns)
+    bool ok = (ld & 1) == 0 && ld < (1LL << 28) && cld < (1 << 21);
     if (tid < UTN)
       ok = ok && (((unsigned long long)colY[tid] | (unsigned long long)colY2[tid] | (unsigned long long)colZ[tid]) & 15) == 0;
     const int nab = __builtin_amdgcn_readfirstlane(A.ncols >= 0 ? 1 : cdiv(kA, e.J));
