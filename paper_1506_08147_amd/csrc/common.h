@@ -270,6 +270,18 @@ inline int gram_grid_items(const Elem& e, int K, const Opnd& A, const Opnd* B, i
     }
   return items;
 }
+// Products of a batch per launch, each with `items` items and `part` doubles of
+// partial sums: all while these fit GRAM_BATCH_PART (allocating the partials
+// costs about 4 us per MiB: with all 200 products 96 x 32 over 13824 rows at once
+// 430 us of a call went there), else launches of some 2048 items, four rounds of
+// the card, that share them.
+constexpr long long GRAM_BATCH_PART = 1LL << 22;
+constexpr int GRAM_BATCH_ITEMS = 2048;
+inline int gram_batch(int count, int items, long long part) {
+  if (part * count <= GRAM_BATCH_PART) return count;
+  const long long launches = ((long long)count * items + GRAM_BATCH_ITEMS - 1) / GRAM_BATCH_ITEMS;
+  return (int)((count + launches - 1) / launches);
+}
 // chunk length, a multiple of 16
 __host__ __device__ inline int gram_chunklen(int K, int nchunk) { return cdiv(cdiv(K, nchunk), 16) * 16; }
 

@@ -2506,10 +2506,36 @@ int32_t dgdft_gemm_batched(int32_t trans, int32_t count, int64_t K, int32_t m, i
   hipStream_t s = (hipStream_t)stream;
   try {
     TmpDev t;
-    std::vector<Elem> eh(count);
-    const long long cap = (long long)GRAM_CHUNKS * m * n;
-    const int nch = gram_nchunk((int)K, m, n, n, cap);
-    double* gp = trans ? t.alloc<double>((size_t)count * nch * m * n) : nullptr;
+    // partial sums of the transposed products; without room for the default
+    // rule's, one product at a time with the fewest chunks
+    long long cap = (long long)GRAM_CHUNKS * m * n;
+    int nch = 1, items = cdiv((int)K, GT) * cdiv(n, tile_edge(n)), per = count;
+    double* gp = nullptr;
+    if (trans) {
+      auto plan = [&] {
+        nch = gram_nchunk((int)K, m, n, n, cap);
+        items = cdiv(m, GT) * cdiv(n, tile_edge(n)) * nch;
+      };
+      plan();
+      per = gram_batch(count, items, (long long)nch * m * n);
+      try {
+        gp = t.alloc<double>((size_t)per * nch * m * n);
+      } catch (HipFail&) {
+        (void)hipGetLastError();
+        cap = (long long)m * n;
+        plan();
+        per = 1;
+        gp = t.alloc<double>((size_t)nch * m * n);
+      }
+    }
+    // descriptors, element numbers and the prefix arrays (those of any launch:
+    // all products have the same items) in one allocation and one copy
+    const size_t off_act = align256(sizeof(Elem) * count), off_pre = off_act + align256(sizeof(int) * count),
+                 off_pre2 = off_pre + align256(sizeof(int) * (per + 1));
+    std::vector<char> host(off_pre2 + align256(sizeof(int) * (per + 1)));
+    Elem* eh = new (host.data()) Elem[count]();
+    int *act = (int*)(host.data() + off_act), *pre = (int*)(host.data() + off_pre),
+        *pre2 = (int*)(host.data() + off_pre2);
     for (int i = 0; i < count; ++i) {
       Elem& e = eh[i];
       e.ng = e.ld = (int)K;
@@ -2518,7 +2544,7 @@ int32_t dgdft_gemm_batched(int32_t trans, int32_t count, int64_t K, int32_t m, i
         e.blk[S_U0] = const_cast<double*>(A) + (size_t)i * K * m;
         e.blk[S_U1] = const_cast<double*>(B) + (size_t)i * K * n;
         e.small = C + (size_t)i * m * n;
-        e.gpart = gp + (size_t)i * nch * m * n;
+        e.gpart = gp + (size_t)(i % per) * nch * m * n;
         e.gpart_cap = cap;
       } else {
         e.blk[S_U0] = const_cast<double*>(A) + (size_t)i * K * m;
@@ -2526,42 +2552,37 @@ int32_t dgdft_gemm_batched(int32_t trans, int32_t count, int64_t K, int32_t m, i
         e.blk[S_U2] = C + (size_t)i * K * n;
       }
       e.small_stride = 0;
+      act[i] = i;
     }
-    Elem* ed = t.alloc<Elem>(count);
-    HCHECK(hipMemcpy(ed, eh.data(), sizeof(Elem) * count, hipMemcpyHostToDevice));
-    std::vector<int> act(count), pre(count + 1, 0), pre2(count + 1, 0);
+    for (int i = 0; i <= per; ++i) {
+      pre[i] = i * items;
+      pre2[i] = i * cdiv(m * n, 256);
+    }
+    char* dev = t.alloc<char>(host.size());
+    HCHECK(hipMemcpy(dev, host.data(), host.size(), hipMemcpyHostToDevice));
+    Elem* ed = (Elem*)dev;
+    const int *d_pre = (const int*)(dev + off_pre), *d_pre2 = (const int*)(dev + off_pre2);
     Opnd oa{}, ob{}, oc{};
     oa.nblk = ob.nblk = oc.nblk = 1;
     oa.slot[0] = S_U0; oa.ncols = m;
     ob.slot[0] = S_U1; ob.ncols = n;
     oc.slot[0] = S_U2; oc.ncols = n;
-    for (int i = 0; i < count; ++i) {
-      act[i] = i;
+    for (int i0 = 0; i0 < count; i0 += per) {
+      const int na = std::min(per, count - i0);
+      const int* d_act = (const int*)(dev + off_act) + i0;
       if (trans) {
-        pre[i + 1] = pre[i] + cdiv(m, GT) * cdiv(n, tile_edge(n)) * nch;
-        pre2[i + 1] = pre2[i] + cdiv(m * n, 256);
+        GramArgs g{};
+        g.A = oa; g.B[0] = ob; g.njob = 1; g.out_mat[0] = 0; g.upper = 0;
+        hipLaunchKernelGGL(fp32 ? dg_gram_w32 : dg_gram_w, dim3(na * items), dim3(256), 0, s, ed, d_act, d_pre, na,
+                           g);
+        hipLaunchKernelGGL(dg_gram_reduce, dim3(pre2[na]), dim3(256), 0, s, ed, d_act, d_pre2, na, g);
       } else {
-        pre[i + 1] = pre[i] + cdiv((int)K, GT) * cdiv(n, tile_edge(n));
+        UpdArgs u{};
+        u.A[0] = oa; u.Y[0] = oc; u.njob = 1; u.cmat = 0; u.ccol0 = 0; u.ncol = n;
+        u.alpha = alpha; u.beta = beta;
+        hipLaunchKernelGGL(fp32 ? dg_update_w32 : dg_update_w, dim3(na * items), dim3(256), 0, s, ed, d_act, d_pre,
+                           na, u);
       }
-    }
-    int* d_act = t.alloc<int>(count);
-    int* d_pre = t.alloc<int>(count + 1);
-    int* d_pre2 = t.alloc<int>(count + 1);
-    HCHECK(hipMemcpy(d_act, act.data(), sizeof(int) * count, hipMemcpyHostToDevice));
-    HCHECK(hipMemcpy(d_pre, pre.data(), sizeof(int) * (count + 1), hipMemcpyHostToDevice));
-    HCHECK(hipMemcpy(d_pre2, pre2.data(), sizeof(int) * (count + 1), hipMemcpyHostToDevice));
-    if (trans) {
-      GramArgs g{};
-      g.A = oa; g.B[0] = ob; g.njob = 1; g.out_mat[0] = 0; g.upper = 0;
-      hipLaunchKernelGGL(fp32 ? dg_gram_w32 : dg_gram_w, dim3(pre[count]), dim3(256), 0, s, ed, d_act,
-                         d_pre, count, g);
-      hipLaunchKernelGGL(dg_gram_reduce, dim3(pre2[count]), dim3(256), 0, s, ed, d_act, d_pre2, count, g);
-    } else {
-      UpdArgs u{};
-      u.A[0] = oa; u.Y[0] = oc; u.njob = 1; u.cmat = 0; u.ccol0 = 0; u.ncol = n;
-      u.alpha = alpha; u.beta = beta;
-      hipLaunchKernelGGL(fp32 ? dg_update_w32 : dg_update_w, dim3(pre[count]), dim3(256), 0, s, ed, d_act,
-                         d_pre, count, u);
     }
     HCHECK(hipGetLastError());
     HCHECK(hipStreamSynchronize(s));
