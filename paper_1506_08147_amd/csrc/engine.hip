@@ -2388,7 +2388,7 @@ static bool syev_args_ok(int32_t count, int32_t n, int32_t k, const double* A, c
 
 static void launch_syev(int32_t count, int32_t n, int32_t k, const double* A, double* w, double* Z,
                         int32_t method, double* work, hipStream_t s) {
-  if (method == 0 && n <= EIG_MAXN) {
+  if (method == 0 && n > SYEV_TINY && n <= EIG_MAXN) {
     const int nb = cdiv(n, SYEV_COPY_TILE);
     EigSrc src{};
     src.kind = 2;
@@ -2397,7 +2397,7 @@ static void launch_syev(int32_t count, int32_t n, int32_t k, const double* A, do
     src.Z = Z;
     src.n = n;
     src.k = k;
-    hipLaunchKernelGGL(dg_syev_batch_copy, dim3((unsigned)count * nb * nb), dim3(256), 0, s, A, n, k, work);
+    hipLaunchKernelGGL(dg_syev_batch_copy, dim3(count, nb * nb), dim3(256), 0, s, A, n, k, work);
     dgdft_alb::EigOrders o;
     o.add(n, k);
     dgdft_alb::eig_solve(src, count, o, s);

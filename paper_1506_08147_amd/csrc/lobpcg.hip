@@ -1124,8 +1124,8 @@ dg_check_finite(const double* __restrict__ a, long long n, int* flag) {
 namespace dg {
 // Batched symmetric eigensolver for tests: matrix b of A (n x n, upper
 // triangle read) -> w[b*n ..] ascending, Z[b*n*k ..] first k eigenvectors.
-// method 0 above order EIG_MAXN: Householder + bisection + inverse iteration
-// (lowest k only); method 1: Householder + implicit QL on the whole spectrum.
+// method 0 up to order SYEV_TINY or above EIG_MAXN: Householder + bisection +
+// inverse iteration (lowest k only); method 1: Householder + implicit QL on the whole spectrum.
 extern "C" __global__ void __launch_bounds__(SMALL_THREADS)
 dg_syev_batch(const double* __restrict__ A, double* w, double* Z, int n, int k, double* work,
               int method) {
@@ -1145,18 +1145,22 @@ dg_syev_batch(const double* __restrict__ A, double* w, double* Z, int n, int k, 
   }
 }
 
-// Method 0 up to order EIG_MAXN: the lower triangle of each matrix's copy from
-// its upper one, in 32 x 32 tiles through LDS (blockIdx.x = matrix x tile),
+// Method 0 for orders above SYEV_TINY up to EIG_MAXN: the lower triangle of each matrix's copy from
+// its upper one, in 32 x 32 tiles through LDS (grid (matrices, tiles)),
 // then the tridiagonalisation and the stages of eig_split.h.
 constexpr int SYEV_COPY_TILE = 32;
+// Orders up to SYEV_TINY stay in dg_syev_batch: six launches against one.
+// Measured, 4 matrices of order 1, 3, 4, 5: 47, 55, 58, 61 us in stages; 28, 48,
+// 56, 74 in one launch.
+constexpr int SYEV_TINY = 4;
 extern "C" __global__ void __launch_bounds__(256)
 dg_syev_batch_copy(const double* __restrict__ A, int n, int k, double* work) {
   constexpr int TS = SYEV_COPY_TILE;
   __shared__ double tile[TS][TS + 1];
   const int nb = cdiv(n, TS);
-  const int q = blockIdx.x % (nb * nb), bi = q % nb, bj = q / nb;
+  const int q = blockIdx.y, bi = q % nb, bj = q / nb;
   if (bj > bi) return;
-  const long long b = blockIdx.x / (nb * nb);
+  const long long b = blockIdx.x;
   const double* S = A + b * n * n;
   double* Aw = work + b * syev_stride(n, k);
   const int r = threadIdx.x % TS, c0 = threadIdx.x / TS;
