@@ -14,6 +14,10 @@
 namespace dg {
 
 constexpr int CH_B = 16;                   // block
+// below, column by column: a block always takes its 16 steps.  Measured,
+// orthonormalisation of order 1, 4, 8, 12: 70, 84, 85, 87 us in blocks, 61, 79,
+// 86, 92 column by column.
+constexpr int CH_MINN = 8;
 constexpr int CH_MAXN = 832;               // one panel row per lane, panel in LDS
 constexpr int CH_LDX = CH_B + 1;           // panel row stride (conflict-free fragment reads)
 constexpr int CH_THREADS = 1024;
@@ -254,11 +258,11 @@ __device__ void tri_inv_t_blocked(T& t, const double* L, int ldl, double* Y, int
 // Either form by order.
 template <class T>
 __device__ __forceinline__ int chol_any(T& t, double* A, int lda, int n, double tol, double* lds) {
-  return n <= CH_MAXN ? chol_blocked(t, A, lda, n, tol, lds) : chol_lower(t, A, lda, n, tol);
+  return n >= CH_MINN && n <= CH_MAXN ? chol_blocked(t, A, lda, n, tol, lds) : chol_lower(t, A, lda, n, tol);
 }
 template <class T>
 __device__ __forceinline__ void tri_inv_t_any(T& t, const double* L, int ldl, double* Y, int ldy, int n, double* lds) {
-  if (n <= CH_MAXN) tri_inv_t_blocked(t, L, ldl, Y, ldy, n, lds);
+  if (n >= CH_MINN && n <= CH_MAXN) tri_inv_t_blocked(t, L, ldl, Y, ldy, n, lds);
   else tri_inv_lower_t(t, L, ldl, Y, ldy, n, lds, CH_LDS);
 }
 
