@@ -148,11 +148,14 @@ struct LglTab {
 };
 
 // Legendre P_N(x) and P_{N-1}(x) by the three-term recurrence; rk[k] = 1 / (k + 1).
+// The quotient is corrected by its remainder, which rounds it as a division
+// does: with the product alone the volume blocks of the slab were 6.9e-15 off
+// their value in 64 bits, with divisions 6.1e-15.
 __device__ inline void legendre_pair(int N, double x, const double* rk, double& pn, double& pn1) {
   double p0 = 1.0, p1 = x;
   if (N == 0) { pn = 1.0; pn1 = 0.0; return; }
   for (int k = 1; k < N; ++k) {
-    double p2 = ((2 * k + 1) * x * p1 - k * p0) * rk[k];
+    const double s = (2 * k + 1) * x * p1 - k * p0, q = s * rk[k], p2 = fma(fma(-(k + 1.0), q, s), rk[k], q);
     p0 = p1;
     p1 = p2;
   }
