@@ -31,7 +31,6 @@ struct EigView {
 constexpr int EIG_MAXN = 832;              // orders handled here
 constexpr int EIG_BIS_THREADS = 256;
 constexpr int EIG_BIS_G = 32;              // lanes per eigenvalue
-constexpr int EIG_BIS_P = 1;               // points per lane
 constexpr int EIG_BIS_COLS = EIG_BIS_THREADS / EIG_BIS_G;
 constexpr int EIG_INV_COLS = 64;           // vectors per (one-wave) workgroup
 constexpr int EIG_CL_THREADS = 1024;
@@ -77,9 +76,9 @@ __device__ __forceinline__ TriBounds tri_bounds(T& t, const double* d, const dou
 }
 
 // Eigenvalues [wg EIG_BIS_COLS, + EIG_BIS_COLS): G lanes per eigenvalue, each
-// with P points of the interval, so a round divides the interval by G P + 1 =
-// 33 (a double's 53 bits in 11 rounds).  G = 32, P = 1 against 16 and 2 (the
-// same points): the second recurrence of a lane filled issue slots that the
+// with one point of the interval, so a round divides the interval by G + 1 =
+// 33 (a double's 53 bits in 11 rounds).  G = 32 against 16 with two points a lane
+// (the same points): the second recurrence of a lane filled issue slots that the
 // extra waves fill as well, and where there are few waves it only lengthened
 // the step.  Lowest 32 of 96, 4 matrices: 95 -> 70 us; 272 of 816, 16 matrices:
 // 1.29 -> 1.21 ms, with d and e^2 read from LDS ahead of the recurrence.
@@ -100,7 +99,7 @@ __device__ __forceinline__ void eig_bisect_body(const EigView& m, int wg, double
   const TriBounds b = tri_bounds(t, d, e2, n);
   for (int i = t.tid(); i < n; i += t.nt()) e2[i] *= e2[i];
   t.sync();
-  constexpr int G = EIG_BIS_G, P = EIG_BIS_P;
+  constexpr int G = EIG_BIS_G;
   const double eps = 2.220446049250313e-16, pivmin = b.pivmin;
   const int lane = threadIdx.x & 63, sidx = threadIdx.x % G;
   const int j = wg * EIG_BIS_COLS + threadIdx.x / G;
@@ -111,23 +110,15 @@ __device__ __forceinline__ void eig_bisect_body(const EigView& m, int wg, double
   for (int it = 0; it < 200; ++it) {
     if (!done && hi - lo <= 2.0 * eps * fmax(fabs(lo), fabs(hi)) + pivmin) done = true;
     if (__all(done ? 1 : 0)) break;
-    // points in ascending order over (p, lane): p G + sidx + 1 of G P + 1
-    double x[P], q[P];
-    int c[P];
-#pragma unroll
-    for (int p = 0; p < P; ++p) {
-      x[p] = lo + (hi - lo) * (double)(p * G + sidx + 1) / (double)(G * P + 1);
-      q[p] = d[0] - x[p];
-      if (fabs(q[p]) < pivmin) q[p] = -pivmin;
-      c[p] = q[p] < 0.0;
-    }
+    // points in ascending order over the lanes
+    const double x = lo + (hi - lo) * (double)(sidx + 1) / (double)(G + 1);
+    double q = d[0] - x;
+    if (fabs(q) < pivmin) q = -pivmin;
+    int c = q < 0.0;
     auto step = [&](double di, double ei) {
-#pragma unroll
-      for (int p = 0; p < P; ++p) {
-        q[p] = fma(-ei, recip(q[p]), di - x[p]);
-        if (fabs(q[p]) < pivmin) q[p] = -pivmin;
-        c[p] += q[p] < 0.0;
-      }
+      q = fma(-ei, recip(q), di - x);
+      if (fabs(q) < pivmin) q = -pivmin;
+      c += q < 0.0;
     };
     // d and e^2 a chunk ahead of the recurrence
     constexpr int CH = 8;
@@ -155,17 +146,10 @@ __device__ __forceinline__ void eig_bisect_body(const EigView& m, int wg, double
     }
     for (; i < n; ++i) step(d[i], e2[i - 1]);
     // points whose count is at most j lie below the eigenvalue
-    int cnt = 0;
-#pragma unroll
-    for (int p = 0; p < P; ++p) cnt += __popcll(__ballot((!done && c[p] <= j) ? 1 : 0) & gmask);
-    double plo = lo, phi = hi;
-#pragma unroll
-    for (int p = 0; p < P; ++p) {
-      const double a = __shfl(x[p], base + ((cnt - 1) & (G - 1)), 64);
-      const double z = __shfl(x[p], base + (cnt & (G - 1)), 64);
-      if (cnt > 0 && (cnt - 1) / G == p) plo = a;
-      if (cnt < G * P && cnt / G == p) phi = z;
-    }
+    const int cnt = __popcll(__ballot((!done && c <= j) ? 1 : 0) & gmask);
+    const double a = __shfl(x, base + ((cnt - 1) & (G - 1)), 64);
+    const double z = __shfl(x, base + (cnt & (G - 1)), 64);
+    const double plo = cnt > 0 ? a : lo, phi = cnt < G ? z : hi;
     if (!done) {
       if (plo == lo && phi == hi) done = true;
       lo = plo;

@@ -928,95 +928,10 @@ __host__ __device__ void tridiag_lowest(T& t, const double* d, const double* e, 
 }
 
 // Z <- H_0 H_1 ... H_{n-3} Z for the reflectors left by the tridiagonalisation
-// (Z is n x k).  Reflectors go through LDS in blocks; on the device each wave
-// holds one column of Z in registers while it applies a block (n <= 768).
-// Device back-transformation Z := H_0 ... H_{n-3} Z for n <= 64 R: reflectors
-// staged in LDS sixteen at a time (applied last to first), each wave carries
-// U columns of Z in registers (R entries per lane) through a batch, so that
-// U independent dot-product chains share every reflector load.
-template <int R, int U, class T>
-__device__ __forceinline__ void bt_fast(T& t, const double* A, int lda, const double* tau, int n,
-                                        double* Z, int ldz, int k, double* lds, int lds_size) {
-  const int lane = t.tid() & 63, wv = t.tid() >> 6, nw = (t.nt() + 63) >> 6;
-  // reflector block in lds[0, NB n), its tau values in lds[NB n, NB n + NB)
-  int NB = (lds_size - 16) / n;
-  NB = NB > 16 ? 16 : NB;
-  double* tl = lds + (long long)NB * n;
-  for (int kb = n - 3; kb >= 0; kb -= NB) {
-    int kl = kb - NB + 1 > 0 ? kb - NB + 1 : 0;   // reflectors kb, kb-1, ..., kl
-    // stage reflectors: lds[(kk - kl) * n + i] = v_kk[i] (zero above k+1)
-    for (int q = t.tid(); q < (kb - kl + 1) * n; q += t.nt()) {
-      int kk = kl + q / n, i = q % n;
-      lds[q] = (i >= kk + 1) ? gld(A + (long long)i + (long long)lda * kk) : 0.0;
-    }
-    for (int q = t.tid(); q < kb - kl + 1; q += t.nt()) tl[q] = gld(tau + kl + q);
-    t.sync();
-    for (int j0 = wv; j0 < k; j0 += U * nw) {
-      double z[U][R];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int j = j0 + u * nw;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          int i = lane + 64 * r;
-          z[u][r] = (j < k && i < n) ? gld(Z + (long long)i + (long long)ldz * j) : 0.0;
-        }
-      }
-      for (int kk = kb; kk >= kl; --kk) {
-        double tk = tl[kk - kl];
-        if (tk == 0.0) continue;
-        const double* v = lds + (kk - kl) * n;
-        double vv[R], s[U];
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          int i = lane + 64 * r;
-          vv[r] = i < n ? v[i] : 0.0;
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          s[u] = 0.0;
-#pragma unroll
-          for (int r = 0; r < R; ++r) {
-            int i = lane + 64 * r;
-            if (i < n) s[u] += vv[r] * z[u][r];
-          }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) s[u] = wave_sum_dpp(s[u]);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          s[u] *= tk;
-#pragma unroll
-          for (int r = 0; r < R; ++r) {
-            int i = lane + 64 * r;
-            if (i < n) z[u][r] -= s[u] * vv[r];
-          }
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int j = j0 + u * nw;
-        if (j >= k) break;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          int i = lane + 64 * r;
-          if (i < n) gst(Z + (long long)i + (long long)ldz * j, z[u][r]);
-        }
-      }
-    }
-    t.sync();
-  }
-}
-
+// (Z is n x k), one at a time.  lds: k doubles.
 template <class T>
 __host__ __device__ void backtransform(T& t, const double* A, int lda, const double* tau, int n,
-                                       double* Z, int ldz, int k, double* lds, int lds_size) {
-  if constexpr (T::is_device) {
-    if (lds_size >= n + 16 && n <= 64 * 6) { bt_fast<6, 2>(t, A, lda, tau, n, Z, ldz, k, lds, lds_size); return; }
-    if (lds_size >= n + 16 && n <= 64 * 7) { bt_fast<7, 2>(t, A, lda, tau, n, Z, ldz, k, lds, lds_size); return; }
-    if (lds_size >= n + 16 && n <= 64 * 12) { bt_fast<12, 1>(t, A, lda, tau, n, Z, ldz, k, lds, lds_size); return; }
-  }
-  // generic path
+                                       double* Z, int ldz, int k, double* lds) {
   double* cs = lds;
   for (int kk = n - 3; kk >= 0; --kk) {
     double tk = tau[kk];
@@ -1039,7 +954,7 @@ __host__ __device__ void backtransform(T& t, const double* A, int lda, const dou
 
 // Lowest k eigenpairs of the symmetric A (lower triangle read, destroyed):
 // w[0..k) ascending, Z (n x k).  work: 9 n + 6 n k doubles; cl: k ints
-// (global); lds: >= 2n doubles (and >= k for the generic back-transform).
+// (global); lds: >= 2n doubles.
 template <class T>
 __host__ __device__ void syev_lowest(T& t, double* A, int lda, int n, int k, double* w, double* Z,
                                      int ldz, double* work, int* cl, double* lds, int lds_size) {
@@ -1048,7 +963,7 @@ __host__ __device__ void syev_lowest(T& t, double* A, int lda, int n, int k, dou
   double* tau = work + 2 * n;
   tridiagonalize_lower(t, A, lda, n, d, e, tau, lds, lds + n);
   tridiag_lowest(t, d, e, n, k, w, Z, ldz, work + 3 * n, cl, lds, lds_size);
-  backtransform(t, A, lda, tau, n, Z, ldz, k, lds, lds_size);
+  backtransform(t, A, lda, tau, n, Z, ldz, k, lds);
 }
 
 }  // namespace dg
