@@ -208,10 +208,19 @@ constexpr int TRI_STEP_THREADS_S = 512;    // the others
 constexpr int TRI_NWG_MAX = 16;
 constexpr int TRI_NWG_S = 8;
 // Workgroups per matrix: by its order alone, so that a matrix gives the same
-// result in any batch.  Measured (all stages): 16 matrices of order 816 21.8 ms
-// on 8 workgroups, 17.8 on 16; 8 of order 432 8.9 on 4, 6.7 on 8; 100 of order
-// 480 16.9 on 4, 18.8 on 8 (19.9 on 4 and 25.3 on 8 of 1024 lanes, of which
-// only one fits a compute unit).
+// result in any batch; the rule has to serve few matrices, where a step is
+// latency and more workgroups shorten it, and many, where the card is full and
+// fewer have less to repeat.  Orders up to 512 on 8 and on 4 (all stages, ms):
+//   count       1            32            64            100           200
+//   300     2.63  3.24    3.59  4.10    4.32  4.73    5.96  5.53    9.34  8.92
+//   432     4.87  6.65    7.02  8.79    8.64  9.38   12.8  11.7    21.3  20.3
+//   480     5.94  8.26    8.46 10.7    10.6  11.6    15.9  14.5    26.9  25.9
+//   512     6.66  9.38    9.34 11.8    12.1  13.0    18.8  17.2    31.7  30.7
+// 8 costs at most 9% (100 matrices, which fill the card one and a half times) and
+// saves up to 29%; six lie between.  (200 of order 432: one workgroup per matrix
+// 24.4.)  Above 512, 16 of order 816: 21.8 ms on 8 workgroups, 17.8 on 16 (before
+// tri_tail).  Workgroups of 1024 lanes up to order 512 instead of 512: 100 of order
+// 480 19.9 on 4 and 25.3 on 8, only one of them fits a compute unit.
 __host__ __device__ inline int tri_nwg(int n) { return n <= TRI_STEP_SPLIT ? TRI_NWG_S : TRI_NWG_MAX; }
 __host__ __device__ inline int tri_step_ncw(int n) { return n / tri_nwg(n) + 1; }
 // (grows with n, so the largest order of a launch sizes it for all)
