@@ -191,11 +191,12 @@ int32_t dgdft_alb_sizes(const dgdft_alb* h, int32_t elem, int64_t* ng, int64_t* 
                         int32_t* n_states, int32_t* n_alb, int64_t* offsets);
 
 /* Tuned parameters of element `elem` (host outputs, nullable): the split-K
- * chunk count of its N_g-long Gram products (0 = the default rule). */
+ * chunk count of its N_g-long Gram products (0 = the default rule; 8 = 8 or
+ * what the default rule gives, if that is more). */
 int32_t dgdft_alb_get_tuning(const dgdft_alb* h, int32_t elem, int32_t* gram_split);
 
 /* Cached tuning: set element `elem`'s split-K chunk count (0 = the default
- * rule, else 1..8), e.g. a value dgdft_alb_get_tuning returned for a
+ * rule, else 1..8, of which 8 stands for at least 8, see above), e.g. a value dgdft_alb_get_tuning returned for a
  * handle of the same element shapes created with opts.tune = 1, so that a
  * new handle skips the timing runs.  The three tuning modes are thus: off
  * (opts.tune = 0), full (opts.tune = 1), cached (opts.tune = 0, then this

@@ -1085,7 +1085,8 @@ static void grid_shells(const Elem& E, std::vector<int>& shell_of, std::vector<d
 
 // Autotuner: for each element shape (N_g, J), time the Rayleigh-Ritz Gram
 // product (S^T [S, HS] upper triangles, S = three N_g x J blocks) with 1, 2,
-// 4 and 8 split-K chunks on a representative element and keep the fastest
+// 4 and 8 (or, if more, the default rule's) split-K chunks on a representative
+// element and keep the fastest
 // for every element of that shape.  Contents of the blocks do not matter.
 static void tune_gram(dgdft_alb* h) {
   std::vector<std::pair<long long, int>> shapes;

@@ -57,10 +57,45 @@ int main() {
 """
 
 
-def test_grid_covers_every_state(tmp_path):
+TUNED = r"""
+#include <cstdio>
+#include "common.h"
+using namespace dg;
+
+int main() {
+  for (int K : {15, 100, 1728, 13824, 55296, 110592})
+    for (int J = 1; J <= 272; ++J) {
+      Elem e{};
+      e.J = J;
+      e.ng = K;
+      e.gpart_cap = 16LL * (3 * J) * (3 * J);
+      const int dflt = gram_nchunk_e(e, K, 3 * J, J, 2 * J);
+      for (int split = 1; split <= 8; ++split) {
+        e.gram_split = split;
+        const int c = gram_nchunk_e(e, K, 3 * J, J, 2 * J), most = cdiv(K, 16);
+        const int want = split < most ? split : most;
+        if (c != (split < 8 || want > dflt ? want : dflt)) std::printf("K %d J %d split %d: %d\n", K, J, split, c);
+        if ((long long)c * 3 * J * 2 * J > e.gpart_cap) std::printf("K %d J %d split %d: partials\n", K, J, split);
+      }
+    }
+  std::printf("done\n");
+}
+"""
+
+
+def _run(text, tmp_path):
     src, exe = tmp_path / "items.hip", tmp_path / "items"
-    src.write_text(SRC)
+    src.write_text(text)
     subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "-std=c++17", "-O1", "--offload-host-only",
                     "-I" + os.path.join(ROOT, "paper_1506_08147_amd", "csrc"), str(src), "-o", str(exe)], check=True)
-    lines = subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.strip().split("\n")
+    return subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.strip().split("\n")
+
+
+def test_grid_covers_every_state(tmp_path):
+    lines = _run(SRC, tmp_path)
     assert len(lines) == 1 and lines[0].endswith("items"), lines[:5]
+
+
+def test_tuned_chunk_counts(tmp_path):
+    """Exactly the tuned count, of which the largest is never below the default."""
+    assert _run(TUNED, tmp_path) == ["done"]
